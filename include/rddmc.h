@@ -192,8 +192,8 @@ typedef struct {
  *   chunk        steps between refills of finished lanes (0 = automatic).
  *   tail_lanes   once every packet of the run has started, a wave with at most this many
  *                packets left hands them to a cooperative walk in which a whole wave
- *                advances one packet (0 = automatic (16), < 0 = never).  Results are
- *                bit-identical either way.
+ *                advances one packet (0 = automatic: 16, up to 64 in runs too small to
+ *                occupy the device; < 0 = never).  Results are bit-identical either way.
  *   surrogate    1D clouds: learned escape surrogate (rddmc_surrogate_attach), exact exit
  *                kernel (rddmc_exitkernel_build) or NULL for plain rDDMC; with one, a packet
  *                in a state of its cloud's window leaves the cell by one exit drawn from that

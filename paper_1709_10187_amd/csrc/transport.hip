@@ -35,7 +35,7 @@ struct WalkArgs {
     int32_t chunk;
     int32_t n_clouds;
     int32_t tail_lanes;    // export a wave's packets once the queue is empty and <= this many remain
-    int32_t pad;
+    int32_t one_round;     // the producers have a lane for every packet: the queue is empty after one refill
     uint64_t tail_capacity;
     const uint8_t *surr;   // learned escape surrogate (windows and records) or null
     uint32_t producer_blocks;   // blocks [0, producer_blocks) walk packets from the queue;
@@ -43,15 +43,16 @@ struct WalkArgs {
 };
 
 // Work area (u64 words, the polled ones on their own 128-byte lines): [0] packet queue
-// counter, [16] export slots handed out, [17] slots claimed by consumer waves of the
-// lane-walk launch, [18] producer waves finished, [24] slots claimed by the closing
+// counter, [8] export slots handed out, [16] tickets taken by consumer waves of the
+// lane-walk launch, [24] producer waves finished, [25] slots claimed by the closing
 // cooperative kernel; export slots start at byte kWorkHeaderBytes.
 constexpr uint64_t kWorkHeaderBytes = 256;
-constexpr int kWGiven = 16, kWClaimed = 17, kWDone = 18, kWSweep = 24;
+constexpr int kWGiven = 8, kWClaimed = 16, kWDone = 24, kWSweep = 25;
 
 // One exported packet.  `flag` moves empty -> ready (published by the exporting lane) ->
 // taken (claimed by a walking wave), or empty -> abandoned (a consumer claimed the slot
-// before its packet was published and moved on; the exporter then walks it itself).
+// before its packet was published and moved on) -> ready again (the exporter leaves the packet to
+// the closing kernel) -> taken.
 struct TailPacket {        // 48 bytes
     uint32_t cl, pid;
     int32_t i, j;
@@ -61,13 +62,9 @@ struct TailPacket {        // 48 bytes
     uint64_t pad1;
 };
 constexpr uint32_t kSlotEmpty = 0u, kSlotReady = 1u, kSlotTaken = 2u, kSlotAbandoned = 3u;
-// A consumer wave with nothing to claim polls every 32 x s_sleep 127 (about 0.1 ms) and
-// gives up after this many polls in a row (about 100 s); in normal operation it leaves
-// much earlier, as soon as every producer wave has finished.
-constexpr int kConsumerIdlePolls = 1000000;
-// A consumer that claims a slot not yet published re-reads its flag at most this many times
-// (s_sleep 2 apart, ~0.2 ms in all) before leaving the packet to its exporter.
-constexpr int kPublishWaitPolls = 4096;
+// Polls of one export slot before a consumer wave gives up on it (about 100 s); in normal
+// operation it leaves much earlier, as soon as every producer wave has finished.
+constexpr int kConsumerPolls = 2000000;
 
 // Domain tags in the second counter word (high bits of the step index never reach them).
 constexpr uint32_t kDomAux = 0x80000000u;   // extra draws inside step k (re-binning, escape)
@@ -406,42 +403,6 @@ __device__ __forceinline__ StepWords words_of_step(const Packet1D &p, uint64_t s
     return (step & 1) ? StepWords{r.z, r.w, 0u, 0u} : StepWords{r.x, r.y, 0u, 0u};
 }
 
-// A few single steps of one packet (lane-walk arithmetic), used by the cooperative walk on
-// static media where spatial leaks dominate (moving media use moving_steps).
-template <bool MOVING>
-__device__ void single_steps(Packet1D &p, int n, const uint8_t *__restrict__ tb,
-                             const DevCloud *__restrict__ clouds, const WalkArgs &a,
-                             unsigned long long *__restrict__ tally)
-{
-    for (int k = 0; k < n && p.active && p.steps < a.max_steps; ++k) {
-        const StepWords w = words_of_step<MOVING>(p, p.steps, a);
-        const uint4 rec = p.hot[p.i * p.nb + p.j];
-        const float4 cm = (MOVING && p.moving) ? p.cmap[p.i] : make_float4(1.f, 0.f, 1.f, 0.f);
-        one_step<MOVING>(p, w, rec, cm, tb, clouds, a, tally);
-    }
-}
-
-// Single steps of one packet with the lane walk's surrogate exits (a step that starts in the
-// window is replaced by one exit, at the lane walk's check points), used by the cooperative
-// walk where spatial leaks dominate.
-template <bool MOVING>
-__device__ void surr_single_steps(Packet1D &p, int n, const SurrWin &sw, const float *__restrict__ recs,
-                                  const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
-                                  const WalkArgs &a, unsigned long long *__restrict__ tally)
-{
-    for (int k = 0; k < n && p.active && p.steps < a.max_steps; ++k) {
-        const bool chk = (MOVING && p.moving) || !(p.steps & 1ull);
-        if (chk && p.steps + 3ull <= a.max_steps && in_window(p, sw)) {
-            surrogate_exit<MOVING>(p, sw, recs, tb, clouds[p.cl], a);
-            continue;
-        }
-        const StepWords w = words_of_step<MOVING>(p, p.steps, a);
-        const uint4 rec = p.hot[p.i * p.nb + p.j];
-        const float4 cm = (MOVING && p.moving) ? p.cmap[p.i] : make_float4(1.f, 0.f, 1.f, 0.f);
-        one_step<MOVING>(p, w, rec, cm, tb, clouds, a, tally);
-    }
-}
-
 // One step's fast path as selects (no branches): the clock advances for every enabled lane;
 // a frequency move or a spatial move inside the grid is applied; returns true when the step
 // needs the slow path (a tie with a threshold's high word, or a leak out of the grid), which
@@ -589,6 +550,11 @@ __device__ __forceinline__ uint32_t rl(uint32_t v, int lane)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
+// v with `s` (wave-uniform) in lane `lane`: the compiler has no builtin for v_writelane_b32, and
+// only the intrinsic lets it place the wait states after the instruction that wrote `s`
+extern "C" __device__ int amdgcn_writelane_i32(int s, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ int write_lane(int s, int lane, int v) { return amdgcn_writelane_i32(s, lane, v); }
+
 __device__ __forceinline__ TailPacket *slots_of(unsigned long long *work)
 {
     return reinterpret_cast<TailPacket *>(reinterpret_cast<uint8_t *>(work) + kWorkHeaderBytes);
@@ -625,69 +591,50 @@ __device__ Packet1D load_slot(const TailPacket *ts, const uint8_t *__restrict__ 
     return q;
 }
 
-// A consumer wave (a block past the producers) walks handed-over packets cooperatively,
-// one after another.  It claims only slot indices already handed out (a CAS on the claim
-// counter bounded by the hand-out counter: each failed CAS means another wave claimed one,
-// so the retries end); a claimed slot whose packet is not yet published is marked abandoned
-// (its exporter walks it).  With nothing to claim it exits once every producer wave has
-// finished, or after kConsumerIdlePolls polls; what it leaves, the closing kernel walks.
+// A consumer wave (a block past the producers) walks handed-over packets cooperatively, one after
+// another.  It takes a ticket, the index of the export slot it will walk next, with one atomic
+// add, and polls that slot alone: claiming the next published slot by compare-and-swap on a
+// shared counter let a few thousand waves fail against one that succeeded, ~25 us per claim.
+// (The efficient-grid sphere of 64 shells, 6e4 packets: 390 ms with the shared claim, 5.5 ms with
+// tickets.)  Polls start about 1 us apart and double to about 50 us; they are relaxed (an acquire would
+// invalidate the compute unit's vector cache under the waves that still walk there).  Before every poll the wave reads how
+// many producer waves have finished: once all have, a slot that was never handed out ends the
+// wave, and one that was is already published.  After kConsumerPolls polls of one slot the wave
+// marks it abandoned and leaves; what is left, the closing kernel walks.
 template <bool MOVING, bool SURR>
 __device__ void consume_exported(const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
                                  const WalkArgs &a, unsigned long long *__restrict__ tally,
                                  unsigned long long *__restrict__ work, int lane)
 {
     TailPacket *slots = slots_of(work);
-    constexpr uint64_t kNone = ~0ull;
-    int idle = 0;
     for (;;) {
-        uint64_t idx = kNone;
-        uint32_t done = 0u;
-        if (lane == 0) {
-            for (;;) {
-                const uint64_t taken = __hip_atomic_load(&work[kWClaimed], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint64_t given = __hip_atomic_load(&work[kWGiven], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (taken >= given || taken >= a.tail_capacity) {
-                    done = __hip_atomic_load(&work[kWDone], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
-                                   (unsigned long long)a.producer_waves
-                               ? 1u
-                               : 0u;
-                    break;
-                }
-                unsigned long long expect = taken;
-                if (__hip_atomic_compare_exchange_strong(&work[kWClaimed], &expect, taken + 1ull, __ATOMIC_RELAXED,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                    idx = taken;
-                    break;
-                }
-            }
-        }
-        idx = shfl_u64(idx, 0);
-        if (idx == kNone) {
-            if (rl(done, 0) != 0u || ++idle > kConsumerIdlePolls) return;
-            for (int z = 0; z < 32; ++z) __builtin_amdgcn_s_sleep(127);
-            continue;
-        }
-        idle = 0;
+        uint64_t idx = 0;
         uint32_t got = 0u;
         if (lane == 0) {
-            // the exporter hands the slot out just before it writes and publishes it: give it
-            // a bounded moment, then take the packet or leave it to the exporter
-            uint32_t *f = &slots[idx].flag;
-            int tries = 0;
-            while (__hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == kSlotEmpty &&
-                   ++tries < kPublishWaitPolls)
-                __builtin_amdgcn_s_sleep(2);
-            uint32_t expect = kSlotEmpty;
-            if (!__hip_atomic_compare_exchange_strong(f, &expect, kSlotAbandoned, __ATOMIC_ACQ_REL, __ATOMIC_ACQUIRE,
-                                                      __HIP_MEMORY_SCOPE_AGENT) &&
-                expect == kSlotReady) {
-                got = __hip_atomic_compare_exchange_strong(f, &expect, kSlotTaken, __ATOMIC_ACQ_REL, __ATOMIC_ACQUIRE,
-                                                           __HIP_MEMORY_SCOPE_AGENT)
-                          ? 1u
-                          : 0u;
+            idx = __hip_atomic_fetch_add(&work[kWClaimed], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (idx < a.tail_capacity) {
+                uint32_t *f = &slots[idx].flag;
+                int nap = 1;
+                for (int poll = 0; poll < kConsumerPolls; ++poll) {
+                    const bool over = __hip_atomic_load(&work[kWDone], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
+                                      (unsigned long long)a.producer_waves;
+                    if (over) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    if (__hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kSlotReady) {
+                        got = 1u;
+                        break;
+                    }
+                    if (over) break;
+                    for (int z = 0; z < nap; ++z) __builtin_amdgcn_s_sleep(32);
+                    nap = nap < 64 ? 2 * nap : 64;
+                }
+                uint32_t expect = got ? kSlotReady : kSlotEmpty;
+                if (__hip_atomic_compare_exchange_strong(f, &expect, got ? kSlotTaken : kSlotAbandoned, __ATOMIC_ACQ_REL,
+                                                         __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == false)
+                    got = 0u;
             }
         }
-        if (rl(got, 0) == 0u) continue;
+        if (rl(got, 0) == 0u) return;
+        idx = ((uint64_t)rl((uint32_t)(idx >> 32), 0) << 32) | rl((uint32_t)idx, 0);
         Packet1D q = load_slot(slots + idx, tb, clouds);
         coop_walk<MOVING, SURR>(q, tb, clouds, a, tally, lane);
     }
@@ -730,7 +677,7 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
                 uint64_t base = 0;
                 if (lane == leader) base = atomicAdd(work, (unsigned long long)cnt);
                 base = shfl_u64(base, leader);
-                if (base + cnt >= a.count) exhausted = true;
+                if (base + cnt >= a.count || a.one_round) exhausted = true;
                 if (!p.active) {
                     const int rank = __popcll(need & ((1ull << lane) - 1ull));
                     const uint64_t q = base + rank;
@@ -806,14 +753,11 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     p.active = false;
                 }
-                // slots a consumer claimed before they were published: walk them here
-                uint64_t mine = __ballot(keep);
-                while (mine) {
-                    const int l = __ffsll((unsigned long long)mine) - 1;
-                    mine &= mine - 1ull;
-                    const uint64_t slot = base + __popcll(live & ((1ull << l) - 1ull));
-                    Packet1D q = load_slot(slots_of(work) + slot, tb, clouds);
-                    coop_walk<MOVING, SURR>(q, tb, clouds, a, tally, lane);
+                // slots a consumer gave up on before they were published (its claim is spent, so no
+                // other consumer looks at them): published again for the closing kernel
+                if (keep) {
+                    TailPacket *tp = slots_of(work) + base + __popcll(live & ((1ull << lane) - 1ull));
+                    __hip_atomic_store(&tp->flag, kSlotReady, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 break;
             }
@@ -950,6 +894,208 @@ __device__ __forceinline__ void clock_from(double &t, uint32_t dlo, uint32_t dhi
     }
 }
 
+// The packet as lane 0 left it, made wave-uniform again.
+template <bool SURR>
+__device__ __forceinline__ void take_lane0(Packet1D &q, const Packet1D &s1)
+{
+    q.i = (int)rl((uint32_t)s1.i, 0);
+    q.j = (int)rl((uint32_t)s1.j, 0);
+    q.steps = ((uint64_t)rl((uint32_t)(s1.steps >> 32), 0) << 32) | rl((uint32_t)s1.steps, 0);
+    const uint64_t tbits = (uint64_t)__double_as_longlong(s1.t);
+    q.t = __longlong_as_double((long long)(((uint64_t)rl((uint32_t)(tbits >> 32), 0) << 32) | rl((uint32_t)tbits, 0)));
+    q.active = rl(s1.active ? 1u : 0u, 0) != 0u;
+    if (SURR) q.surr_calls = rl(s1.surr_calls, 0);
+}
+
+// ---- blocks of mixed steps -------------------------------------------------------------------
+// Where spatial leaks are frequent the table scan above stops after a few steps.  A mixed block
+// holds a window of states around the packet instead, one state per lane: 2^(6-b) cells x 2^b
+// bins, lane = (cell - wi) 2^b + (bin - wj).  For step k every lane computes where that step
+// would take a packet of ITS state (the event word is wave-uniform), and the packet's position
+// follows by one readlane: p <- next[p].  Lane 63 is the stop: its own next position is 63, and
+// a move out of the window or the grid, and (with the surrogate) a step that starts in the
+// surrogate window at a check point, lead to it.  Ties with a threshold's high word are found
+// after the chain, when lane k holds step k's position and its records, and cut the block.
+// The step a block stops at is taken with the lane walk's arithmetic.
+// Bound: instruction issue of one wave, 9 vector instructions per step (about 25 with a Doppler
+// re-binning), and per block ~250 for the words, the window and the clock.  The static slab of 9
+// cells x 17 bins (tau0 = 300, 3e4 packets) takes 5.0 ms where lane 0 walking such runs alone took
+// 157 ms (with the claims below); the slowest packet of a 40 x 50 sphere (3.1e5 steps) 58 ns per step.
+struct MixWindow {
+    int b, wi, wj;                             // shape and corner
+    uint32_t lk, dhi, shi, fhi;                // the lane's record
+    int dn, up, lo, hi;                        // where the four moves lead (63: stop)
+    float4 cm;                                 // the Doppler map of the lane's cell
+    bool id0, id1;                             // identity across face 0 / face 1
+};
+
+template <bool MOVING>
+__device__ __forceinline__ void mix_load(MixWindow &w, const Packet1D &q, int b, int lane)
+{
+    const int wjn = 1 << b, win = 64 >> b;
+    int wi = q.i - (win >> 1), wj = q.j - (wjn >> 1);
+    if (wi > q.nc - win) wi = q.nc - win;
+    if (wi < 0) wi = 0;
+    if (wj > q.nb - wjn) wj = q.nb - wjn;
+    if (wj < 0) wj = 0;
+    if (((q.i - wi) << b) + (q.j - wj) == 63) ++wj;   // the packet's own state needs a lane
+    w.b = b;
+    w.wi = wi;
+    w.wj = wj;
+    const int il = lane >> b, jl = lane & (wjn - 1);
+    const int i = wi + il, j = wj + jl;
+    const bool in = i < q.nc && j < q.nb;
+    const uint4 r = q.hot[in ? i * q.nb + j : 0];
+    w.lk = r.x;
+    w.dhi = r.y;
+    w.shi = r.z;
+    w.fhi = r.w;
+    const bool live = in && lane < 63;
+    w.dn = live && jl > 0 ? lane - 1 : 63;
+    w.up = live && jl < wjn - 1 && j + 1 < q.nb ? lane + 1 : 63;
+    w.lo = live && il > 0 ? lane - wjn : 63;
+    w.hi = live && il < win - 1 && i + 1 < q.nc ? lane + wjn : 63;
+    if (MOVING && q.moving) {
+        w.cm = q.cmap[in ? i : 0];
+        w.id0 = w.cm.x == 1.0f && w.cm.y == 0.0f;
+        w.id1 = w.cm.z == 1.0f && w.cm.w == 0.0f;
+    }
+}
+
+// Step k of the chain: every lane's next position, then the packet's.
+template <bool MOVING, bool SURR>
+__device__ __forceinline__ void mix_step(const MixWindow &w, const Packet1D &q, bool rebins, int k, uint32_t ew, float u,
+                                         bool stop_here, int lane, int &p, int &post)
+{
+    const uint32_t e = rl(ew, k);
+    const int f = e < w.dhi ? w.dn : w.up;
+    const bool inner = e < w.fhi;
+    int x = inner ? w.lo : w.hi;
+    if (MOVING && rebins) {
+        const float uk = __uint_as_float(rl(__float_as_uint(u), k));
+        const int j = w.wj + (lane & ((1 << w.b) - 1));
+        const float xj = __fmaf_rn(__fadd_rn((float)j, uk), q.dx, q.x0);
+        const float rho = inner ? w.cm.x : w.cm.z, sh = inner ? w.cm.y : w.cm.w;
+        int jn = (int)floorf(__fmul_rn(__fsub_rn(__fmaf_rn(rho, xj, sh), q.x0), q.inv_dx));
+        jn = jn < 0 ? 0 : (jn > q.nb - 1 ? q.nb - 1 : jn);
+        const int moved = x + (jn - j);   // x: the same bin of the neighbour
+        const bool out = x == 63 || (unsigned)(jn - w.wj) >= (1u << w.b) || moved == 63;
+        x = (inner ? w.id0 : w.id1) ? x : (out ? 63 : moved);
+    }
+    int n = e < w.shi ? f : x;
+    if (SURR) n = stop_here ? 63 : n;
+    p = (int)rl((uint32_t)n, p);
+    post = write_lane(p, k, post);
+}
+
+template <bool MOVING, bool SURR, int G>
+__device__ __forceinline__ void mix_from(const MixWindow &w, const Packet1D &q, bool rebins, uint32_t ew, float u,
+                                         bool stop_even, bool stop_odd, int lane, int &p, int &post)
+{
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        mix_step<MOVING, SURR>(w, q, rebins, 8 * G + k, ew, u, (k & 1) ? stop_odd : stop_even, lane, p, post);
+    if constexpr (G < 7) {
+        if (p != 63) mix_from<MOVING, SURR, G + 1>(w, q, rebins, ew, u, stop_even, stop_odd, lane, p, post);
+    }
+}
+
+// The window's shape for the recent share of spatial leaks: a walk leaves a window of W cells
+// and V bins after about W^2 / 4s or V^2 / 4f steps (s, f the shares of spatial and frequency
+// steps), equal at V / W = sqrt(f / s); of the shapes V / W = 16, 4, 1, 1/4, 1/16 the nearest,
+// no dimension more than needed to cover the grid.
+__device__ __forceinline__ int mix_shape(const Packet1D &q, int nt, int ns)
+{
+    const int nf = nt - ns;
+    int b = nf >= 64 * ns ? 5 : (nf >= 4 * ns ? 4 : (4 * nf >= ns ? 3 : (64 * nf >= ns ? 2 : 1)));
+    while (b > 1 && (1 << (b - 1)) >= q.nb) --b;
+    while (b < 5 && (32 >> b) >= q.nc) ++b;
+    return b;
+}
+
+// One mixed block of up to 64 steps (at least 68 steps below the step cap).  Adds the block's
+// steps and spatial leaks to `nt` and `ns`.
+template <bool MOVING, bool SURR>
+__device__ __forceinline__ void mix_block(Packet1D &q, int b, const SurrWin &sw, const float *__restrict__ recs,
+                                          const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
+                                          const WalkArgs &a, unsigned long long *__restrict__ tally, int lane,
+                                          int &nt, int &ns)
+{
+    MixWindow w;
+    mix_load<MOVING>(w, q, b, lane);
+    const bool mv = MOVING && q.moving;
+    const StepWords wl = words_of_step<MOVING>(q, q.steps + (uint64_t)lane, a);
+    const float u = __fmul_rn(__fadd_rn((float)(wl.z >> 8), 0.5f), 5.9604644775390625e-8f);   // as rebin_uniform
+    bool stop_even = false, stop_odd = false;
+    if (SURR) {   // surrogate exits: every step in moving media, even step counts in static ones
+        const int i = w.wi + (lane >> b), j = w.wj + (lane & ((1 << b) - 1));
+        const bool in = (unsigned)(i - sw.i_lo) <= (unsigned)(sw.i_hi - sw.i_lo) &&
+                        (unsigned)(j - sw.j_lo) <= (unsigned)(sw.j_hi - sw.j_lo);
+        stop_even = in && (mv || !(q.steps & 1ull));
+        stop_odd = in && (mv || (q.steps & 1ull));
+    }
+    const int p0 = ((q.i - w.wi) << b) + (q.j - w.wj);
+    int p = (int)rl((uint32_t)p0, 0), post = 63;
+    if (mv)   // on a uniform grid (the caller's choice)
+        mix_from<MOVING, SURR, 0>(w, q, true, wl.e, u, stop_even, stop_odd, lane, p, post);
+    else
+        mix_from<MOVING, SURR, 0>(w, q, false, wl.e, u, stop_even, stop_odd, lane, p, post);
+    // lane k: the position step k starts from, and that state's record
+    int pre = __shfl_up(post, 1);
+    if (lane == 0) pre = p0;
+    const uint32_t lk = (uint32_t)__shfl((int)w.lk, pre);
+    const uint32_t dh = (uint32_t)__shfl((int)w.dhi, pre), sh = (uint32_t)__shfl((int)w.shi, pre);
+    const uint32_t fh = (uint32_t)__shfl((int)w.fhi, pre);
+    const bool tie = wl.e == dh || wl.e == sh || wl.e == fh;
+    const uint64_t stops = __ballot(post == 63 || tie);
+    const int done = stops ? __ffsll((unsigned long long)stops) - 1 : 64;
+    const int pos = done < 64 ? (int)rl((uint32_t)pre, done) : (int)rl((uint32_t)post, 63);
+    const double dd = lane < done ? (double)path_length(wl.t, __uint_as_float(lk)) : 0.0;
+    double t = q.t;                    // the lane walk's FP64 additions, same bits
+    if (done > 0 && !clock_parallel(t, dd))
+        clock_from<0>(t, (uint32_t)__double_as_longlong(dd), (uint32_t)((uint64_t)__double_as_longlong(dd) >> 32), done);
+    q.t = t;
+    q.steps += (uint64_t)done;
+    q.i = w.wi + (pos >> b);
+    q.j = w.wj + (pos & ((1 << b) - 1));
+    nt += done;
+    ns += __popcll(__ballot(lane < done && wl.e >= sh));
+    if (done == 64) return;
+    // the step the block stopped at, taken by the whole wave with the lane walk's selects; a
+    // surrogate exit, a tie or an escape runs in lane 0
+    Packet1D s1 = q;
+    bool exits = false;
+    if (SURR) {
+        const bool chk = mv || !(q.steps & 1ull);
+        if (chk && in_window(q, sw)) {
+            exits = true;
+            if (lane == 0) surrogate_exit<MOVING>(s1, sw, recs, tb, clouds[s1.cl], a);
+        }
+    }
+    if (!exits) {
+        const StepWords ws = {rl(wl.t, done), rl(wl.e, done), rl(wl.z, done), rl(wl.w, done)};
+        const uint4 rec = make_uint4(rl(w.lk, pos), rl(w.dhi, pos), rl(w.shi, pos), rl(w.fhi, pos));
+        float4 cm = make_float4(1.f, 0.f, 1.f, 0.f);
+        bool slow;
+        int d;
+        if (mv) {
+            cm = make_float4(__uint_as_float(rl(__float_as_uint(w.cm.x), pos)),
+                             __uint_as_float(rl(__float_as_uint(w.cm.y), pos)),
+                             __uint_as_float(rl(__float_as_uint(w.cm.z), pos)),
+                             __uint_as_float(rl(__float_as_uint(w.cm.w), pos)));
+            slow = select_step_moving(s1, true, ws, rec, cm, clouds, tb);
+        } else {
+            slow = select_step(s1, true, ws.t, ws.e, rec, d);
+        }
+        ++nt;
+        ns += ws.e >= rec.z ? 1 : 0;
+        if (__any(slow)) {
+            if (lane == 0) slow_step<MOVING>(s1, ws, rec, cm, tb, clouds, a, tally);
+        }
+    }
+    take_lane0<SURR>(q, s1);
+}
+
 template <bool MOVING, bool SURR>
 __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
                           const WalkArgs &a, unsigned long long *__restrict__ tally, int lane)
@@ -966,7 +1112,9 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
         sw = SurrWin{scl->i_lo, scl->i_hi, scl->j_lo, scl->j_hi, scl->rec_off};
     }
     int wi = -1, jb = 0;
-    int short_run = 0;   // consecutive blocks stopped by a slow-path step within 16 steps
+    int short_run = 0;   // consecutive table blocks stopped by a slow-path step within 16 steps
+    bool mixed = false;
+    int nt = 0, ns = 0;  // recent steps and spatial leaks (mixed blocks)
     uint32_t v_lk = 0u, v_dhi = 0u, v_shi = 0u, v_fhi = 0u;
     while (q.active) {
         const uint64_t left = a.max_steps - q.steps;
@@ -974,6 +1122,24 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
             if (lane == 0) tally_finish(tally, clouds[q.cl], false, 0, 0, q.t, q.steps);
             q.active = false;
             break;
+        }
+        if (mixed && left >= 68 && MOVING && q.moving && !q.uniform) {
+            // re-binning on other grids searches the bin edges: lane 0 walks on alone for a while
+            Packet1D s1 = q;
+            const int n = left < 1024 ? (int)left : 1024;
+            if (lane == 0) moving_steps<SURR>(s1, n, n, tb, clouds, a, tally, &sw, recs);
+            take_lane0<SURR>(q, s1);
+            mixed = false;
+            continue;
+        }
+        if (mixed && left >= 68) {
+            mix_block<MOVING, SURR>(q, mix_shape(q, nt, ns), sw, recs, tb, clouds, a, tally, lane, nt, ns);
+            if (nt > 256) {   // forget older steps; back to table blocks where leaks are rare
+                mixed = 64 * ns > nt;
+                nt >>= 1;
+                ns >>= 1;
+            }
+            continue;
         }
         const int m = left < 64 ? (int)left : 64;
         // band of 64 bins around the packet (reloaded on a new cell or near its edges)
@@ -1044,7 +1210,7 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
             else chi |= two << (4 * (b - 8));
         }
         // sequential part: the chain of positions, in scalar registers, two steps at a time
-        uint32_t st = kScanWidth | ((uint32_t)(q.j - jw) << 2);
+        uint32_t st = rl(kScanWidth | ((uint32_t)(q.j - jw) << 2), 0);
         int vst = (int)kScanStop;
         scan_from<0>(st, vst, clo, chi);
         // each lane's starting position (odd lanes: one step from the even lane before);
@@ -1092,9 +1258,8 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
         q.j = jj;
         short_run = special && done < 16 ? short_run + 1 : 0;
         if (special) {
-            // the step at `done` in lane 0 with the lane walk's arithmetic; then, if several
-            // blocks in a row stopped early (spatial leaks dominate here), a run of single
-            // steps in lane 0, twice as long (up to 1024) for every further such block
+            // the step at `done` in lane 0 with the lane walk's arithmetic; several blocks in a
+            // row that stopped early (spatial leaks are frequent here) hand over to mixed blocks
             const int b = (jj - jb) & 63;
             const StepWords ws = {rl(wl.t, done), rl(ew, done), rl(wl.z, done), rl(wl.w, done)};
             const uint4 rec = make_uint4(rl(v_lk, b), rl(v_dhi, b), rl(v_shi, b), rl(v_fhi, b));
@@ -1104,28 +1269,15 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
             } else if (lane == 0) {
                 const float4 cm = (MOVING && s1.moving) ? s1.cmap[s1.i] : make_float4(1.f, 0.f, 1.f, 0.f);
                 one_step<MOVING>(s1, ws, rec, cm, tb, clouds, a, tally);
-                if (SURR && short_run >= 3) {
-                    surr_single_steps<MOVING>(s1, 64 << (short_run - 3 < 4 ? short_run - 3 : 4), sw, recs, tb,
-                                              clouds, a, tally);
-                } else if (short_run >= 3) {
-                    const int n = 64 << (short_run - 3 < 4 ? short_run - 3 : 4);
-                    if (MOVING && s1.moving) {
-                        const uint64_t left = s1.active ? a.max_steps - s1.steps : 0ull;
-                        const int budget = left < (uint64_t)n ? (int)left : n;
-                        moving_steps(s1, budget, budget, tb, clouds, a, tally);
-                    } else {
-                        single_steps<MOVING>(s1, n, tb, clouds, a, tally);
-                    }
-                }
             }
-            q.i = (int)rl((uint32_t)s1.i, 0);
-            q.j = (int)rl((uint32_t)s1.j, 0);
-            q.steps = ((uint64_t)rl((uint32_t)(s1.steps >> 32), 0) << 32) | rl((uint32_t)s1.steps, 0);
-            const uint64_t tbits = (uint64_t)__double_as_longlong(s1.t);
-            q.t = __longlong_as_double((long long)(((uint64_t)rl((uint32_t)(tbits >> 32), 0) << 32) |
-                                                   rl((uint32_t)tbits, 0)));
-            q.active = rl(s1.active ? 1u : 0u, 0) != 0u;
-            if (SURR) q.surr_calls = rl(s1.surr_calls, 0);
+            take_lane0<SURR>(q, s1);
+            if (short_run >= 2) {
+                mixed = true;
+                short_run = 0;
+                wi = -1;
+                nt = 64;
+                ns = 8;
+            }
         }
     }
     if (SURR && lane == 0 && q.surr_calls)
@@ -1267,10 +1419,10 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
     a.key1 = (uint32_t)(run.seed >> 32);
     a.chunk = run.chunk > 0 ? (run.chunk + 1) / 2 : 32;   // in pairs of steps
     a.n_clouds = h.n_clouds;
-    a.tail_lanes = run.tail_lanes == 0 ? 16 : (run.tail_lanes < 0 ? 0 : run.tail_lanes);
-    a.pad = 0;
+    a.tail_lanes = run.tail_lanes < 0 ? 0 : run.tail_lanes;
     a.tail_capacity = work_bytes > kWorkHeaderBytes ? (work_bytes - kWorkHeaderBytes) / sizeof(TailPacket) : 0;
     if (a.tail_capacity == 0) a.tail_lanes = 0;
+    a.one_round = 0;
     const int block = run.block > 0 ? run.block : 256;
     uint64_t grid = run.grid > 0 ? (uint64_t)run.grid : 0;
     if (grid == 0) {
@@ -1280,6 +1432,19 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
         if (grid < 1) grid = 1;
     }
     const uint64_t lanes = grid * (uint64_t)block;
+    if (run.tail_lanes == 0) {
+        // A SIMD's issue slots take a lane walk one step per live lane in ~460 cycles and a
+        // cooperative walk one step in 35-50, whatever the number of waves that share it: the
+        // hand-over pays once about 14 packets per SIMD are left.  A wave's own threshold is
+        // that number where the producers fill the SIMDs, more where they leave some idle (4096
+        // packets of the tau0 = 1e5 slab, 64 producer waves: 530 ms handed over at once, 971 ms at
+        // 16 per wave).
+        const uint64_t simds = 4ull * (uint64_t)device_cu_count(), waves = (lanes + 63) / 64;
+        const uint64_t t = 14 * simds / (waves < simds ? waves : simds);
+        a.tail_lanes = t < 16 ? 16 : (t > 64 ? 64 : (int)t);
+        if (a.tail_capacity == 0) a.tail_lanes = 0;
+    }
+    a.one_round = lanes >= count ? 1 : 0;
     if (a.tail_lanes > 0 && (lanes < count ? lanes : count) > a.tail_capacity) {
         // every exported packet (at most one per lane, at most `count`) needs a slot
         grid = a.tail_capacity / block;
@@ -1287,6 +1452,7 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
             grid = 1;
             a.tail_lanes = 0;
         }
+        a.one_round = grid * (uint64_t)block >= count ? 1 : 0;
     }
     bool moving = false;
     for (int c = 0; c < h.n_clouds; ++c) moving |= host_clouds[c].moving != 0;
