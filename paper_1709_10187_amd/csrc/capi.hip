@@ -874,20 +874,9 @@ rddmc_status rddmc_surrogate_attach(const rddmc_batch *batch, const void *d_tabl
     uint8_t *base = static_cast<uint8_t *>(d_surr);
     hipError_t e = hipMemcpyAsync(base, hdr.data(), hdr.size(), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(surrogate header)");
-    const int64_t cap = (max_batch + 31) & ~31ll;
-    float *X = reinterpret_cast<float *>(base + S.off_x);
-    float *SW = reinterpret_cast<float *>(base + S.off_sw);
-    float *R = reinterpret_cast<float *>(base + S.h.off_records);
-    for (uint64_t first = 0; first < S.h.n_records; first += (uint64_t)max_batch) {
-        const uint64_t cnt = std::min<uint64_t>((uint64_t)max_batch, S.h.n_records - first);
-        if ((e = launch_surr_features(static_cast<const uint8_t *>(d_tables), base, first, cnt, X, SW, s)) !=
-            hipSuccess)
-            return hip_fail(e, "surrogate features");
-        if ((e = mdn_forward(d_params, d_work, cap, X, (int)cnt, nullptr, s)) != hipSuccess)
-            return hip_fail(e, "surrogate inference");
-        if ((e = launch_surr_records(mdn_outputs(d_work, cap), SW, cnt, R + first * kSurrRec, s)) != hipSuccess)
-            return hip_fail(e, "surrogate records");
-    }
+    if ((e = mdn_records(d_params, static_cast<const uint8_t *>(d_tables), base, S.h.n_records,
+                         reinterpret_cast<float *>(base + S.h.off_records), s)) != hipSuccess)
+        return hip_fail(e, "surrogate records");
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     return RDDMC_OK;
 }
@@ -1238,8 +1227,7 @@ rddmc_status rddmc_mdn_forward(void *d_params, void *d_work, int64_t max_batch, 
 {
     if (!d_params || !d_work || !d_x) return fail(RDDMC_EINVAL, "NULL argument");
     if (n < 1 || n > max_batch) return fail(RDDMC_EINVAL, "n must be in [1, max_batch]");
-    const int64_t cap = (max_batch + 31) & ~31ll;
-    hipError_t e = mdn_forward(d_params, d_work, cap, d_x, n, d_out, reinterpret_cast<hipStream_t>(stream));
+    hipError_t e = mdn_forward(d_params, d_x, n, d_out, reinterpret_cast<hipStream_t>(stream));
     return e == hipSuccess ? RDDMC_OK : hip_fail(e, "mdn forward");
 }
 

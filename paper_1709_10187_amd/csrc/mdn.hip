@@ -7,15 +7,24 @@
 // at o[80+k] / o[96+k], correlation 0.95 tanh(o[112+k]); log-sigmas clamped to [-6, 4]).
 // The loss is the mean negative log-likelihood of the targets.
 //
-// Every matrix product is one launch of `gemm`: a block of four waves computes a 64x64 FP32
-// tile, 32x32 per wave with 32x32x16 MFMA steps, from 64x32 slices of A and B staged in LDS.
-// The slices are read from global memory with 16-byte loads along whichever dimension of the
-// operand is contiguous (K for activations and transposed weights, M or N for the operands of
-// the weight gradients, which are transposed on their way into LDS), so no operand is copied
-// or read element by element.  An epilogue adds the bias, applies GELU or its derivative, and
-// stores FP32 and / or BF16.  The weight-gradient products contract over the batch (4096 rows
-// for 16 output tiles): they split K over blocks, write FP32 partials, and a second kernel
-// adds the partials to the gradient in a fixed order (the result does not depend on timing).
+// The products are small (4096 rows x 170 k weights in training), so what bounds them is the
+// number of launches and passes over memory, not the matrix cores:
+//   mdn_rows   everything that is local to a row, one block per 32 rows: the four layers, and for
+//              training the likelihood and the three backward products.  Eight waves own 32
+//              output columns each; activations stay in LDS, the GELU derivatives of the three
+//              hidden layers in the registers of the lanes that will need them.  Weights are
+//              read from L2 in the order of the MFMA operand (refresh_bf16 lays them out), 1 KiB
+//              contiguous per load.  The same kernel computes the surrogate's inputs and sampling
+//              records when a cloud's window is evaluated.
+//   mdn_wgrad  all four weight gradients and the bias gradients, contracted over the batch from
+//              operands that mdn_rows left in MFMA order ([feature][32 rows] per row tile, so no
+//              transposition and no LDS), split over the batch into FP32 partials;
+//   mdn_reduce adds the partials in a fixed order (the result does not depend on timing).
+// One training step of 4096 rows takes 4 launches and 53 us (268 us and 30 launches with one launch
+// per product, operands staged and transposed through LDS); the 40 000 records of sixteen clouds
+// 66 us on the device (10 batches of 7 launches, 750 us).  What is left: the row kernel's 128
+// blocks for 4096 rows fill half of the compute units, and its time is the serial chain of seven
+// products with ~50 instructions of erfc per activation.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -24,6 +33,7 @@
 #include <algorithm>
 
 #include "rddmc_internal.h"
+#include "surrogate_dev.h"
 
 namespace rddmc {
 
@@ -41,157 +51,6 @@ __device__ __forceinline__ uint16_t f2bf(float f)
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * erfcf(-z * 0.70710678118654752f); }
-__device__ __forceinline__ float gelu_grad(float z)
-{
-    return 0.5f * erfcf(-z * 0.70710678118654752f) + z * 0.39894228040143268f * __expf(-0.5f * z * z);
-}
-
-enum Epilogue : int {
-    EP_STORE_F32 = 0,      // C = AB (+ bias)
-    EP_GELU = 1,           // Z = AB + bias -> f32 Z, bf16 gelu(Z)
-    EP_GELU_BACK = 2,      // dH = AB -> bf16 dH * gelu'(Z)   (Z given, f32)
-    EP_ACCUM_F32 = 3,      // C += AB
-    EP_PARTIAL = 4,        // P[split] = A[., ks] B[ks, .] (K split over blocks; summed by splitk_add)
-};
-
-struct GemmArgs {
-    const uint16_t *A;     // bf16, element (m, k) at A[m * sam + k * sak]
-    const uint16_t *B;     // bf16, element (k, n) at B[k * sbk + n * sbn]
-    int64_t sam, sak, sbk, sbn;
-    int M, N, K;           // K a multiple of 16; rows / columns past M / N read as zero
-    const float *bias;     // [N] or null
-    float *C;              // f32 [M, N] row-major (ldc = N)
-    uint16_t *Cb;          // bf16 [M, N] row-major
-    const float *Z;        // f32 [M, N] for the GELU derivative
-    float *P;              // f32 [splits, M, N] partial products (EP_PARTIAL)
-    int mode;
-    int splits;            // K ranges (multiples of 32) per output tile; 1 unless EP_PARTIAL
-};
-
-constexpr int kTile = 64, kKs = 32, kLdsRow = 40;   // block tile, K slice, padded LDS row (bf16)
-
-// Stage the K slice [k0, k0 + 32) of rows [r0, r0 + 64) of an operand into L[row][k] (bf16,
-// rows padded to 40): element (r, k) lives at X[r * sr + k * sk].  K-contiguous operands
-// (sk == 1) are read 8 k at a time along a row, row-contiguous ones (sr == 1) 8 rows at a
-// time along a k, anything else element by element; out-of-range elements read as zero.
-__device__ __forceinline__ void stage(uint16_t *__restrict__ L, const uint16_t *__restrict__ X, int64_t sr,
-                                      int64_t sk, int rows, int K, int r0, int k0, int t)
-{
-    if (sk == 1) {
-        const int r = t >> 2, c = (t & 3) << 3;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        const int gr = r0 + r, gk = k0 + c;
-        if (gr < rows && gk + 8 <= K) {
-            v = *reinterpret_cast<const uint4 *>(X + (int64_t)gr * sr + gk);
-        } else if (gr < rows) {
-            uint16_t h[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = gk + e < K ? X[(int64_t)gr * sr + gk + e] : (uint16_t)0;
-            v = make_uint4(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16), h[4] | ((uint32_t)h[5] << 16),
-                           h[6] | ((uint32_t)h[7] << 16));
-        }
-        *reinterpret_cast<uint4 *>(L + r * kLdsRow + c) = v;
-    } else if (sr == 1) {
-        const int kk = t >> 3, c = (t & 7) << 3;
-        const int gk = k0 + kk, gr = r0 + c;
-        uint16_t h[8];
-        if (gk < K && gr + 8 <= rows) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(X + (int64_t)gk * sk + gr);
-            h[0] = (uint16_t)v.x; h[1] = (uint16_t)(v.x >> 16); h[2] = (uint16_t)v.y; h[3] = (uint16_t)(v.y >> 16);
-            h[4] = (uint16_t)v.z; h[5] = (uint16_t)(v.z >> 16); h[6] = (uint16_t)v.w; h[7] = (uint16_t)(v.w >> 16);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = (gk < K && gr + e < rows) ? X[(int64_t)gk * sk + gr + e] : (uint16_t)0;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) L[(c + e) * kLdsRow + kk] = h[e];
-    } else {
-        for (int q = t; q < kTile * kKs; q += 256) {
-            const int r = q / kKs, kk = q % kKs;
-            const int gr = r0 + r, gk = k0 + kk;
-            L[r * kLdsRow + kk] = (gr < rows && gk < K) ? X[(int64_t)gr * sr + (int64_t)gk * sk] : (uint16_t)0;
-        }
-    }
-}
-
-// Block (tile_m, tile_n, split) of 256 lanes: wave w owns rows m0 + 32 (w >> 1), columns
-// n0 + 32 (w & 1).  Lane l supplies A row (l % 32), k-slice [(l / 32) * 8, +8) of each 16-deep
-// step from LDS, likewise B column (l % 32); its 16 accumulators hold rows
-// 8 (r / 4) + 4 (l / 32) + (r % 4) of the wave's sub-tile, column l % 32.
-__global__ __launch_bounds__(256) void gemm(GemmArgs g)
-{
-    __shared__ __attribute__((aligned(16))) uint16_t As[kTile * kLdsRow];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[kTile * kLdsRow];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int tiles_n = (g.N + kTile - 1) / kTile, tiles_m = (g.M + kTile - 1) / kTile;
-    const int tile = blockIdx.x % (tiles_m * tiles_n), split = blockIdx.x / (tiles_m * tiles_n);
-    const int m0 = (tile / tiles_n) * kTile, n0 = (tile % tiles_n) * kTile;
-    // this block's K range: whole slices, the last split takes the remainder
-    const int nks = (g.K + kKs - 1) / kKs;
-    const int per = (nks + g.splits - 1) / g.splits;
-    const int ks_lo = split * per, ks_hi = min(nks, ks_lo + per);
-    const int r32 = lane & 31, kh = (lane >> 5) << 3;
-    const int wm = (w >> 1) << 5, wn = (w & 1) << 5;
-    f32x16 acc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    for (int ks = ks_lo; ks < ks_hi; ++ks) {
-        const int k0 = ks * kKs;
-        // A rows are M, B "rows" are N with element (n, k) at B[n * sbn + k * sbk]
-        stage(As, g.A, g.sam, g.sak, g.M, g.K, m0, k0, t);
-        stage(Bs, g.B, g.sbn, g.sbk, g.N, g.K, n0, k0, t);
-        __syncthreads();
-#pragma unroll
-        for (int h = 0; h < kKs; h += 16) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(As + (wm + r32) * kLdsRow + h + kh);
-            const bf16x8 b = *reinterpret_cast<const bf16x8 *>(Bs + (wn + r32) * kLdsRow + h + kh);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    const int col = n0 + wn + r32;
-    if (col >= g.N) return;
-    if (g.mode == EP_PARTIAL) {
-        float *P = g.P + (int64_t)split * g.M * g.N;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = m0 + wm + ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3);
-            if (row < g.M) P[(int64_t)row * g.N + col] = acc[r];
-        }
-        return;
-    }
-    const float bv = g.bias ? g.bias[col] : 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm + ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3);
-        if (row >= g.M) continue;
-        const int64_t o = (int64_t)row * g.N + col;
-        const float v = acc[r] + bv;
-        if (g.mode == EP_STORE_F32) {
-            if (g.C) g.C[o] = v;
-            if (g.Cb) g.Cb[o] = f2bf(v);
-        } else if (g.mode == EP_GELU) {
-            g.C[o] = v;
-            g.Cb[o] = f2bf(gelu(v));
-        } else if (g.mode == EP_GELU_BACK) {
-            g.Cb[o] = f2bf(v * gelu_grad(g.Z[o]));
-        } else {
-            g.C[o] += v;
-        }
-    }
-}
-
-// C[i] += sum over splits of P[split][i], splits in order.
-__global__ void splitk_add(const float *__restrict__ P, int splits, int64_t n, float *__restrict__ C)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float v = 0.0f;
-    for (int q = 0; q < splits; ++q) v += P[(int64_t)q * n + i];
-    C[i] += v;
-}
-
 // ---- parameter layout ---------------------------------------------------------------
 constexpr int kIn = 16, kHid = 256, kOut = 128, kComp = 16;
 constexpr int kMaxSplits = 16;     // K splits of a weight-gradient product
@@ -202,12 +61,20 @@ constexpr int64_t kLayerB[4] = {kB1, kB2, kB3, kB4};
 constexpr int kLayerIn[4] = {kIn, kHid, kHid, kHid};
 constexpr int kLayerOut[4] = {kHid, kHid, kHid, kOut};
 
-// Parameter buffer: f32 theta, Adam m, Adam v, grad (kNParams each), then bf16 copies of
-// every W ([in, out]) and of its transpose ([out, in]).
+// Parameter buffer: f32 theta, Adam m, Adam v, grad (kNParams each), then two bf16 copies of
+// every W in MFMA operand order: wt for the forward product (contraction over the inputs), w for
+// the backward one (contraction over the outputs).
 struct ParamView {
     float *theta, *m, *v, *grad;
     uint16_t *w, *wt;     // bf16, kNParams entries each (bias slots unused)
 };
+
+// Place of element (k, n) of a [K, N] right operand in MFMA order: 32-column tiles, 16-deep
+// steps, 64 lanes (column n % 32, half (k % 16) / 8) of 8 consecutive k.
+__host__ __device__ inline int64_t frag_of(int k, int n, int K)
+{
+    return ((((int64_t)(n >> 5) * (K >> 4) + (k >> 4)) << 6) + (n & 31) + (((k >> 3) & 1) << 5)) * 8 + (k & 7);
+}
 
 __host__ __device__ inline ParamView param_view(void *base)
 {
@@ -223,16 +90,13 @@ __host__ __device__ inline ParamView param_view(void *base)
 }
 constexpr uint64_t kParamBytes = 4ull * 4 * kNParams + 2ull * 2 * kNParams;
 
-// Work buffer for a batch of up to `cap` samples (cap a multiple of 32).
+// Work buffer for a batch of up to `cap` samples (cap a multiple of 32).  Activations and
+// gradients are kept per 32-row tile as [feature][32 rows], the operand order of mdn_wgrad.
 struct WorkView {
-    uint16_t *xb;                  // [cap, 16]
-    float *z[3];                   // [cap, 256]
-    uint16_t *h[3];                // [cap, 256]
-    float *o;                      // [cap, 128]
-    uint16_t *dout;                // [cap, 128]
-    uint16_t *dz[2];               // [cap, 256] ping-pong
-    float *part;                   // [kMaxSplits, 256, 256] split-K partials of a weight gradient
-    float *loss;                   // [1]
+    uint16_t *act[4];              // the inputs of layer l: [tile][16 or 256][32]
+    uint16_t *d[4];                // d loss / d (pre-activation of layer l): [tile][256 or 128][32]
+    float *part;                   // [kMaxSplits, kNParams] partial gradients
+    float *lossp;                  // [cap / 32] loss of each row tile
 };
 
 __host__ __device__ inline WorkView work_view(void *base, int64_t cap)
@@ -244,51 +108,40 @@ __host__ __device__ inline WorkView work_view(void *base, int64_t cap)
         p += (bytes + 255) & ~255ull;
         return q;
     };
-    w.xb = reinterpret_cast<uint16_t *>(take(2ull * cap * kIn));
-    for (int l = 0; l < 3; ++l) w.z[l] = reinterpret_cast<float *>(take(4ull * cap * kHid));
-    for (int l = 0; l < 3; ++l) w.h[l] = reinterpret_cast<uint16_t *>(take(2ull * cap * kHid));
-    w.o = reinterpret_cast<float *>(take(4ull * cap * kOut));
-    w.dout = reinterpret_cast<uint16_t *>(take(2ull * cap * kOut));
-    for (int l = 0; l < 2; ++l) w.dz[l] = reinterpret_cast<uint16_t *>(take(2ull * cap * kHid));
-    w.part = reinterpret_cast<float *>(take(4ull * kMaxSplits * kHid * kHid));
-    w.loss = reinterpret_cast<float *>(take(256));
+    for (int l = 0; l < 4; ++l) w.act[l] = reinterpret_cast<uint16_t *>(take(2ull * cap * kLayerIn[l]));
+    for (int l = 0; l < 4; ++l) w.d[l] = reinterpret_cast<uint16_t *>(take(2ull * cap * kLayerOut[l]));
+    w.part = reinterpret_cast<float *>(take(4ull * kMaxSplits * kNParams));
+    w.lossp = reinterpret_cast<float *>(take(4ull * (cap / 32)));
     return w;
 }
 
 __host__ inline uint64_t work_bytes_for(int64_t cap)
 {
     WorkView w = work_view(nullptr, cap);
-    return reinterpret_cast<uint64_t>(w.loss) + 256;
+    return reinterpret_cast<uint64_t>(w.lossp) + ((4ull * (cap / 32) + 255) & ~255ull);
 }
 
 // ---- small kernels --------------------------------------------------------------------
-// bf16 copy of n values, zero up to n_pad
-__global__ void to_bf16_padded(const float *x, uint16_t *y, int64_t n, int64_t n_pad)
+// bf16 copies of one weight (parameter i), in both operand orders
+__device__ __forceinline__ void refresh_weight(const ParamView &p, int64_t i, float theta)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_pad) y[i] = i < n ? f2bf(x[i]) : (uint16_t)0;
-}
-
-// bf16 copies of every weight matrix and its transpose
-__global__ void refresh_bf16(ParamView p)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kNParams) return;
+#pragma unroll
     for (int l = 0; l < 4; ++l) {
-        const int64_t w0 = kLayerW[l], n = (int64_t)kLayerIn[l] * kLayerOut[l];
-        if (i >= w0 && i < w0 + n) {
-            const int64_t r = (i - w0) / kLayerOut[l], c = (i - w0) % kLayerOut[l];
-            const uint16_t b = f2bf(p.theta[i]);
-            p.w[i] = b;
-            p.wt[w0 + c * kLayerIn[l] + r] = b;
+        const int64_t w0 = kLayerW[l];
+        const int K = kLayerIn[l], N = kLayerOut[l];
+        if (i >= w0 && i < w0 + (int64_t)K * N) {
+            const int k = (int)(i - w0) / N, n = (int)(i - w0) % N;
+            const uint16_t b = f2bf(theta);
+            p.wt[w0 + frag_of(k, n, K)] = b;
+            if (l > 0) p.w[w0 + frag_of(n, k, N)] = b;   // the inputs need no gradient
         }
     }
 }
 
-__global__ void zero_f32(float *x, int64_t n)
+__global__ void refresh_bf16(ParamView p)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = 0.0f;
+    if (i < kNParams) refresh_weight(p, i, p.theta[i]);
 }
 
 // Glorot-uniform weights and zero biases from a Philox-free hash of (seed, index): the
@@ -316,102 +169,330 @@ __global__ void init_params(ParamView p, uint64_t seed)
     p.grad[i] = 0.0f;
 }
 
-// Mixture likelihood of one sample and d(mean NLL)/d(o) (stored bf16, scaled by 1/n).
-__global__ void nll_kernel(const float *__restrict__ o, const float *__restrict__ y, int n, int n_pad,
-                           uint16_t *__restrict__ dout, float *__restrict__ loss_sum)
+// ---- everything local to a row -------------------------------------------------------------
+constexpr int kRows = 32, kLd = kHid + 8, kLdO = kOut + 4;   // rows per block, padded LDS rows
+
+// What a block of mdn_rows reads and writes besides the parameters.
+struct RowArgs {
+    const float *x;        // f32 [n, 16] inputs (kForward, kTrain)
+    const float *y;        // f32 [n, 3] targets (kTrain)
+    float *out;            // kForward: f32 [n, 128] raw outputs; kRecords: records of rows 0 .. n-1
+    int64_t n;
+    WorkView w;            // kTrain
+    const uint8_t *tb, *surr;   // kRecords: tables and surrogate header
+};
+enum RowMode : int { kForward = 0, kTrain = 1, kRecords = 2 };
+
+// The wave's 32 x 32 tile of H [32, K] B [K, .] for output columns 32 tile ..: H in LDS, B in MFMA
+// order in global memory.  Lane l supplies row l % 32 of H and column l % 32 of B, k-slice
+// [(l / 32) * 8, +8) of each 16-deep step; accumulator r holds row 8 (r / 4) + 4 (l / 32) + (r % 4),
+// column l % 32.
+template <int K>
+__device__ __forceinline__ f32x16 product(const uint16_t *__restrict__ H, const uint16_t *__restrict__ B, int tile,
+                                          int lane)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_pad) return;
-    uint16_t *g = dout + (int64_t)i * kOut;
-    if (i >= n) {   // padding rows contribute nothing
-        for (int c = 0; c < kOut; ++c) g[c] = 0;
+    constexpr int S = K / 16;
+    const bf16x8 *bp = reinterpret_cast<const bf16x8 *>(B) + (int64_t)tile * S * 64 + lane;
+    const uint16_t *ap = H + (lane & 31) * kLd + ((lane >> 5) << 3);
+    bf16x8 b[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) b[s] = bp[s * 64];
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ap + 16 * s), b[s], acc, 0, 0, 0);
+    return acc;
+}
+
+__device__ __forceinline__ int acc_row(int r, int lane) { return ((r >> 2) << 3) + ((lane >> 5) << 2) + (r & 3); }
+
+// The lane's 16 values (one column) into LDS H[row][col] and, if T, the tile's [feature][32 rows]
+__device__ __forceinline__ void put_rows(uint16_t *__restrict__ H, uint16_t *__restrict__ T, int col, int lane,
+                                         const uint16_t *v)
+{
+#pragma unroll
+    for (int r = 0; r < 16; ++r) H[acc_row(r, lane) * kLd + col] = v[r];
+    if (T) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<uint2 *>(T + col * 32 + 8 * q + ((lane >> 5) << 2)) =
+                make_uint2(v[4 * q] | ((uint32_t)v[4 * q + 1] << 16), v[4 * q + 2] | ((uint32_t)v[4 * q + 3] << 16));
+    }
+}
+
+// One hidden layer of the forward pass: H <- bf16 gelu(H W + b); `gd` receives gelu' of the
+// lane's pre-activations.
+template <int K, bool TRAIN>
+__device__ __forceinline__ void hidden(uint16_t *__restrict__ Hin, uint16_t *__restrict__ Hout, const ParamView &p, int l,
+                                       uint16_t *T, int wave, int lane, float *gd)
+{
+    const f32x16 acc = product<K>(Hin, p.wt + kLayerW[l], wave, lane);
+    const int col = 32 * wave + (lane & 31);
+    const float bias = p.theta[kLayerB[l] + col];
+    uint16_t v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float z = acc[r] + bias;
+        const float e = erfcf(-z * 0.70710678118654752f);   // gelu and its derivative share it
+        v[r] = f2bf(0.5f * z * e);
+        if (TRAIN) gd[r] = 0.5f * e + z * 0.39894228040143268f * __expf(-0.5f * z * z);
+    }
+    put_rows(Hout, T, col, lane, v);
+}
+
+// One backward product: D <- bf16 (D W^T) * gelu'.
+template <int K>
+__device__ __forceinline__ void backward(const uint16_t *__restrict__ Din, uint16_t *__restrict__ Dout, const ParamView &p,
+                                         int l, uint16_t *T, int wave, int lane, const float *gd)
+{
+    const f32x16 acc = product<K>(Din, p.w + kLayerW[l], wave, lane);
+    uint16_t v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = f2bf(acc[r] * gd[r]);
+    put_rows(Dout, T, 32 * wave + (lane & 31), lane, v);
+}
+
+// The likelihood of one row and d(mean NLL)/d(o), by its 16 lanes (lane k: component k); q: the
+// row's 128 outputs in LDS, lcs: 16 floats of scratch of the row, g: the row's gradient (bf16).
+// Sums over components run in order in every lane, so they do not depend on the layout.
+__device__ __forceinline__ float row_nll(const float *__restrict__ q, const float *__restrict__ y, bool live, float inv_n,
+                                         int k, float *__restrict__ lcs, uint16_t *__restrict__ g)
+{
+    const int f = live ? (int)y[0] : 0;
+    const float y1 = live ? y[1] : 0.0f, y2 = live ? y[2] : 0.0f;
+    float amax = -INFINITY;
+    for (int c = 0; c < kComp; ++c) amax = fmaxf(amax, q[c]);
+    float asum = 0.0f;
+    for (int c = 0; c < kComp; ++c) asum += __expf(q[c] - amax);
+    const float log_asum = amax + __logf(asum);
+    const float f0 = q[16 + 2 * k], f1 = q[17 + 2 * k];
+    const float fm = fmaxf(f0, f1);
+    const float e0 = __expf(f0 - fm), e1 = __expf(f1 - fm);
+    const float lse_f = fm + __logf(e0 + e1);
+    const float s1r = q[64 + k], s2r = q[96 + k];
+    const float s1 = fminf(fmaxf(s1r, -6.0f), 4.0f), s2 = fminf(fmaxf(s2r, -6.0f), 4.0f);
+    const float rr = tanhf(q[112 + k]);
+    const float rho = 0.95f * rr;
+    const float e1s = __expf(-s1), e2s = __expf(-s2);
+    const float z1 = (y1 - q[48 + k]) * e1s, z2 = (y2 - q[80 + k]) * e2s;
+    const float om = 1.0f - rho * rho;
+    const float qq = (z1 * z1 - 2.0f * rho * z1 * z2 + z2 * z2) / om;
+    const float lc = (q[k] - log_asum) + ((f ? f1 : f0) - lse_f) +
+                     (-1.8378770664093453f - s1 - s2 - 0.5f * __logf(om) - 0.5f * qq);
+    lcs[k] = lc;
+    __syncthreads();
+    float lmax = -INFINITY;
+    for (int c = 0; c < kComp; ++c) lmax = fmaxf(lmax, lcs[c]);
+    float lsum = 0.0f;
+    for (int c = 0; c < kComp; ++c) lsum += __expf(lcs[c] - lmax);
+    const float ll = lmax + __logf(lsum);
+    const float w = __expf(lc - ll);
+    const float pi = __expf(q[k] - log_asum);
+    const float p0 = e0 / (e0 + e1), p1 = e1 / (e0 + e1);
+    const float dq1 = (2.0f * z1 - 2.0f * rho * z2) / om, dq2 = (2.0f * z2 - 2.0f * rho * z1) / om;
+    const float dqr = (-2.0f * z1 * z2) / om + qq * (2.0f * rho) / om;
+    const float in1 = (s1r > -6.0f && s1r < 4.0f) ? 1.0f : 0.0f;
+    const float in2 = (s2r > -6.0f && s2r < 4.0f) ? 1.0f : 0.0f;
+    // padding rows contribute nothing
+    g[k] = live ? f2bf((pi - w) * inv_n) : (uint16_t)0;
+    g[16 + 2 * k] = live ? f2bf(w * (p0 - (f == 0 ? 1.0f : 0.0f)) * inv_n) : (uint16_t)0;
+    g[17 + 2 * k] = live ? f2bf(w * (p1 - (f == 1 ? 1.0f : 0.0f)) * inv_n) : (uint16_t)0;
+    g[48 + k] = live ? f2bf(-w * 0.5f * dq1 * e1s * inv_n) : (uint16_t)0;
+    g[64 + k] = live ? f2bf(-w * (-1.0f + 0.5f * dq1 * z1) * in1 * inv_n) : (uint16_t)0;
+    g[80 + k] = live ? f2bf(-w * 0.5f * dq2 * e2s * inv_n) : (uint16_t)0;
+    g[96 + k] = live ? f2bf(-w * (-1.0f + 0.5f * dq2 * z2) * in2 * inv_n) : (uint16_t)0;
+    g[112 + k] = live ? f2bf(-w * (rho / om - 0.5f * dqr) * 0.95f * (1.0f - rr * rr) * inv_n) : (uint16_t)0;
+    return ll;
+}
+
+// The sampling record of one window state from its outputs q (LDS), by its 16 lanes.
+__device__ __forceinline__ void row_record(const float *__restrict__ q, float S, float wd, int k, float *__restrict__ r)
+{
+    float amax = -INFINITY;
+    for (int c = 0; c < kComp; ++c) amax = fmaxf(amax, q[c]);
+    float sum = 0.0f, cum = 0.0f;
+    for (int c = 0; c < kComp; ++c) {
+        sum += __expf(q[c] - amax);
+        if (c == k) cum = sum;
+    }
+    r[kRecCdf + k] = k == 15 ? 1.0f : cum / sum;
+    r[kRecPf0 + k] = 1.0f / (1.0f + __expf(q[17 + 2 * k] - q[16 + 2 * k]));
+    r[kRecMu1 + k] = q[48 + k];
+    r[kRecSg1 + k] = __expf(fminf(fmaxf(q[64 + k], -6.0f), 4.0f));
+    r[kRecMu2 + k] = q[80 + k];
+    r[kRecSg2 + k] = __expf(fminf(fmaxf(q[96 + k], -6.0f), 4.0f));
+    r[kRecRho + k] = 0.95f * tanhf(q[112 + k]);
+    r[kRecS + k] = k == 0 ? S : (k == kRecW - kRecS ? wd : 0.0f);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(512) void mdn_rows(ParamView p, RowArgs a)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t H[2][kRows * kLd];
+    __shared__ float O[kRows * kLdO];
+    __shared__ float scr[kRows * kComp];     // component log-likelihoods; states' scales
+    __shared__ float rowloss[kRows];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t tile = blockIdx.x, row0 = tile * kRows;
+    constexpr bool TRAIN = MODE == kTrain;
+    // inputs (bf16; rows past n are zero)
+    if (MODE == kRecords) {
+        if (t < kRows) {
+            float f[kSurrIn], S = 0.0f, wd = 0.0f;
+            for (int k = 0; k < kSurrIn; ++k) f[k] = 0.0f;
+            if (row0 + t < a.n) surr_state_features(a.tb, a.surr, (uint64_t)(row0 + t), f, S, wd);
+            for (int k = 0; k < kIn; ++k) H[0][t * kLd + k] = f2bf(f[k]);
+            scr[2 * t] = S;
+            scr[2 * t + 1] = wd;
+        }
+    } else {
+        const int r = t >> 4, k = t & 15;
+        const uint16_t v = row0 + r < a.n ? f2bf(a.x[(row0 + r) * kIn + k]) : (uint16_t)0;
+        H[0][r * kLd + k] = v;
+        if (TRAIN) a.w.act[0][(tile * kIn + k) * 32 + r] = v;
+    }
+    __syncthreads();
+    uint16_t *T1 = TRAIN ? a.w.act[1] + tile * kHid * 32 : nullptr;
+    uint16_t *T2 = TRAIN ? a.w.act[2] + tile * kHid * 32 : nullptr;
+    uint16_t *T3 = TRAIN ? a.w.act[3] + tile * kHid * 32 : nullptr;
+    float gd1[16], gd2[16], gd3[16];
+    hidden<kIn, TRAIN>(H[0], H[1], p, 0, T1, wave, lane, gd1);
+    __syncthreads();
+    hidden<kHid, TRAIN>(H[1], H[0], p, 1, T2, wave, lane, gd2);
+    __syncthreads();
+    hidden<kHid, TRAIN>(H[0], H[1], p, 2, T3, wave, lane, gd3);
+    __syncthreads();
+    if (wave < kOut / 32) {
+        const f32x16 acc = product<kHid>(H[1], p.wt + kLayerW[3], wave, lane);
+        const int col = 32 * wave + (lane & 31);
+        const float bias = p.theta[kLayerB[3] + col];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = acc_row(r, lane);
+            const float v = acc[r] + bias;
+            if (MODE == kForward) {
+                if (row0 + row < a.n) a.out[(row0 + row) * kOut + col] = v;
+            } else {
+                O[row * kLdO + col] = v;
+            }
+        }
+    }
+    if (MODE == kForward) return;
+    __syncthreads();
+    const int r = t >> 4, k = t & 15;
+    const bool live = row0 + r < a.n;
+    if (MODE == kRecords) {
+        if (live) row_record(O + r * kLdO, scr[2 * r], scr[2 * r + 1], k, a.out + (row0 + r) * kSurrRec);
         return;
     }
-    const float *q = o + (int64_t)i * kOut;
-    const int f = (int)y[3 * i];
-    const float y1 = y[3 * i + 1], y2 = y[3 * i + 2];
-    float lc[kComp];
-    float amax = -INFINITY;
-    for (int k = 0; k < kComp; ++k) amax = fmaxf(amax, q[k]);
-    float asum = 0.0f;
-    for (int k = 0; k < kComp; ++k) asum += __expf(q[k] - amax);
-    const float log_asum = amax + __logf(asum);
-    float lmax = -INFINITY;
-    for (int k = 0; k < kComp; ++k) {
-        const float f0 = q[16 + 2 * k], f1 = q[17 + 2 * k];
-        const float fm = fmaxf(f0, f1);
-        const float lse_f = fm + __logf(__expf(f0 - fm) + __expf(f1 - fm));
-        const float s1 = fminf(fmaxf(q[64 + k], -6.0f), 4.0f), s2 = fminf(fmaxf(q[96 + k], -6.0f), 4.0f);
-        const float rho = 0.95f * tanhf(q[112 + k]);
-        const float z1 = (y1 - q[48 + k]) * __expf(-s1), z2 = (y2 - q[80 + k]) * __expf(-s2);
-        const float om = 1.0f - rho * rho;
-        const float qq = (z1 * z1 - 2.0f * rho * z1 * z2 + z2 * z2) / om;
-        lc[k] = (q[k] - log_asum) + ((f ? f1 : f0) - lse_f) +
-                (-1.8378770664093453f - s1 - s2 - 0.5f * __logf(om) - 0.5f * qq);
-        lmax = fmaxf(lmax, lc[k]);
-    }
-    float lsum = 0.0f;
-    for (int k = 0; k < kComp; ++k) lsum += __expf(lc[k] - lmax);
-    const float ll = lmax + __logf(lsum);
-    atomicAdd(loss_sum, -ll / (float)n);      // the mean NLL
-    const float inv_n = 1.0f / (float)n;
-    for (int k = 0; k < kComp; ++k) {
-        const float w = __expf(lc[k] - ll);
-        const float pi = __expf(q[k] - log_asum);
-        g[k] = f2bf((pi - w) * inv_n);
-        const float f0 = q[16 + 2 * k], f1 = q[17 + 2 * k];
-        const float fm = fmaxf(f0, f1);
-        const float e0 = __expf(f0 - fm), e1 = __expf(f1 - fm);
-        const float p0 = e0 / (e0 + e1), p1 = e1 / (e0 + e1);
-        g[16 + 2 * k] = f2bf(w * (p0 - (f == 0 ? 1.0f : 0.0f)) * inv_n);
-        g[17 + 2 * k] = f2bf(w * (p1 - (f == 1 ? 1.0f : 0.0f)) * inv_n);
-        const float s1r = q[64 + k], s2r = q[96 + k];
-        const float s1 = fminf(fmaxf(s1r, -6.0f), 4.0f), s2 = fminf(fmaxf(s2r, -6.0f), 4.0f);
-        const float rr = tanhf(q[112 + k]);
-        const float rho = 0.95f * rr;
-        const float e1s = __expf(-s1), e2s = __expf(-s2);
-        const float z1 = (y1 - q[48 + k]) * e1s, z2 = (y2 - q[80 + k]) * e2s;
-        const float om = 1.0f - rho * rho;
-        const float dq1 = (2.0f * z1 - 2.0f * rho * z2) / om, dq2 = (2.0f * z2 - 2.0f * rho * z1) / om;
-        const float qq = (z1 * z1 - 2.0f * rho * z1 * z2 + z2 * z2) / om;
-        const float dqr = (-2.0f * z1 * z2) / om + qq * (2.0f * rho) / om;
-        const float in1 = (s1r > -6.0f && s1r < 4.0f) ? 1.0f : 0.0f;
-        const float in2 = (s2r > -6.0f && s2r < 4.0f) ? 1.0f : 0.0f;
-        g[48 + k] = f2bf(-w * 0.5f * dq1 * e1s * inv_n);
-        g[64 + k] = f2bf(-w * (-1.0f + 0.5f * dq1 * z1) * in1 * inv_n);
-        g[80 + k] = f2bf(-w * 0.5f * dq2 * e2s * inv_n);
-        g[96 + k] = f2bf(-w * (-1.0f + 0.5f * dq2 * z2) * in2 * inv_n);
-        g[112 + k] = f2bf(-w * (rho / om - 0.5f * dqr) * 0.95f * (1.0f - rr * rr) * inv_n);
-    }
-}
-
-// column sums of a bf16 [M, N] matrix, added into out[N]
-// Column sums of a bf16 [M, N] matrix in two passes: block (column chunk of 64, row chunk of
-// `rows`) has 4 lanes per column each summing a quarter of the chunk's rows, reduced in LDS
-// to partial[row chunk][column]; colsum_finish adds the row chunks' partials to out in order.
-// At most kMaxSplits * kHid * kHid / N row chunks (the partial buffer), of at least 256 rows.
-__global__ __launch_bounds__(256) void colsum_partial(const uint16_t *__restrict__ d, int M, int N, int rows,
-                                                     float *__restrict__ part)
-{
-    __shared__ float red[4][64];
-    const int cl = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + cl;
-    const int r0 = blockIdx.y * rows;
-    float s = 0.0f;
-    if (c < N)
-        for (int r = r0 + g; r < min(M, r0 + rows); r += 4) s += bf2f(d[(int64_t)r * N + c]);
-    red[g][cl] = s;
+    const float ll = row_nll(O + r * kLdO, a.y + 3 * (row0 + r), live, 1.0f / (float)a.n, k, scr + r * kComp, H[0] + r * kLd);
+    if (k == 0) rowloss[r] = live ? -ll / (float)a.n : 0.0f;
     __syncthreads();
-    if (g == 0 && c < N) part[(int64_t)blockIdx.y * N + c] = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
+    if (t == 0) {   // the tile's share of the mean NLL
+        float v = 0.0f;
+        for (int q = 0; q < kRows; ++q) v += rowloss[q];
+        a.w.lossp[tile] = v;
+    }
+    {
+        const int c = t >> 2, q0 = (t & 3) << 3;
+        uint16_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = H[0][(q0 + e) * kLd + c];
+        *reinterpret_cast<uint4 *>(a.w.d[3] + (tile * kOut + c) * 32 + q0) =
+            make_uint4(v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16), v[4] | ((uint32_t)v[5] << 16),
+                       v[6] | ((uint32_t)v[7] << 16));
+    }
+    backward<kOut>(H[0], H[1], p, 3, a.w.d[2] + tile * kHid * 32, wave, lane, gd3);
+    __syncthreads();
+    backward<kHid>(H[1], H[0], p, 2, a.w.d[1] + tile * kHid * 32, wave, lane, gd2);
+    __syncthreads();
+    backward<kHid>(H[0], H[1], p, 1, a.w.d[0] + tile * kHid * 32, wave, lane, gd1);
 }
 
-__global__ void colsum_finish(const float *__restrict__ part, int chunks, int N, float *__restrict__ out)
+// ---- weight and bias gradients ------------------------------------------------------------------
+// Block: one 64 x 64 tile of one layer's dW = act^T d over one range of row tiles, 32 x 32 per
+// wave; the waves of the first tile row also sum d's columns (the bias gradient).  Partials go
+// to part[split][parameter].
+constexpr int kWgTiles[4] = {4, 16, 16, 8};      // 64 x 64 tiles of each layer (16 inputs: one row)
+constexpr int kWgAll = 44;
+
+template <int L>
+__device__ __forceinline__ void wgrad_tile(const WorkView &w, int tile, int lo, int hi, float *__restrict__ P, int wave,
+                                           int lane)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= N) return;
-    float s = 0.0f;
-    for (int q = 0; q < chunks; ++q) s += part[(int64_t)q * N + c];
-    out[c] += s;
+    constexpr int K = kLayerIn[L], N = kLayerOut[L];
+    const int m0 = (tile / (N / 64)) * 64 + ((wave >> 1) << 5), n0 = (tile % (N / 64)) * 64 + ((wave & 1) << 5);
+    if (m0 >= K) return;
+    const int m = m0 + (lane & 31), n = n0 + (lane & 31), kh = (lane >> 5) << 3;
+    const bool in = m < K;
+    const uint16_t *A = w.act[L] + (int64_t)(in ? m : 0) * 32 + kh;
+    const uint16_t *B = w.d[L] + (int64_t)n * 32 + kh;
+    const bool bias = m0 == 0;
+    float db = 0.0f;
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll 4
+    for (int q = lo; q < hi; ++q) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint4 av = *reinterpret_cast<const uint4 *>(A + (int64_t)q * K * 32 + 16 * h);
+            const uint4 bv = *reinterpret_cast<const uint4 *>(B + (int64_t)q * N * 32 + 16 * h);
+            if (!in) av = make_uint4(0u, 0u, 0u, 0u);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv),
+                                                          acc, 0, 0, 0);
+            if (bias) {
+                const uint32_t u[4] = {bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) db += bf2f((uint16_t)u[e]) + bf2f((uint16_t)(u[e] >> 16));
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = m0 + acc_row(r, lane);
+        if (row < K) P[kLayerW[L] + (int64_t)row * N + n] = acc[r];
+    }
+    if (bias) {
+        db += __shfl_xor(db, 32);
+        if (lane < 32) P[kLayerB[L] + n] = db;
+    }
+}
+
+__global__ __launch_bounds__(256) void mdn_wgrad(WorkView w, int tiles, int splits)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int split = blockIdx.x / kWgAll;
+    int b = blockIdx.x % kWgAll;
+    const int per = (tiles + splits - 1) / splits;
+    const int lo = split * per, hi = min(tiles, lo + per);
+    float *P = w.part + (int64_t)split * kNParams;
+    if (b < kWgTiles[0]) return wgrad_tile<0>(w, b, lo, hi, P, wave, lane);
+    b -= kWgTiles[0];
+    if (b < kWgTiles[1]) return wgrad_tile<1>(w, b, lo, hi, P, wave, lane);
+    b -= kWgTiles[1];
+    if (b < kWgTiles[2]) return wgrad_tile<2>(w, b, lo, hi, P, wave, lane);
+    wgrad_tile<3>(w, b - kWgTiles[2], lo, hi, P, wave, lane);
+}
+
+// grad = the partials' sum, splits in order; the loss, row tiles in order (64 strided sums, then
+// in lane order).
+__global__ __launch_bounds__(256) void mdn_reduce(ParamView p, WorkView w, int splits, int tiles, float *__restrict__ loss)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kNParams) {
+        float v = 0.0f;
+        for (int q = 0; q < splits; ++q) v += w.part[(int64_t)q * kNParams + i];
+        p.grad[i] = v;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 64 && loss) {
+        float v = 0.0f;
+        for (int q = threadIdx.x; q < tiles; q += 64) v += w.lossp[q];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (threadIdx.x == 0) *loss = v;
+    }
 }
 
 __global__ void adam_kernel(ParamView p, float lr, float b1, float b2, float eps, float c1, float c2)
@@ -423,106 +504,9 @@ __global__ void adam_kernel(ParamView p, float lr, float b1, float b2, float eps
     const float v = b2 * p.v[i] + (1.0f - b2) * g * g;
     p.m[i] = m;
     p.v[i] = v;
-    p.theta[i] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
-}
-
-// ---- host orchestration -----------------------------------------------------------------
-hipError_t launch_gemm(const GemmArgs &g, hipStream_t s)
-{
-    const int tiles = ((g.M + kTile - 1) / kTile) * ((g.N + kTile - 1) / kTile);
-    gemm<<<(unsigned)(tiles * g.splits), 256, 0, s>>>(g);
-    if (g.mode == EP_PARTIAL) {
-        const int64_t n = (int64_t)g.M * g.N;
-        splitk_add<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(g.P, g.splits, n, g.C);
-    }
-    return hipGetLastError();
-}
-
-GemmArgs gemm_args(const uint16_t *A, int64_t sam, int64_t sak, const uint16_t *B, int64_t sbk, int64_t sbn, int M,
-                   int N, int K)
-{
-    GemmArgs g{};
-    g.A = A;
-    g.sam = sam;
-    g.sak = sak;
-    g.B = B;
-    g.sbk = sbk;
-    g.sbn = sbn;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    g.splits = 1;
-    return g;
-}
-
-// forward of `mp` (multiple of 32) rows whose bf16 inputs are in w.xb
-hipError_t forward(const ParamView &p, const WorkView &w, int mp, hipStream_t s)
-{
-    hipError_t e;
-    const uint16_t *in = w.xb;
-    for (int l = 0; l < 4; ++l) {
-        const int K = kLayerIn[l], N = kLayerOut[l];
-        // B = W [K, N]: element (k, n) read from the transposed copy at n * K + k
-        GemmArgs g = gemm_args(in, K, 1, p.wt + kLayerW[l], 1, K, mp, N, K);
-        g.bias = p.theta + kLayerB[l];
-        if (l < 3) {
-            g.mode = EP_GELU;
-            g.C = w.z[l];
-            g.Cb = w.h[l];
-            in = w.h[l];
-        } else {
-            g.mode = EP_STORE_F32;
-            g.C = w.o;
-        }
-        if ((e = launch_gemm(g, s)) != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-// loss and gradient (into p.grad, overwritten) of n samples (padded to mp rows)
-hipError_t loss_grad(const ParamView &p, const WorkView &w, const float *d_x, const float *d_y, int n, int mp,
-                     hipStream_t s)
-{
-    hipError_t e;
-    to_bf16_padded<<<(unsigned)(((int64_t)mp * kIn + 255) / 256), 256, 0, s>>>(d_x, w.xb, (int64_t)n * kIn,
-                                                                             (int64_t)mp * kIn);
-    if ((e = forward(p, w, mp, s)) != hipSuccess) return e;
-    zero_f32<<<1, 64, 0, s>>>(w.loss, 1);
-    zero_f32<<<(unsigned)((kNParams + 255) / 256), 256, 0, s>>>(p.grad, kNParams);
-    nll_kernel<<<(unsigned)((mp + 127) / 128), 128, 0, s>>>(w.o, d_y, n, mp, w.dout, w.loss);
-    // layer 4: dW4 = h3^T dout, db4 = colsum(dout), dz3 = (dout W4^T) * gelu'(z3)
-    const uint16_t *dcur = w.dout;
-    int dn = kOut;
-    int pp = 0;
-    for (int l = 3; l >= 0; --l) {
-        const int K = kLayerIn[l], N = kLayerOut[l];
-        const uint16_t *hin = l > 0 ? w.h[l - 1] : w.xb;
-        // dW[K, N] += hin^T (K x mp) * dcur (mp x N)
-        GemmArgs gw = gemm_args(hin, 1, K, dcur, dn, 1, K, N, mp);
-        gw.mode = EP_PARTIAL;
-        gw.splits = std::max(1, std::min(kMaxSplits, mp / 256));
-        gw.P = w.part;
-        gw.C = p.grad + kLayerW[l];
-        if ((e = launch_gemm(gw, s)) != hipSuccess) return e;
-        {
-            const int max_chunks = (int)(kMaxSplits * kHid * kHid / N);
-            const int rows = std::max(256, (mp + max_chunks - 1) / max_chunks);
-            const int chunks = (mp + rows - 1) / rows;
-            colsum_partial<<<dim3((N + 63) / 64, chunks), 256, 0, s>>>(dcur, mp, N, rows, w.part);
-            colsum_finish<<<(N + 127) / 128, 128, 0, s>>>(w.part, chunks, N, p.grad + kLayerB[l]);
-        }
-        if (l == 0) break;
-        // dz_{l-1}[mp, K] = (dcur [mp, N] * W^T [N, K]) * gelu'(z_{l-1}); B element (o, i) = W[i, o]
-        GemmArgs gd = gemm_args(dcur, dn, 1, p.w + kLayerW[l], 1, N, mp, K, N);
-        gd.mode = EP_GELU_BACK;
-        gd.Z = w.z[l - 1];
-        gd.Cb = w.dz[pp];
-        if ((e = launch_gemm(gd, s)) != hipSuccess) return e;
-        dcur = w.dz[pp];
-        dn = K;
-        pp ^= 1;
-    }
-    return hipGetLastError();
+    const float th = p.theta[i] - lr * (m / c1) / (sqrtf(v / c2) + eps);
+    p.theta[i] = th;
+    refresh_weight(p, i, th);
 }
 
 }  // namespace
@@ -546,30 +530,45 @@ hipError_t mdn_refresh(void *d_params, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t mdn_forward(void *d_params, void *d_work, int64_t cap, const float *d_x, int n, float *d_out,
+hipError_t mdn_forward(void *d_params, const float *d_x, int n, float *d_out, hipStream_t s)
+{
+    if (!d_out) return hipSuccess;
+    RowArgs a{};
+    a.x = d_x;
+    a.out = d_out;
+    a.n = n;
+    mdn_rows<kForward><<<(unsigned)((n + kRows - 1) / kRows), 512, 0, s>>>(param_view(d_params), a);
+    return hipGetLastError();
+}
+
+hipError_t mdn_records(void *d_params, const uint8_t *d_tables, const uint8_t *d_surr, uint64_t n, float *d_rec,
                        hipStream_t s)
 {
-    ParamView p = param_view(d_params);
-    WorkView w = work_view(d_work, cap);
-    const int mp = (n + 31) & ~31;
-    hipError_t e;
-    to_bf16_padded<<<(unsigned)(((int64_t)mp * kIn + 255) / 256), 256, 0, s>>>(d_x, w.xb, (int64_t)n * kIn,
-                                                                             (int64_t)mp * kIn);
-    if ((e = forward(p, w, mp, s)) != hipSuccess) return e;
-    if (d_out && (e = hipMemcpyAsync(d_out, w.o, 4ull * n * kOut, hipMemcpyDeviceToDevice, s)) != hipSuccess)
-        return e;
+    if (n == 0) return hipSuccess;
+    RowArgs a{};
+    a.tb = d_tables;
+    a.surr = d_surr;
+    a.out = d_rec;
+    a.n = (int64_t)n;
+    mdn_rows<kRecords><<<(unsigned)((n + kRows - 1) / kRows), 512, 0, s>>>(param_view(d_params), a);
     return hipGetLastError();
 }
 
 hipError_t mdn_loss_grad(void *d_params, void *d_work, int64_t cap, const float *d_x, const float *d_y, int n,
                          float *d_loss, hipStream_t s)
 {
-    ParamView p = param_view(d_params);
-    WorkView w = work_view(d_work, cap);
-    const int mp = (n + 31) & ~31;
-    hipError_t e = loss_grad(p, w, d_x, d_y, n, mp, s);
-    if (e != hipSuccess) return e;
-    if (d_loss && (e = hipMemcpyAsync(d_loss, w.loss, 4, hipMemcpyDeviceToDevice, s)) != hipSuccess) return e;
+    const ParamView p = param_view(d_params);
+    RowArgs a{};
+    a.x = d_x;
+    a.y = d_y;
+    a.n = n;
+    a.w = work_view(d_work, cap);
+    const int tiles = (n + kRows - 1) / kRows;
+    // ranges of the batch for the weight gradients: at least 256 rows each
+    const int splits = std::max(1, std::min(kMaxSplits, tiles * kRows / 256));
+    mdn_rows<kTrain><<<(unsigned)tiles, 512, 0, s>>>(p, a);
+    mdn_wgrad<<<(unsigned)(kWgAll * splits), 256, 0, s>>>(a.w, tiles, splits);
+    mdn_reduce<<<(unsigned)((kNParams + 255) / 256), 256, 0, s>>>(p, a.w, splits, tiles, d_loss);
     return hipGetLastError();
 }
 
@@ -579,11 +578,7 @@ hipError_t mdn_adam(void *d_params, int64_t step, float lr, hipStream_t s)
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
     adam_kernel<<<(unsigned)((kNParams + 255) / 256), 256, 0, s>>>(p, lr, b1, b2, eps, c1, c2);
-    refresh_bf16<<<(unsigned)((kNParams + 255) / 256), 256, 0, s>>>(p);
     return hipGetLastError();
 }
-
-// raw network outputs of the current batch (work buffer), for the surrogate table kernel
-const float *mdn_outputs(void *d_work, int64_t cap) { return work_view(d_work, cap).o; }
 
 }  // namespace rddmc

@@ -148,21 +148,18 @@ hipError_t launch_zero(void *d, size_t words64, hipStream_t s);
 hipError_t launch_subwalk(const uint8_t *d_tables, bool moving, uint64_t seed, uint64_t max_steps,
                           const int32_t *d_cloud, const int32_t *d_state, int64_t n, float *d_x, float *d_y,
                           unsigned long long *d_steps, hipStream_t s);
-hipError_t launch_surr_features(const uint8_t *d_tables, const uint8_t *d_surr, uint64_t first, uint64_t count,
-                                float *d_x, float *d_sw, hipStream_t s);
-hipError_t launch_surr_records(const float *d_out, const float *d_sw, uint64_t count, float *d_rec, hipStream_t s);
 // mixture-density network (mdn.hip)
 uint64_t mdn_param_bytes();
 uint64_t mdn_work_bytes(int64_t cap);
 int64_t mdn_n_params();
 hipError_t mdn_init(void *d_params, uint64_t seed, hipStream_t s);
 hipError_t mdn_refresh(void *d_params, hipStream_t s);
-hipError_t mdn_forward(void *d_params, void *d_work, int64_t cap, const float *d_x, int n, float *d_out,
+hipError_t mdn_forward(void *d_params, const float *d_x, int n, float *d_out, hipStream_t s);
+hipError_t mdn_records(void *d_params, const uint8_t *d_tables, const uint8_t *d_surr, uint64_t n, float *d_rec,
                        hipStream_t s);
 hipError_t mdn_loss_grad(void *d_params, void *d_work, int64_t cap, const float *d_x, const float *d_y, int n,
                          float *d_loss, hipStream_t s);
 hipError_t mdn_adam(void *d_params, int64_t step, float lr, hipStream_t s);
-const float *mdn_outputs(void *d_work, int64_t cap);
 hipError_t launch_build_redistribution(const DevCloud &c, uint8_t *d_tables, hipStream_t s);
 hipError_t launch_build_line_tables(const DevHeader &h, uint8_t *d_tables, hipStream_t s);
 hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddmc_run &run, uint64_t first,

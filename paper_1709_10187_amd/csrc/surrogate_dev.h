@@ -99,4 +99,23 @@ __device__ inline void surr_features(const DevCloud &c, const uint8_t *tb, int i
     w = (float)wd;
 }
 
+// Features and scales of window state g (the index of its record) of a batch.
+__device__ inline void surr_state_features(const uint8_t *tb, const uint8_t *surr, uint64_t g, float *f, float &S,
+                                           float &w)
+{
+    const SurrHeader *SH = reinterpret_cast<const SurrHeader *>(surr);
+    const SurrCloud *sc = reinterpret_cast<const SurrCloud *>(surr + SH->off_clouds);
+    int lo = 0, hi = SH->n_clouds;          // last cloud whose first record is <= g
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (sc[mid].rec_off <= g) lo = mid; else hi = mid;
+    }
+    const SurrCloud win = sc[lo];
+    const DevHeader *H = reinterpret_cast<const DevHeader *>(tb);
+    const DevCloud &c = reinterpret_cast<const DevCloud *>(tb + H->off_clouds)[lo];
+    const int nj = win.j_hi - win.j_lo + 1;
+    const int64_t r = (int64_t)(g - win.rec_off);
+    surr_features(c, tb, win.i_lo + (int)(r / nj), win.j_lo + (int)(r % nj), f, S, w);
+}
+
 }  // namespace rddmc
