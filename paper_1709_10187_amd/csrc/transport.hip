@@ -541,9 +541,9 @@ __device__ __forceinline__ void moving_steps(Packet1D &p, int budget, int lim, c
 // escape frequencies.  Static media take one Philox block per pair of steps ((x, y) for the
 // even step and (z, w) for the odd one; all active lanes of a wave are at even step counts
 // between pairs); moving media take one block per step.
-template <bool MOVING, bool SURR>
-__device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
-                          const WalkArgs &a, unsigned long long *__restrict__ tally, int lane);
+template <bool MOVING, bool SURR, bool SUB = false>
+__device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
+                         const WalkArgs &a, unsigned long long *__restrict__ tally, int lane);
 
 __device__ __forceinline__ uint32_t rl(uint32_t v, int lane)
 {
@@ -560,6 +560,22 @@ __device__ __forceinline__ TailPacket *slots_of(unsigned long long *work)
     return reinterpret_cast<TailPacket *>(reinterpret_cast<uint8_t *>(work) + kWorkHeaderBytes);
 }
 
+// The packet's copies of its cloud's fields.
+__device__ __forceinline__ void set_cloud(Packet1D &p, const uint8_t *__restrict__ tb, const DevCloud &c)
+{
+    p.key = c.stream;
+    p.nb = c.nb;
+    p.nc = c.nc;
+    p.geom = c.geometry;
+    p.hot = reinterpret_cast<const uint4 *>(tb + c.off_hot);
+    p.cmap = reinterpret_cast<const float4 *>(tb + c.off_cmap);
+    p.x0 = c.x0;
+    p.dx = c.dx;
+    p.inv_dx = c.inv_dx;
+    p.uniform = c.uniform_bins != 0;
+    p.moving = c.moving != 0;
+}
+
 // The packet of an export slot as a wave-uniform state.
 __device__ Packet1D load_slot(const TailPacket *ts, const uint8_t *__restrict__ tb,
                               const DevCloud *__restrict__ clouds)
@@ -567,25 +583,14 @@ __device__ Packet1D load_slot(const TailPacket *ts, const uint8_t *__restrict__ 
     const TailPacket tk = *ts;
     Packet1D q;
     q.cl = (int)rl(tk.cl, 0);
-    const DevCloud &c = clouds[q.cl];
+    set_cloud(q, tb, clouds[q.cl]);
     q.pid = rl(tk.pid, 0);
-    q.key = c.stream;
     q.i = (int)rl((uint32_t)tk.i, 0);
     q.j = (int)rl((uint32_t)tk.j, 0);
     q.steps = ((uint64_t)rl((uint32_t)(tk.steps >> 32), 0) << 32) | rl((uint32_t)tk.steps, 0);
     const uint64_t tb64 = ((uint64_t)rl((uint32_t)(__double_as_longlong(tk.t) >> 32), 0) << 32) |
                           rl((uint32_t)__double_as_longlong(tk.t), 0);
     q.t = __longlong_as_double((long long)tb64);
-    q.nb = c.nb;
-    q.nc = c.nc;
-    q.geom = c.geometry;
-    q.hot = reinterpret_cast<const uint4 *>(tb + c.off_hot);
-    q.cmap = reinterpret_cast<const float4 *>(tb + c.off_cmap);
-    q.x0 = c.x0;
-    q.dx = c.dx;
-    q.inv_dx = c.inv_dx;
-    q.uniform = c.uniform_bins != 0;
-    q.moving = c.moving != 0;
     q.active = true;
     q.surr_calls = rl(tk.surr_calls, 0);
     return q;
@@ -691,17 +696,7 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
                         p.cl = lo;
                         const DevCloud &c = clouds[lo];
                         p.pid = (uint32_t)(g - prefix[lo]);
-                        p.key = c.stream;
-                        p.nb = c.nb;
-                        p.nc = c.nc;
-                        p.geom = c.geometry;
-                        p.hot = reinterpret_cast<const uint4 *>(tb + c.off_hot);
-                        p.cmap = reinterpret_cast<const float4 *>(tb + c.off_cmap);
-                        p.x0 = c.x0;
-                        p.dx = c.dx;
-                        p.inv_dx = c.inv_dx;
-                        p.uniform = c.uniform_bins != 0;
-                        p.moving = c.moving != 0;
+                        set_cloud(p, tb, c);
                         last_state = (int)c.n_states - 1;
                         // emission (Sec. 2.3): a source state drawn by its probability
                         const u32x4 r = philox4x32_10(0u, kDomEmit, p.pid, p.key, a.key0, a.key1);
@@ -1096,9 +1091,11 @@ __device__ __forceinline__ void mix_block(Packet1D &q, int b, const SurrWin &sw,
     take_lane0<SURR>(q, s1);
 }
 
-template <bool MOVING, bool SURR>
-__device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
-                          const WalkArgs &a, unsigned long long *__restrict__ tally, int lane)
+// With SUB the walk is a sub-walk: it ends with the first spatial leak, of which it returns the
+// bin (-1 if the step cap came first), and tallies nothing.
+template <bool MOVING, bool SURR, bool SUB>
+__device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
+                         const WalkArgs &a, unsigned long long *__restrict__ tally, int lane)
 {
     // the cloud's surrogate window: a step that starts in it is replaced by one exit, at the
     // same points as in the lane walk (every step in moving media, even step counts in
@@ -1119,7 +1116,7 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
     while (q.active) {
         const uint64_t left = a.max_steps - q.steps;
         if (left == 0) {
-            if (lane == 0) tally_finish(tally, clouds[q.cl], false, 0, 0, q.t, q.steps);
+            if (!SUB && lane == 0) tally_finish(tally, clouds[q.cl], false, 0, 0, q.t, q.steps);
             q.active = false;
             break;
         }
@@ -1270,8 +1267,10 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
                 const float4 cm = (MOVING && s1.moving) ? s1.cmap[s1.i] : make_float4(1.f, 0.f, 1.f, 0.f);
                 one_step<MOVING>(s1, ws, rec, cm, tb, clouds, a, tally);
             }
+            const int i0 = q.i;
             take_lane0<SURR>(q, s1);
-            if (short_run >= 2) {
+            if (SUB && q.i != i0) return jj;
+            if (!SUB && short_run >= 2) {
                 mixed = true;
                 short_run = 0;
                 wi = -1;
@@ -1282,6 +1281,7 @@ __device__ void coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const Dev
     }
     if (SURR && lane == 0 && q.surr_calls)
         atomicAdd(&tally[clouds[q.cl].tally_off + TW_SURR_CALLS], (unsigned long long)q.surr_calls);
+    return -1;
 }
 
 template <bool MOVING, bool SURR>
@@ -1313,6 +1313,25 @@ __global__ __launch_bounds__(64) void walk1d_coop(const uint8_t *__restrict__ tb
     }
 }
 
+// An event whose word ties with the high word of a threshold, decided by the full u64 with the
+// low word of the step's auxiliary block: 0 / 1 a lower / upper bin, 2 / 3 a leak through face 0 / 1.
+__device__ int tied_event(const Packet1D &p, uint32_t ew, uint4 rec, const uint8_t *__restrict__ tb, const DevCloud &c,
+                          const WalkArgs &a)
+{
+    const u32x4 aux = philox4x32_10((uint32_t)p.steps, kDomAux | (uint32_t)(p.steps >> 32), p.pid, p.key, a.key0,
+                                    a.key1);
+    const uint4 lw = reinterpret_cast<const uint4 *>(tb + c.off_lo_words)[p.i * p.nb + p.j];
+    const uint64_t U = ((uint64_t)ew << 32) | aux.x;
+    if (U < (((uint64_t)rec.y << 32) | lw.x)) return 0;
+    if (U < (((uint64_t)rec.z << 32) | lw.y)) return 1;
+    return U < (((uint64_t)rec.w << 32) | lw.z) ? 2 : 3;
+}
+
+// Live lanes of a sub-walk wave at which it turns to walking them one by one: a side-by-side step
+// of the whole wave costs as much issue as ~14 cooperative ones (a lone lane 0.75 us per step, a
+// cooperative packet ~0.04).
+constexpr int kSubTail = 14;
+
 // Sub-walks for the surrogate's training data: sample q starts in state s_state[q] of
 // cloud s_cloud[q] (a cell with two neighbours) and takes DDMC steps until its first
 // spatial leak.  Writes the state's features X[q, 16] and the exit Y[q] = (face, y1, y2),
@@ -1320,52 +1339,75 @@ __global__ __launch_bounds__(64) void walk1d_coop(const uint8_t *__restrict__ tb
 template <bool MOVING>
 __global__ __launch_bounds__(256) void subwalk1d(const uint8_t *__restrict__ tb, WalkArgs a,
                                                  const int32_t *__restrict__ s_cloud,
-                                                 const int32_t *__restrict__ s_state, int64_t n,
+                                                 const int32_t *__restrict__ s_state, int64_t n, int per_wave,
                                                  float *__restrict__ X, float *__restrict__ Y,
                                                  unsigned long long *__restrict__ steps_out)
 {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
+    const int lane = threadIdx.x & 63;
+    int64_t q = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * per_wave + lane;
+    const bool mine = lane < per_wave && q < n;
+    if (!mine) q = n - 1;
     const DevHeader *H = reinterpret_cast<const DevHeader *>(tb);
     const DevCloud *clouds = reinterpret_cast<const DevCloud *>(tb + H->off_clouds);
-    const int cl = s_cloud[q];
-    const DevCloud &c = clouds[cl];
     Packet1D p;
-    p.cl = cl;
-    p.nb = c.nb;
-    p.nc = c.nc;
-    p.geom = c.geometry;
+    p.cl = s_cloud[q];
+    const DevCloud &c = clouds[p.cl];
+    set_cloud(p, tb, c);
     p.pid = (uint32_t)q;
-    p.key = c.stream;
     p.i = s_state[q] / c.nb;
     p.j = s_state[q] - p.i * c.nb;
     p.t = 0.0;
     p.steps = 0;
-    p.hot = reinterpret_cast<const uint4 *>(tb + c.off_hot);
-    p.cmap = reinterpret_cast<const float4 *>(tb + c.off_cmap);
-    p.x0 = c.x0;
-    p.dx = c.dx;
-    p.inv_dx = c.inv_dx;
-    p.uniform = c.uniform_bins != 0;
-    p.moving = c.moving != 0;
-    p.active = true;
+    p.active = mine;
     p.surr_calls = 0u;
     float f[kSurrIn], S, w;
     surr_features(c, tb, p.i, p.j, f, S, w);
-    for (int k = 0; k < kSurrIn; ++k) X[q * kSurrIn + k] = f[k];
+    if (mine)
+        for (int k = 0; k < kSurrIn; ++k) X[q * kSurrIn + k] = f[k];
     int face = -1, jexit = p.j;
-    while (p.steps < a.max_steps) {
-        const int i0 = p.i, j0 = p.j;
-        const StepWords wd = words_of_step<MOVING>(p, p.steps, a);
-        const uint4 rec = p.hot[p.i * p.nb + p.j];
-        const float4 cm = (MOVING && p.moving) ? p.cmap[p.i] : make_float4(1.f, 0.f, 1.f, 0.f);
-        one_step<MOVING>(p, wd, rec, cm, tb, clouds, a, nullptr);
-        if (p.i != i0) {
-            face = p.i > i0 ? 1 : 0;
-            jexit = j0;
-            break;
+    // lanes walk side by side until few are left ...
+    while (__popcll(__ballot(p.active)) > kSubTail) {
+        for (int k = 0; k < 32; ++k) {
+            if (p.active) {
+                const uint4 rec = p.hot[p.i * p.nb + p.j];
+                const StepWords w = words_of_step<MOVING>(p, p.steps, a);
+                p.t += (double)path_length(w.t, __uint_as_float(rec.x));
+                int ev = w.e < rec.y ? 0 : (w.e < rec.z ? 1 : (w.e < rec.w ? 2 : 3));   // bins -, +, faces 0, 1
+                if (w.e == rec.y || w.e == rec.z || w.e == rec.w) ev = tied_event(p, w.e, rec, tb, c, a);
+                ++p.steps;
+                if (ev >= 2) {
+                    face = ev - 2;
+                    jexit = p.j;
+                }
+                p.j += ev == 0 ? -1 : (ev == 1 ? 1 : 0);
+                p.active = ev < 2 && p.steps < a.max_steps;
+            }
         }
     }
+    // ... and the wave takes those one after another, cooperatively
+    for (uint64_t left = __ballot(p.active); left;) {
+        const int l = __ffsll((unsigned long long)left) - 1;
+        left &= left - 1ull;
+        Packet1D u;   // that lane's packet, the same in every lane
+        u.active = true;
+        u.surr_calls = 0u;
+        u.cl = (int)rl((uint32_t)p.cl, l);
+        u.pid = rl(p.pid, l);
+        u.i = (int)rl((uint32_t)p.i, l);
+        u.j = (int)rl((uint32_t)p.j, l);
+        u.steps = ((uint64_t)rl((uint32_t)(p.steps >> 32), l) << 32) | rl((uint32_t)p.steps, l);
+        u.t = rl_f64(p.t, l);
+        set_cloud(u, tb, clouds[u.cl]);
+        const int i0 = u.i;
+        const int j = coop_walk<MOVING, false, true>(u, tb, clouds, a, nullptr, lane);
+        if (lane == l) {
+            p.t = u.t;
+            p.steps = u.steps;
+            face = j < 0 ? -1 : (u.i > i0 ? 1 : 0);
+            jexit = j < 0 ? u.j : j;
+        }
+    }
+    if (!mine) return;
     const double *e = reinterpret_cast<const double *>(tb + c.off_edges);
     const u32x4 r = philox4x32_10((uint32_t)q, kDomSub | (uint32_t)((uint64_t)q >> 32), p.pid, p.key, a.key0, a.key1);
     const double xo = e[jexit] + (e[jexit + 1] - e[jexit]) * u01_open_low(r.x);
@@ -1497,11 +1539,18 @@ hipError_t launch_subwalk(const uint8_t *d_tables, bool moving, uint64_t seed, u
     a.max_steps = max_steps;
     a.key0 = (uint32_t)seed;
     a.key1 = (uint32_t)(seed >> 32);
-    const unsigned grid = (unsigned)((n + 255) / 256);
+    // as many waves as fill the device four times over before a wave takes more than a few samples:
+    // the last of them are walked one after another (13 320 samples of 35 000 steps: 414 ms at 64
+    // per wave, 107 spread out)
+    const int64_t fill = 16ll * device_cu_count();
+    const int64_t per = (n + fill - 1) / fill;
+    const int per_wave = per < 4 ? 4 : (per > 64 ? 64 : (int)per);
+    const int64_t waves = (n + per_wave - 1) / per_wave;
+    const unsigned grid = (unsigned)((waves + 3) / 4);
     if (moving)
-        subwalk1d<true><<<grid, 256, 0, s>>>(d_tables, a, d_cloud, d_state, n, d_x, d_y, d_steps);
+        subwalk1d<true><<<grid, 256, 0, s>>>(d_tables, a, d_cloud, d_state, n, per_wave, d_x, d_y, d_steps);
     else
-        subwalk1d<false><<<grid, 256, 0, s>>>(d_tables, a, d_cloud, d_state, n, d_x, d_y, d_steps);
+        subwalk1d<false><<<grid, 256, 0, s>>>(d_tables, a, d_cloud, d_state, n, per_wave, d_x, d_y, d_steps);
     return hipGetLastError();
 }
 
