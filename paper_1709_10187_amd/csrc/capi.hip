@@ -437,10 +437,10 @@ rddmc_status rddmc_work_bytes(const rddmc_batch *batch, size_t *bytes)
     Layout L;
     rddmc_status st = make_layout(batch, L);
     if (st != RDDMC_OK) return st;
-    // queue counters, then one 48-byte slot per lane that may hand its packet to the
-    // cooperative tail walk (at most 2^20 lanes are ever resident)
+    // queue counters, then one slot (48 bytes; hybrid 1D walk: 104) per lane that may hand its
+    // packet to the cooperative tail walk (at most 2^20 lanes are ever resident)
     const uint64_t lanes = L.h.total_packets < (1ull << 20) ? L.h.total_packets : (1ull << 20);
-    *bytes = 256 + 48 * lanes;
+    *bytes = 256 + (L.h.hybrid1d ? 104 : 48) * lanes;
     return RDDMC_OK;
 }
 
@@ -578,9 +578,19 @@ rddmc_status rddmc_transport(const rddmc_batch *batch, const void *d_tables, con
     if (L.h.hybrid1d) {
         if (run->surrogate)
             return fail(RDDMC_EUNSUPPORTED, "the escape surrogate runs with pure-DDMC 1D batches only");
-        hipError_t e = launch_walk1dh(static_cast<const uint8_t *>(d_tables), L.h, *run, run->first, count,
+        // no state is thick where the threshold is above every cell's line-centre width (H <= 1)
+        bool any_thick = false;
+        for (int ci = 0; ci < L.h.n_clouds && !any_thick; ++ci) {
+            const rddmc_medium &m = batch->clouds[ci];
+            for (int i = 0; i < m.n_cells[0] && !any_thick; ++i) {
+                const double ks = m.dust_sca ? m.dust_sca[i] : 0.0;
+                any_thick = (m.k0[i] + ks) * (m.faces[0][i + 1] - m.faces[0][i]) >= m.tau_threshold;
+            }
+        }
+        hipError_t e = launch_walk1dh(static_cast<const uint8_t *>(d_tables), L.h, any_thick, *run, run->first, count,
                                       static_cast<unsigned long long *>(d_tally),
-                                      static_cast<unsigned long long *>(d_work), reinterpret_cast<hipStream_t>(stream));
+                                      static_cast<unsigned long long *>(d_work), work_bytes,
+                                      reinterpret_cast<hipStream_t>(stream));
         return e == hipSuccess ? RDDMC_OK : hip_fail(e, "1D hybrid walk kernel");
     }
     hipError_t e = launch_walk(static_cast<const uint8_t *>(d_tables), L.h, L.clouds.data(), *run, run->first,

@@ -18,12 +18,15 @@ constexpr float kTwoPi = 6.28318530717959f;
 constexpr int kUparMaxTries = 1 << 20;          // the sampler's acceptance is >= ~1e-3
 
 // Launch arguments of the hybrid walks: packet range, step cap, Philox key (the run's seed),
-// steps between refills, number of clouds, and the counter domain of the walk's streams.
+// steps between refills, number of clouds, the counter domain of the walk's streams, and how the
+// 1D walk shares packets out.
 struct McArgs {
     uint64_t first, count, max_steps;
     uint32_t key0, key1;
     int32_t chunk, n_clouds;
     uint32_t dom;
+    int32_t lanes;     // 1D: lanes of a wave that take packets
+    uint64_t slots;    // 1D: export slots for the cooperative walk (0: it takes no packets)
 };
 
 // Per-packet stream: block b is Philox4x32-10 of counter (b_lo, dom | b_hi, packet id,

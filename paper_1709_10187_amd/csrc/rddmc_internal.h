@@ -164,8 +164,9 @@ hipError_t launch_build_redistribution(const DevCloud &c, uint8_t *d_tables, hip
 hipError_t launch_build_line_tables(const DevHeader &h, uint8_t *d_tables, hipStream_t s);
 hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddmc_run &run, uint64_t first,
                          uint64_t count, unsigned long long *d_tally, unsigned long long *d_work, hipStream_t s);
-hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, const rddmc_run &run, uint64_t first,
-                          uint64_t count, unsigned long long *d_tally, unsigned long long *d_work, hipStream_t s);
+hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_thick, const rddmc_run &run,
+                          uint64_t first, uint64_t count, unsigned long long *d_tally, unsigned long long *d_work,
+                          uint64_t work_bytes, hipStream_t s);
 hipError_t launch_philox_fill(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t c2,
                               uint32_t c3, uint64_t n, uint32_t *d_out, hipStream_t s);
 int device_cu_count();

@@ -22,6 +22,7 @@
 #include "philox.h"
 #include "rddmc_internal.h"
 #include "surrogate_dev.h"
+#include "wave_dev.h"
 
 namespace rddmc {
 
@@ -545,16 +546,6 @@ template <bool MOVING, bool SURR, bool SUB = false>
 __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
                          const WalkArgs &a, unsigned long long *__restrict__ tally, int lane);
 
-__device__ __forceinline__ uint32_t rl(uint32_t v, int lane)
-{
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
-
-// v with `s` (wave-uniform) in lane `lane`: the compiler has no builtin for v_writelane_b32, and
-// only the intrinsic lets it place the wait states after the instruction that wrote `s`
-extern "C" __device__ int amdgcn_writelane_i32(int s, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
-__device__ __forceinline__ int write_lane(int s, int lane, int v) { return amdgcn_writelane_i32(s, lane, v); }
-
 __device__ __forceinline__ TailPacket *slots_of(unsigned long long *work)
 {
     return reinterpret_cast<TailPacket *>(reinterpret_cast<uint8_t *>(work) + kWorkHeaderBytes);
@@ -826,66 +817,6 @@ __device__ __forceinline__ void scan_from(uint32_t &st, int &vst, uint32_t tlo, 
     scan_step<8 * G + 6>(st, vst, tlo, thi);
     if constexpr (G < 7) {
         if (st != kScanStop) scan_from<G + 1>(st, vst, tlo, thi);
-    }
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, false);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-__device__ __forceinline__ double rl_f64(double v, int lane)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    return __longlong_as_double((long long)(((uint64_t)rl((uint32_t)(b >> 32), lane) << 32) | rl((uint32_t)b, lane)));
-}
-
-// Clock of a block without the sequential chain, where that gives the same bits.  With
-// t0 in [2^e, 2^(e+1)), ulp = 2^(e-52), and every partial sum below 2^(e+1), each
-// addition t + d (d >= 0) rounds to t + ulp * rint(d / ulp), unless d / ulp lies exactly
-// halfway between integers (then the rounding depends on the running sum).  Without such
-// a tie the block's result is t0 + ulp * (sum of the rint values): an exact integer sum,
-// reduced across the wave in any order.  Returns false (t unchanged) where the premises
-// fail; the caller then adds in order.
-__device__ __forceinline__ bool clock_parallel(double &t, double dd)
-{
-    const uint64_t tbits = (uint64_t)__double_as_longlong(t);
-    const int be = (int)((tbits >> 52) & 0x7ffu);
-    if (be == 0 || be >= 0x7fe) return false;        // zero, subnormal or near the top
-    const int e = be - 1023;
-    const double qv = ldexp(dd, 52 - e);               // exact: a power-of-two scaling
-    const double n = rint(qv);
-    const bool tie = (qv - floor(qv)) == 0.5;
-    if (__any(tie)) return false;
-    double s = n;                                      // integers below 2^53: exact sums
-    s += dpp_f64<0xb1>(s);                             // quad_perm [1,0,3,2]
-    s += dpp_f64<0x4e>(s);                             // quad_perm [2,3,0,1]
-    s += dpp_f64<0x124>(s);                            // row_ror:4
-    s += dpp_f64<0x128>(s);                            // row_ror:8
-    const double S = (rl_f64(s, 0) + rl_f64(s, 16)) + (rl_f64(s, 32) + rl_f64(s, 48));
-    const double tf = t + ldexp(S, e - 52);
-    if (!(tf < ldexp(1.0, e + 1))) return false;       // left the binade: add in order
-    t = tf;
-    return true;
-}
-
-// Clock of a block: t += the FP64 path lengths of lanes 0, 1, ... in order (lanes at or
-// beyond `done` hold +0, which leaves t unchanged).
-template <int G>
-__device__ __forceinline__ void clock_from(double &t, uint32_t dlo, uint32_t dhi, int done)
-{
-    double v[8];   // read the group's eight values first, then add them in order
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-        v[u] = __longlong_as_double((long long)(((uint64_t)rl(dhi, 8 * G + u) << 32) | rl(dlo, 8 * G + u)));
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t += v[u];
-    if constexpr (G < 7) {
-        if (done > 8 * (G + 1)) clock_from<G + 1>(t, dlo, dhi, done);
     }
 }
 

@@ -37,11 +37,13 @@
 // Escapes add face row (slab: face; sphere: one row), lab bin and time to the int64 tallies.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "mc_dev.h"
 #include "philox.h"
 #include "rddmc_internal.h"
+#include "wave_dev.h"
 
 namespace rddmc {
 
@@ -705,6 +707,496 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// ---- cooperative walk of one packet ----------------------------------------------------------
+// A DDMC step is one lane's chain of a few hundred dependent instructions and a gather, about
+// 0.9 us for a lone lane, however few lanes of the wave are left.  Here the whole wave advances
+// one packet: in a block, lane k draws the k-th pair of words of the packet's stream, the lanes
+// hold the records of a window of states (2^(6-b) cells x 2^b bins, lane = (cell - wi) 2^b +
+// (bin - wj)), and every lane computes where pair k would take a packet of its state, so that the
+// packet's own position follows by one readlane per pair.  A step takes one pair {time, event},
+// and a second {face, x} if its event is a spatial leak: a position with bit 6 set waits for its
+// face pair.  Lane 63 is the stop: moves out of the window lead to it (the step is completed after
+// the chain), and so do the steps a block does not take: ties, leaks into thin states or vacuum,
+// dust absorption, spatial leaks of a moving cloud on a non-uniform grid or out of the window, and a
+// residence that crosses a census time.
+// Those run in lane 0 with the step functions above, as do the continuous-MC events that follow
+// a conversion, until the packet is in a DDMC state again.  The clock is that of the cooperative
+// walk of pure clouds, census sums are integers: results do not depend on who walks a packet.
+struct Window1 {
+    int b, wi, wj;                        // shape and corner
+    uint32_t lk, dhi, shi, ahi, split, flags;
+    int dn, up, lo, hi, pend;             // where the events lead (63: stop)
+    double ka;                            // continuous dust weights: absorption of the lane's cell
+    double rho[2], sh[2];                 // moving clouds: eq. 20 across the faces of the lane's cell
+};
+
+constexpr int kPend = 64;                 // position bit: the face pair comes next
+__shared__ unsigned long long s_path_block[kBlockMax];   // a block's residence sums per position
+
+// Words of the stream consumed so far, and the stream positioned there.
+__device__ __forceinline__ uint64_t word_pos(const Rng &r)
+{
+    const uint64_t next = ((uint64_t)r.ctr_hi << 32) | r.ctr;
+    return 4ull * (next - (r.ahead ? 2ull : 1ull)) + r.idx;
+}
+__device__ __forceinline__ void set_words(Rng &r, uint64_t wp, const McArgs &a)
+{
+    const uint64_t blk = wp >> 2;
+    r.ctr = (uint32_t)blk;
+    r.ctr_hi = (uint32_t)(blk >> 32);
+    r.ahead = false;
+    r.idx = 4u;
+    if (wp & 3ull) {
+        const u32x4 w = next_block(r, a);
+        r.c0 = w.x;
+        r.c1 = w.y;
+        r.c2 = w.z;
+        r.c3 = w.w;
+        r.idx = (uint32_t)wp & 3u;
+    }
+}
+
+template <bool WGT>
+__device__ __forceinline__ void window_load(Window1 &w, const Pk1 &q, const DevCloud &c, const uint8_t *__restrict__ tb,
+                                            int b, int lane)
+{
+    const int nb = c.nb, nc = c.nc;
+    const int wjn = 1 << b, win = 64 >> b;
+    int wi = q.cell - (win >> 1), wj = q.j - (wjn >> 1);
+    if (wi > nc - win) wi = nc - win;
+    if (wi < 0) wi = 0;
+    if (wj > nb - wjn) wj = nb - wjn;
+    if (wj < 0) wj = 0;
+    if (((q.cell - wi) << b) + (q.j - wj) == 63) ++wj;   // the packet's own state needs a lane
+    w.b = b;
+    w.wi = wi;
+    w.wj = wj;
+    const int il = lane >> b, jl = lane & (wjn - 1);
+    const bool in = wi + il < nc && wj + jl < nb;
+    const int64_t s = in ? (int64_t)(wi + il) * nb + wj + jl : 0;
+    const uint4 r = reinterpret_cast<const uint4 *>(tb + c.off_hot)[s];
+    w.lk = r.x;
+    w.dhi = r.y;
+    w.shi = r.z;
+    w.flags = r.w;
+    w.split = reinterpret_cast<const uint32_t *>(tb + c.off_face_split)[s];
+    w.ahi = 0xffffffffu;
+    if (c.dusty) {   // the absorption band [A, 2^64), if any, belongs to lane 0
+        const uint4 lw = reinterpret_cast<const uint4 *>(tb + c.off_lo_words)[s];
+        if ((lw.w | lw.z) != 0u) w.ahi = lw.w;
+    }
+    if (WGT && c.dust_weight) w.ka = reinterpret_cast<const double *>(tb + c.off_dust)[2 * (in ? wi + il : 0)];
+    const bool live = in && lane < 63;
+    w.dn = live && jl > 0 && !(r.w & kFlagDnThin) ? lane - 1 : 63;
+    w.up = live && jl < wjn - 1 && !(r.w & kFlagUpThin) ? lane + 1 : 63;
+    w.lo = live && il > 0 && !(r.w & (1u << kFlagFaceShift)) ? lane - wjn : 63;
+    w.hi = live && il < win - 1 && !(r.w & (2u << kFlagFaceShift)) ? lane + wjn : 63;
+    // re-binning on non-uniform grids searches the edges: left to lane 0
+    w.pend = live && (!c.moving || c.uniform_bins) ? lane | kPend : 63;
+    if (c.moving) {
+        const double *mp = reinterpret_cast<const double *>(tb + c.off_map) + 6 * (in ? wi + il : 0);
+        w.rho[0] = mp[0];
+        w.sh[0] = mp[1];
+        w.rho[1] = mp[3];
+        w.sh[1] = mp[4];
+    }
+}
+
+// Pair K of the chain: an event pair, or the face pair of a spatial leak.
+template <int K>
+__device__ __forceinline__ void window_step(const Window1 &w, const DevCloud &c, uint32_t wa, uint32_t wb, int lane,
+                                            int &p, int &post)
+{
+    if (p & kPend) {
+        const bool upper = (rl(wa, K) >> 1) >= w.split;
+        int nf = upper ? w.hi : w.lo;
+        if (c.moving) {   // ddmc_step1's re-binning: x uniform in the bin, moved to the neighbour's frame
+            const int j = w.wj + (lane & ((1 << w.b) - 1));
+            const float xin = fmaf((float)j + uf(rl(wb, K)), c.dx, c.x0);
+            const double rho = upper ? w.rho[1] : w.rho[0], sh = upper ? w.sh[1] : w.sh[0];
+            const float x = ((float)(rho * (double)xin + sh) - c.x0) * c.inv_dx;
+            int jn = !(x >= 0.0f) ? 0 : (x >= (float)(c.nb - 1) ? c.nb - 1 : (int)x);
+            if (rho == 1.0 && sh == 0.0) jn = j;
+            const int to = nf + (jn - j);
+            nf = nf == 63 || (unsigned)(jn - w.wj) >= (1u << w.b) ? 63 : to;
+        }
+        p = (int)rl((uint32_t)nf, p & 63);
+        if (c.moving && !(rl(w.flags, p) & kFlagThick)) p = 63;   // into a thin state: lane 0
+    } else {
+        const uint32_t e = rl(wb, K);
+        const int f = e < w.dhi ? w.dn : w.up;
+        const int x = e < w.ahi ? w.pend : 63;
+        p = (int)rl((uint32_t)(e < w.shi ? f : x), p);
+    }
+    post = write_lane(p, K, post);
+}
+
+template <int G>
+__device__ __forceinline__ void window_from(const Window1 &w, const DevCloud &c, uint32_t wa, uint32_t wb, int lane,
+                                            int &p, int &post)
+{
+    window_step<8 * G + 0>(w, c, wa, wb, lane, p, post);
+    window_step<8 * G + 1>(w, c, wa, wb, lane, p, post);
+    window_step<8 * G + 2>(w, c, wa, wb, lane, p, post);
+    window_step<8 * G + 3>(w, c, wa, wb, lane, p, post);
+    window_step<8 * G + 4>(w, c, wa, wb, lane, p, post);
+    window_step<8 * G + 5>(w, c, wa, wb, lane, p, post);
+    window_step<8 * G + 6>(w, c, wa, wb, lane, p, post);
+    window_step<8 * G + 7>(w, c, wa, wb, lane, p, post);
+    if constexpr (G < 7) {
+        if (p != 63) window_from<G + 1>(w, c, wa, wb, lane, p, post);
+    }
+}
+
+__device__ __forceinline__ double shfl_f64(double v, int src)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((uint64_t)(uint32_t)__shfl((int)(uint32_t)(b >> 32), src) << 32) |
+                                            (uint32_t)__shfl((int)(uint32_t)b, src)));
+}
+
+// The log-weight after the residences of lanes K .. 63, added in order as the step functions do
+// (lanes without one hold 0); with KEEP lane k keeps its value before residence k.
+template <bool KEEP, int K>
+__device__ __forceinline__ void log_weight(double &lw, double &lw0, double ka, double dd)
+{
+    if (KEEP) {
+        const uint64_t b = (uint64_t)__double_as_longlong(lw), v = (uint64_t)__double_as_longlong(lw0);
+        const int lo = write_lane((int)rl((uint32_t)b, 0), K, (int)(uint32_t)v);
+        const int hi = write_lane((int)rl((uint32_t)(b >> 32), 0), K, (int)(uint32_t)(v >> 32));
+        lw0 = __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+    }
+    lw = fma(rl_f64(ka, K), rl_f64(dd, K), lw);
+    if constexpr (K < 63) log_weight<KEEP, K + 1>(lw, lw0, ka, dd);
+}
+
+// Shape for the recent shares of spatial and frequency steps (as in the walk of pure clouds).
+__device__ __forceinline__ int window_shape(const DevCloud &c, int nt, int ns)
+{
+    const int nf = nt - ns;
+    int b = nf >= 256 * ns ? 6 : (nf >= 64 * ns ? 5 : (nf >= 4 * ns ? 4 : (4 * nf >= ns ? 3 : (64 * nf >= ns ? 2 : 1))));
+    while (b > 1 && (1 << (b - 1)) >= c.nb) --b;
+    while (b < 5 && (32 >> b) >= c.nc) ++b;
+    return b;
+}
+
+// One block of steps of the wave-uniform packet q (word position wp, at least 64 steps below the
+// step cap).  Returns true when it stopped at a step that lane 0 has to take.
+template <bool WGT, bool CEN>
+__device__ __forceinline__ bool window_block(Pk1 &q, uint64_t &wp, const DevCloud &c, const uint8_t *__restrict__ tb,
+                                             const McArgs &a, unsigned long long *__restrict__ tally, int lane, int &nt,
+                                             int &ns)
+{
+    Window1 w;
+    window_load<WGT>(w, q, c, tb, window_shape(c, nt, ns), lane);
+    // pair `lane` of the stream from wp on
+    const uint64_t first = wp + 2ull * (uint64_t)lane;
+    const uint64_t blk = first >> 2;
+    const u32x4 r = philox4x32_10((uint32_t)blk, a.dom | (uint32_t)(blk >> 32), q.r.pid, q.r.key, a.key0, a.key1);
+    const uint32_t after = (uint32_t)__shfl_down((int)r.x, 1);   // first word of the next lane's block
+    const int ix = (int)(first & 3ull);
+    const uint32_t wa = ix == 0 ? r.x : (ix == 1 ? r.y : (ix == 2 ? r.z : r.w));
+    const uint32_t wb = ix == 0 ? r.y : (ix == 1 ? r.z : (ix == 2 ? r.w : after));
+    const int m = (wp & 1ull) ? 63 : 64;
+    const int p0 = (int)rl((uint32_t)(((q.cell - w.wi) << w.b) + (q.j - w.wj)), 0);
+    int p = p0, post = 63;
+    window_from<0>(w, c, wa, wb, lane, p, post);
+    int pre = __shfl_up(post, 1);
+    if (lane == 0) pre = p0;
+    const bool face = (pre & kPend) != 0;      // this pair decides the face of the step before
+    const int at = pre & 63;
+    const uint32_t lk = (uint32_t)__shfl((int)w.lk, at), fl = (uint32_t)__shfl((int)w.flags, at);
+    const uint32_t dh = (uint32_t)__shfl((int)w.dhi, at), sh = (uint32_t)__shfl((int)w.shi, at);
+    const uint32_t ah = (uint32_t)__shfl((int)w.ahi, at), split = (uint32_t)__shfl((int)w.split, at);
+    const bool spatial = wb >= sh;
+    const int f = (wa >> 1) >= split ? 1 : 0;
+    // the first pair a block leaves out: a step lane 0 takes (its event pair, also where its face
+    // pair decides it), or the end
+    // (in moving clouds a leak out of the window too: where it ends is not known here)
+    const bool hard = face ? (fl & (1u << (kFlagFaceShift + f))) != 0u || (c.moving && post == 63)
+                           : (wb == dh || wb == sh ||
+                              (spatial ? wb >= ah || (c.moving && !c.uniform_bins)
+                                       : (fl & (wb < dh ? kFlagDnThin : kFlagUpThin)) != 0u));
+    const uint64_t hm = __ballot(hard), fm = __ballot(face);
+    uint64_t cutm = (hm & ~fm) | ((hm & fm) >> 1) | (m < 64 ? 1ull << 63 : 0ull);
+    // a move out of the window completes its step: the block ends after its pair (the stop position
+    // of a pair that lane 0 does not have to take)
+    const uint64_t outm = __ballot(post == 63 && !hard);
+    const int out = outm ? __ffsll((unsigned long long)outm) - 1 : 64;
+    int done = cutm ? __ffsll((unsigned long long)cutm) - 1 : 64;
+    bool stopped = done < m && done <= out;
+    if (out < done) {
+        done = out + 1;
+        stopped = false;
+    }
+    // a last event pair whose face pair is not in the block waits for the next one
+    if (!stopped && done > 0 && done <= 64) {
+        const bool last_event = !((fm >> (done - 1)) & 1ull);
+        const bool last_spatial = rl((spatial && !face) ? 1u : 0u, done - 1) != 0u;
+        if (last_event && last_spatial) --done;
+    }
+    // residences of the event pairs
+    const bool ev = lane < done && !face;
+    double dd = ev ? (double)ddmc_path(wa, __uint_as_float(lk)) : 0.0;
+    double t = q.t;
+    double t0 = 0.0, t1 = 0.0;
+    // continuous dust weights: the log-weight, step by step in order; lane k keeps it before step k
+    const bool wgt = WGT && c.dust_weight;
+    double lw0 = 0.0, ka = 0.0, lw = 0.0;
+    if (wgt) {
+        ka = shfl_f64(w.ka, at);
+        lw = q.lw;
+        log_weight<CEN, 0>(lw, lw0, ka, dd);
+        if (lw > kLogWMin) return true;   // eliminated in this block: lane 0 finds the step
+    }
+    if (CEN && c.n_census > 0 && q.ci <= c.n_census) {
+        // every step's own clock: the block's integer sum as a prefix sum
+        double tt = q.t;
+        if (!clock_parallel(tt, dd)) return true;
+        const int e = (int)((((uint64_t)__double_as_longlong(q.t)) >> 52) & 0x7ffu) - 1023;
+        double n = rint(ldexp(dd, 52 - e));
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double v = __shfl_up(n, o);
+            if (lane >= o) n += v;
+        }
+        t1 = q.t + ldexp(n, e - 52);
+        t0 = __shfl_up(t1, 1);
+        if (lane == 0) t0 = q.t;
+        const uint64_t cross = __ballot(ev && t1 > q.tn);
+        if (cross) {   // that step, and what follows, is left to lane 0
+            const int k = __ffsll((unsigned long long)cross) - 1;
+            if (k < done) {
+                done = k;
+                stopped = true;
+            }
+        }
+        t = done > 0 ? rl_f64(t1, done - 1) : q.t;
+        if (q.ci > 0) {
+            // the block's residences per position, then one add per visited state
+            unsigned long long *acc = s_path_block + (threadIdx.x & ~63);
+            acc[lane] = 0ull;
+            __builtin_amdgcn_wave_barrier();
+            if (lane < done && !face && t1 > t0) {
+                const double r = wgt ? weight_integral(t0, t1, t0, lw0, ka) : t1 - t0;
+                atomicAdd(&acc[at], (unsigned long long)rint(r * kPathFix));
+            }
+            __builtin_amdgcn_wave_barrier();
+            const unsigned long long v = acc[lane];
+            if (v) {
+                const int64_t s = (int64_t)(w.wi + (lane >> w.b)) * c.nb + w.wj + (lane & ((1 << w.b) - 1));
+                atomicAdd(&tally[c.tally_off + c.census_path_off + (uint64_t)(q.ci - 1) * c.n_states + s], v);
+            }
+        }
+        // eq. 18: a leak's outward and inward terms over its step's residence
+        const double ts = __shfl_up(t0, 1), ls = __shfl_up(lw0, 1);   // face pairs: the event pair before
+        if (lane < done && face) {
+            const double *kt = reinterpret_cast<const double *>(tb + c.off_k);
+            const int i = w.wi + (at >> w.b), j = w.wj + (at & ((1 << w.b) - 1));
+            const int i2 = f ? i + 1 : i - 1, j2 = post == 63 ? j : w.wj + (post & ((1 << w.b) - 1));
+            const double dir = f ? 1.0 : -1.0;
+            accel_add<WGT>(c, tb, tally, i, ts, t0, dir * kt[(int64_t)i * c.nb + j], ls, ka, q.ci);
+            accel_add<WGT>(c, tb, tally, i2, ts, t0, dir * kt[(int64_t)i2 * c.nb + j2], ls, ka, q.ci);
+        }
+    } else if (done > 0 && !clock_parallel(t, dd)) {
+        clock_from<0>(t, (uint32_t)__double_as_longlong(dd), (uint32_t)((uint64_t)__double_as_longlong(dd) >> 32), done);
+    }
+    if (done == 0) return stopped;
+    // the state after the last pair: inside the window, or one move out of it
+    const int l = done - 1;
+    const int pl = (int)rl((uint32_t)post, l);
+    if (pl != 63) {
+        q.cell = w.wi + ((pl & 63) >> w.b);
+        q.j = w.wj + (pl & 63 & ((1 << w.b) - 1));
+    } else {
+        const int al = (int)rl((uint32_t)at, l);
+        q.cell = w.wi + (al >> w.b);
+        q.j = w.wj + (al & ((1 << w.b) - 1));
+        if ((fm >> l) & 1ull)
+            q.cell += rl((uint32_t)f, l) ? 1 : -1;
+        else
+            q.j += rl(wb < dh ? 1u : 0u, l) ? -1 : 1;
+    }
+    q.t = t;
+    // (only a census time cuts a block after its residences were laid out)
+    if (wgt) q.lw = CEN && done < 64 ? rl_f64(lw0, done) : lw;
+    wp += 2ull * (uint64_t)done;
+    const int steps = __popcll(__ballot(lane < done && !face));
+    q.steps += (uint64_t)steps;
+    nt += steps;
+    ns += __popcll(__ballot(lane < done && face));
+    if (nt > 512) {   // forget older steps
+        nt >>= 1;
+        ns >>= 1;
+    }
+    return stopped;
+}
+
+__device__ __forceinline__ uint64_t rl64(uint64_t v, int l)
+{
+    return ((uint64_t)rl((uint32_t)(v >> 32), l) << 32) | rl((uint32_t)v, l);
+}
+__device__ __forceinline__ float rlf(float v, int l) { return __uint_as_float(rl(__float_as_uint(v), l)); }
+
+// The fields of lane l's packet that a DDMC state carries, wave-uniform.
+__device__ __forceinline__ void share_ddmc(Pk1 &q, const Pk1 &p, int l)
+{
+    q.cell = (int)rl((uint32_t)p.cell, l);
+    q.j = (int)rl((uint32_t)p.j, l);
+    q.active = rl(p.active ? 1u : 0u, l) != 0u;
+    q.t = rl_f64(p.t, l);
+    q.ci = (int)rl((uint32_t)p.ci, l);
+    q.tn = rl_f64(p.tn, l);
+    q.steps = rl64(p.steps, l);
+    q.mcs = rl(p.mcs, l);
+    q.tomc = rl(p.tomc, l);
+    q.toddmc = rl(p.toddmc, l);
+    q.refl = rl(p.refl, l);
+}
+
+// One packet handed over by the lane walk (its census sums flushed).
+struct Tail1 {             // 104 bytes
+    uint32_t cl, pid;
+    int32_t cell, j;
+    uint64_t steps, words;
+    double t;
+    uint32_t mcs, tomc, toddmc, refl;
+    int32_t ci;
+    uint32_t flags;        // bit 0 continuous MC, bit 1 left_inner
+    float pos[3], n[3];
+    float x;
+    uint32_t pad;
+    double lw;
+};
+static_assert(sizeof(Tail1) == 104, "export slots are sized by the work-area query");
+// Work area (u64 words): [0] packet queue, [8] export slots handed out, [16] slots walked; slots
+// from byte 256 on.
+constexpr int kWGiven = 8, kWTaken = 16;
+
+__device__ __forceinline__ Tail1 *slots_of(unsigned long long *work)
+{
+    return reinterpret_cast<Tail1 *>(reinterpret_cast<uint8_t *>(work) + 256);
+}
+
+// Walk the packet of an export slot to its end with the whole wave.
+template <bool SPH, bool WGT, bool CEN>
+__device__ __forceinline__ void coop_walk1(const Tail1 &k, const DevCloud *__restrict__ clouds,
+                                           const uint8_t *__restrict__ tb, const McArgs &a,
+                                           unsigned long long *__restrict__ tally, const float *__restrict__ vtab,
+                                           const float *__restrict__ u0tab, int lane)
+{
+    Pk1 q;                                    // the packet, wave-uniform (DDMC fields)
+    q.cl = (int)rl(k.cl, 0);
+    const DevCloud &c = clouds[q.cl];
+    q.cell = (int)rl((uint32_t)k.cell, 0);
+    q.j = (int)rl((uint32_t)k.j, 0);
+    q.active = true;
+    q.t = rl_f64(k.t, 0);
+    q.ci = (int)rl((uint32_t)k.ci, 0);
+    q.tn = -__builtin_inf();                  // found again by the first residence
+    q.steps = rl64(k.steps, 0);
+    q.mcs = rl(k.mcs, 0);
+    q.tomc = rl(k.tomc, 0);
+    q.toddmc = rl(k.toddmc, 0);
+    q.refl = rl(k.refl, 0);
+    q.lw = WGT ? rl_f64(k.lw, 0) : 0.0;
+    q.r.pid = rl(k.pid, 0);
+    q.r.key = c.stream;
+    uint64_t wp = rl64(k.words, 0);
+    Pk1 s = q;                                // lane 0's own copy, with the continuous-MC fields
+    s.mc = (k.flags & 1u) != 0u;
+    s.left_inner = (k.flags & 2u) != 0u;
+    s.pos = make_float3(k.pos[0], k.pos[1], k.pos[2]);
+    s.n = make_float3(k.n[0], k.n[1], k.n[2]);
+    s.x = k.x;
+    s.cn = 0u;
+    bool alone = true;
+    int singles = 1, nt = 64, ns = 2;
+    while (q.active) {
+        if (!alone && a.max_steps - q.steps < 64ull) {   // near the cap
+            alone = true;
+            singles = 64;
+        }
+        if (alone) {
+            if (lane == 0) {
+                s.cell = q.cell;
+                s.j = q.j;
+                s.t = q.t;
+                s.ci = q.ci;
+                s.tn = q.tn;
+                s.steps = q.steps;
+                s.lw = q.lw;
+                set_words(s.r, wp, a);
+                do {
+                    if (s.steps >= a.max_steps) {
+                        finish1<WGT, CEN>(s, c, tally, false, 0, 0);
+                        break;
+                    }
+                    ++s.steps;
+                    if (!s.mc)
+                        ddmc_step1<SPH, WGT, CEN>(s, c, tb, a, tally);
+                    else if (c.groups)
+                        grp_step1<SPH, WGT, CEN>(s, c, tb, a, tally);
+                    else
+                        mc_step1<SPH, WGT, CEN>(s, c, tb, a, tally, vtab, u0tab);
+                } while (s.active && (s.mc || --singles > 0));
+                wp = word_pos(s.r);
+            }
+            share_ddmc(q, s, 0);
+            if (WGT) q.lw = rl_f64(s.lw, 0);
+            wp = rl64(wp, 0);
+            alone = false;
+            singles = 1;
+            continue;
+        }
+        alone = window_block<WGT, CEN>(q, wp, c, tb, a, tally, lane, nt, ns);
+    }
+}
+
+// The packets the lane walk handed over, each by a whole wave.
+template <bool SPH, bool WGT, bool CEN>
+__global__ __launch_bounds__(256) void walk1dh_coop(const uint8_t *__restrict__ tb, McArgs a,
+                                                    unsigned long long *__restrict__ tally,
+                                                    unsigned long long *__restrict__ work)
+{
+    const uint64_t given = work[kWGiven];
+    const uint64_t n = given < a.slots ? given : a.slots;
+    if (n == 0) return;
+    const DevHeader *H = reinterpret_cast<const DevHeader *>(tb);
+    const DevCloud *clouds = reinterpret_cast<const DevCloud *>(tb + H->off_clouds);
+    const float *vtab = reinterpret_cast<const float *>(tb + H->off_voigt);
+    const float *u0tab = reinterpret_cast<const float *>(tb + H->off_u0);
+    const int lane = threadIdx.x & 63;
+    if (CEN) path_init();
+    for (;;) {
+        uint64_t i = 0;
+        if (lane == 0) i = atomicAdd(&work[kWTaken], 1ull);
+        i = rl64(i, 0);
+        if (i >= n) break;
+        coop_walk1<SPH, WGT, CEN>(slots_of(work)[i], clouds, tb, a, tally, vtab, u0tab, lane);
+    }
+}
+
+constexpr int kCoopLanes = 16;            // most lanes per wave of a job too small to fill the device
+
+// Lanes whose packets the cooperative walk should take now (0: none).  A side-by-side step costs
+// ~1000 issue cycles whatever the lanes, a cooperative one ~48, and a continuous-MC event ~4000
+// either way: with a share f of MC events the hand-over pays below (1000 + 4000 f) / (48 + 4000 f)
+// lanes, and never for packets that are mostly in MC states.
+__device__ __forceinline__ uint64_t hand_over(const Pk1 &p)
+{
+    const bool fit = p.active && p.steps >= 64ull && 32ull * p.mcs < p.steps;
+    const uint64_t m = __ballot(fit);
+    if (!m) return 0ull;
+    float st = fit ? (float)p.steps : 0.0f, mc = fit ? (float)p.mcs : 0.0f;
+    for (int o = 32; o > 0; o >>= 1) {
+        st += __shfl_xor(st, o);
+        mc += __shfl_xor(mc, o);
+    }
+    const float f = 4000.0f * mc;
+    return (float)__popcll(m) * (48.0f * st + f) < 1000.0f * st + f ? m : 0ull;
+}
+
 template <bool SPH, bool SINGLE, bool WGT, bool CEN>
 __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, McArgs a,
                                                unsigned long long *__restrict__ tally,
@@ -740,7 +1232,7 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
 
     for (;;) {
         if (!exhausted) {
-            const uint64_t need = __ballot(!p.active);
+            const uint64_t need = __ballot(!p.active && lane < a.lanes);
             if (need) {
                 const int leader = __ffsll((unsigned long long)need) - 1;
                 const int cnt = __popcll(need);
@@ -748,7 +1240,7 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
                 if (lane == leader) base = atomicAdd(work, (unsigned long long)cnt);
                 base = shfl64(base, leader);
                 if (base + cnt >= a.count) exhausted = true;
-                if (!p.active) {
+                if (!p.active && lane < a.lanes) {
                     const uint64_t q = base + __popcll(need & ((1ull << lane) - 1ull));
                     if (q < a.count) {
                         const uint64_t g = a.first + q;
@@ -802,6 +1294,44 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
             }
         }
         if (!__any(p.active)) break;
+        // few packets left (or few per wave from the start): handed over to the cooperative walk
+        const uint64_t go = a.slots && (exhausted || a.lanes <= kCoopLanes) ? hand_over(p) : 0ull;
+        if (go) {
+            const int leader = __ffsll((unsigned long long)go) - 1;
+            uint64_t base = 0;
+            if (lane == leader) base = atomicAdd(&work[kWGiven], (unsigned long long)__popcll(go));
+            base = shfl64(base, leader) + __popcll(go & ((1ull << lane) - 1ull));
+            if (((go >> lane) & 1ull) && base < a.slots) {
+                const DevCloud &c = clouds[p.cl];
+                if (CEN && c.n_census > 0) path_flush(p, tally + c.tally_off + c.census_path_off);
+                Tail1 k;
+                k.cl = (uint32_t)p.cl;
+                k.pid = p.r.pid;
+                k.cell = p.cell;
+                k.j = p.j;
+                k.steps = p.steps;
+                k.words = word_pos(p.r);
+                k.t = p.t;
+                k.mcs = p.mcs;
+                k.tomc = p.tomc;
+                k.toddmc = p.toddmc;
+                k.refl = p.refl;
+                k.ci = p.ci;
+                k.flags = (p.mc ? 1u : 0u) | (p.left_inner ? 2u : 0u);
+                k.pos[0] = p.pos.x;
+                k.pos[1] = p.pos.y;
+                k.pos[2] = p.pos.z;
+                k.n[0] = p.n.x;
+                k.n[1] = p.n.y;
+                k.n[2] = p.n.z;
+                k.x = p.x;
+                k.pad = 0u;
+                k.lw = p.lw;
+                slots_of(work)[base] = k;
+                p.active = false;
+            }
+            if (!__any(p.active)) continue;   // (packets that found no slot walk on here)
+        }
 
         // Mode-batched passes, as on 3D grids: DDMC lanes take up to two steps, or MC lanes
         // one event; every packet's own sequence of steps and draws is unchanged by this.
@@ -835,15 +1365,16 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
 
 __global__ void reset_queue1(unsigned long long *work)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) work[0] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x < 32) work[threadIdx.x] = 0ull;
 }
 
 }  // namespace
 
-hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, const rddmc_run &run, uint64_t first,
-                          uint64_t count, unsigned long long *d_tally, unsigned long long *d_work, hipStream_t s)
+hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_thick, const rddmc_run &run,
+                          uint64_t first, uint64_t count, unsigned long long *d_tally, unsigned long long *d_work,
+                          uint64_t work_bytes, hipStream_t s)
 {
-    McArgs a;
+    McArgs a{};
     a.first = first;
     a.count = count;
     a.max_steps = run.max_steps;
@@ -854,8 +1385,19 @@ hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, const rdd
     a.dom = kDom1DH;
     const int block = run.block > 0 ? run.block : 256;
     uint64_t grid = run.grid > 0 ? (uint64_t)run.grid : 0;
+    // The cooperative walk suits DDMC steps: not where no state is thick, and not asked for with
+    // tail_lanes < 0.  Jobs with fewer than kCoopLanes packets for each of two waves per SIMD
+    // spread over the device with that many lanes per wave.
+    const bool coop = any_thick && run.tail_lanes >= 0;
+    a.slots = coop && work_bytes > 256 ? (work_bytes - 256) / sizeof(Tail1) : 0;
+    a.lanes = 64;
+    if (grid == 0 && a.slots) {
+        const uint64_t waves = 8ull * (uint64_t)device_cu_count();
+        const uint64_t per = (count + waves - 1) / waves;
+        if (per <= kCoopLanes) a.lanes = per < 1 ? 1 : (int)per;
+    }
     if (grid == 0) {
-        const uint64_t want = (count + block - 1) / block;
+        const uint64_t want = (count + (uint64_t)a.lanes * (block / 64) - 1) / ((uint64_t)a.lanes * (block / 64));
         const uint64_t cap = (uint64_t)device_cu_count() * 8;
         grid = want < cap ? want : cap;
         if (grid < 1) grid = 1;
@@ -875,6 +1417,12 @@ hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, const rdd
             walk1dh<false, true, W, C><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
         else
             walk1dh<false, false, W, C><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
+        if (!a.slots) return;
+        const unsigned blocks = (unsigned)std::min<uint64_t>((count + 3) / 4, 4ull * (uint64_t)device_cu_count());
+        if (sph)
+            walk1dh_coop<true, W, C><<<blocks, 256, 0, s>>>(d_tables, a, d_tally, d_work);
+        else
+            walk1dh_coop<false, W, C><<<blocks, 256, 0, s>>>(d_tables, a, d_tally, d_work);
     };
     if (h.dust_weight1d && h.census1d)
         go(std::true_type{}, std::true_type{});
