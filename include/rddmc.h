@@ -193,8 +193,8 @@ typedef struct {
  *   tail_lanes   once every packet of the run has started, a wave with at most this many
  *                packets left hands them to a cooperative walk in which a whole wave
  *                advances one packet (0 = automatic: 16, up to 64 in runs too small to
- *                occupy the device; < 0 = never).  The hybrid 1D walk decides by the packets'
- *                share of continuous-MC events when it is not negative.  Results are
+ *                occupy the device; < 0 = never).  The hybrid walks decide by the packets'
+ *                shares of events when it is not negative.  Results are
  *                bit-identical either way.
  *   surrogate    1D clouds: learned escape surrogate (rddmc_surrogate_attach), exact exit
  *                kernel (rddmc_exitkernel_build) or NULL for plain rDDMC; with one, a packet
@@ -296,8 +296,8 @@ rddmc_status rddmc_table_bytes(const rddmc_batch *batch, size_t *bytes);
  * rddmc_tally_reset or any fill before the first run; runs accumulate). */
 rddmc_status rddmc_tally_bytes(const rddmc_batch *batch, size_t *bytes);
 
-/* Device bytes for the transport work area: queue counters and one slot (48 bytes; hybrid 1D
- * batches 104) per resident lane for packets handed to the cooperative tail walk. */
+/* Device bytes for the transport work area: queue counters and one slot (48 bytes; 3D 88,
+ * hybrid 1D 104) per resident lane for packets handed to the cooperative tail walk. */
 rddmc_status rddmc_work_bytes(const rddmc_batch *batch, size_t *bytes);
 
 /* ---- the path ------------------------------------------------------------------------ */

@@ -437,10 +437,10 @@ rddmc_status rddmc_work_bytes(const rddmc_batch *batch, size_t *bytes)
     Layout L;
     rddmc_status st = make_layout(batch, L);
     if (st != RDDMC_OK) return st;
-    // queue counters, then one slot (48 bytes; hybrid 1D walk: 104) per lane that may hand its
+    // queue counters, then one slot (48 bytes; 3D: 88, hybrid 1D: 104) per lane that may hand its
     // packet to the cooperative tail walk (at most 2^20 lanes are ever resident)
     const uint64_t lanes = L.h.total_packets < (1ull << 20) ? L.h.total_packets : (1ull << 20);
-    *bytes = 256 + (L.h.hybrid1d ? 104 : 48) * lanes;
+    *bytes = 256 + (L.h.geometry == RDDMC_CART3D ? 88 : (L.h.hybrid1d ? 104 : 48)) * lanes;
     return RDDMC_OK;
 }
 
@@ -572,7 +572,8 @@ rddmc_status rddmc_transport(const rddmc_batch *batch, const void *d_tables, con
     if (L.h.geometry == RDDMC_CART3D) {
         hipError_t e = launch_walk3d(static_cast<const uint8_t *>(d_tables), L.h, *run, run->first, count,
                                      static_cast<unsigned long long *>(d_tally),
-                                     static_cast<unsigned long long *>(d_work), reinterpret_cast<hipStream_t>(stream));
+                                     static_cast<unsigned long long *>(d_work), work_bytes,
+                                     reinterpret_cast<hipStream_t>(stream));
         return e == hipSuccess ? RDDMC_OK : hip_fail(e, "3D walk kernel");
     }
     if (L.h.hybrid1d) {

@@ -19,14 +19,15 @@ constexpr int kUparMaxTries = 1 << 20;          // the sampler's acceptance is >
 
 // Launch arguments of the hybrid walks: packet range, step cap, Philox key (the run's seed),
 // steps between refills, number of clouds, the counter domain of the walk's streams, and how the
-// 1D walk shares packets out.
+// packets are shared out.
 struct McArgs {
     uint64_t first, count, max_steps;
     uint32_t key0, key1;
     int32_t chunk, n_clouds;
     uint32_t dom;
-    int32_t lanes;     // 1D: lanes of a wave that take packets
-    uint64_t slots;    // 1D: export slots for the cooperative walk (0: it takes no packets)
+    int32_t lanes;     // lanes of a wave that take packets
+    int32_t one_round; // there is a lane for every packet: the queue is empty after one refill
+    uint64_t slots;    // export slots for the cooperative walk (0: it takes no packets)
 };
 
 // Per-packet stream: block b is Philox4x32-10 of counter (b_lo, dom | b_hi, packet id,
@@ -85,6 +86,29 @@ __device__ __forceinline__ uint32_t draw(Rng &r, const McArgs &a)
     const uint32_t v = r.idx == 0u ? r.c0 : (r.idx == 1u ? r.c1 : (r.idx == 2u ? r.c2 : r.c3));
     ++r.idx;
     return v;
+}
+
+// Words of the stream consumed so far, and the stream positioned there.
+__device__ __forceinline__ uint64_t word_pos(const Rng &r)
+{
+    const uint64_t next = ((uint64_t)r.ctr_hi << 32) | r.ctr;
+    return 4ull * (next - (r.ahead ? 2ull : 1ull)) + r.idx;
+}
+__device__ __forceinline__ void set_words(Rng &r, uint64_t wp, const McArgs &a)
+{
+    const uint64_t blk = wp >> 2;
+    r.ctr = (uint32_t)blk;
+    r.ctr_hi = (uint32_t)(blk >> 32);
+    r.ahead = false;
+    r.idx = 4u;
+    if (wp & 3ull) {
+        const u32x4 w = next_block(r, a);
+        r.c0 = w.x;
+        r.c1 = w.y;
+        r.c2 = w.z;
+        r.c3 = w.w;
+        r.idx = (uint32_t)wp & 3u;
+    }
 }
 
 // 24-bit uniform in (0, 1) (exactly representable, never 0 or 1)

@@ -733,29 +733,6 @@ struct Window1 {
 constexpr int kPend = 64;                 // position bit: the face pair comes next
 __shared__ unsigned long long s_path_block[kBlockMax];   // a block's residence sums per position
 
-// Words of the stream consumed so far, and the stream positioned there.
-__device__ __forceinline__ uint64_t word_pos(const Rng &r)
-{
-    const uint64_t next = ((uint64_t)r.ctr_hi << 32) | r.ctr;
-    return 4ull * (next - (r.ahead ? 2ull : 1ull)) + r.idx;
-}
-__device__ __forceinline__ void set_words(Rng &r, uint64_t wp, const McArgs &a)
-{
-    const uint64_t blk = wp >> 2;
-    r.ctr = (uint32_t)blk;
-    r.ctr_hi = (uint32_t)(blk >> 32);
-    r.ahead = false;
-    r.idx = 4u;
-    if (wp & 3ull) {
-        const u32x4 w = next_block(r, a);
-        r.c0 = w.x;
-        r.c1 = w.y;
-        r.c2 = w.z;
-        r.c3 = w.w;
-        r.idx = (uint32_t)wp & 3u;
-    }
-}
-
 template <bool WGT>
 __device__ __forceinline__ void window_load(Window1 &w, const Pk1 &q, const DevCloud &c, const uint8_t *__restrict__ tb,
                                             int b, int lane)
@@ -1032,12 +1009,6 @@ __device__ __forceinline__ bool window_block(Pk1 &q, uint64_t &wp, const DevClou
     return stopped;
 }
 
-__device__ __forceinline__ uint64_t rl64(uint64_t v, int l)
-{
-    return ((uint64_t)rl((uint32_t)(v >> 32), l) << 32) | rl((uint32_t)v, l);
-}
-__device__ __forceinline__ float rlf(float v, int l) { return __uint_as_float(rl(__float_as_uint(v), l)); }
-
 // The fields of lane l's packet that a DDMC state carries, wave-uniform.
 __device__ __forceinline__ void share_ddmc(Pk1 &q, const Pk1 &p, int l)
 {
@@ -1177,8 +1148,6 @@ __global__ __launch_bounds__(256) void walk1dh_coop(const uint8_t *__restrict__ 
     }
 }
 
-constexpr int kCoopLanes = 16;            // most lanes per wave of a job too small to fill the device
-
 // Lanes whose packets the cooperative walk should take now (0: none).  A side-by-side step costs
 // ~1000 issue cycles whatever the lanes, a cooperative one ~48, and a continuous-MC event ~4000
 // either way: with a share f of MC events the hand-over pays below (1000 + 4000 f) / (48 + 4000 f)
@@ -1239,7 +1208,7 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
                 uint64_t base = 0;
                 if (lane == leader) base = atomicAdd(work, (unsigned long long)cnt);
                 base = shfl64(base, leader);
-                if (base + cnt >= a.count) exhausted = true;
+                if (base + cnt >= a.count || a.one_round) exhausted = true;
                 if (!p.active && lane < a.lanes) {
                     const uint64_t q = base + __popcll(need & ((1ull << lane) - 1ull));
                     if (q < a.count) {
@@ -1294,8 +1263,8 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
             }
         }
         if (!__any(p.active)) break;
-        // few packets left (or few per wave from the start): handed over to the cooperative walk
-        const uint64_t go = a.slots && (exhausted || a.lanes <= kCoopLanes) ? hand_over(p) : 0ull;
+        // few packets left: handed over to the cooperative walk
+        const uint64_t go = a.slots && exhausted ? hand_over(p) : 0ull;
         if (go) {
             const int leader = __ffsll((unsigned long long)go) - 1;
             uint64_t base = 0;
@@ -1386,15 +1355,16 @@ hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_
     const int block = run.block > 0 ? run.block : 256;
     uint64_t grid = run.grid > 0 ? (uint64_t)run.grid : 0;
     // The cooperative walk suits DDMC steps: not where no state is thick, and not asked for with
-    // tail_lanes < 0.  Jobs with fewer than kCoopLanes packets for each of two waves per SIMD
-    // spread over the device with that many lanes per wave.
+    // tail_lanes < 0.  Jobs of less than a wave per SIMD spread over the device, fewer lanes to a
+    // wave: the lanes do not wait longer, and the cooperative walk finds the packets where it has
+    // issue slots.
     const bool coop = any_thick && run.tail_lanes >= 0;
     a.slots = coop && work_bytes > 256 ? (work_bytes - 256) / sizeof(Tail1) : 0;
     a.lanes = 64;
-    if (grid == 0 && a.slots) {
-        const uint64_t waves = 8ull * (uint64_t)device_cu_count();
+    if (grid == 0) {
+        const uint64_t waves = 4ull * (uint64_t)device_cu_count();
         const uint64_t per = (count + waves - 1) / waves;
-        if (per <= kCoopLanes) a.lanes = per < 1 ? 1 : (int)per;
+        a.lanes = per < 64 ? (int)per : 64;
     }
     if (grid == 0) {
         const uint64_t want = (count + (uint64_t)a.lanes * (block / 64) - 1) / ((uint64_t)a.lanes * (block / 64));
@@ -1402,6 +1372,7 @@ hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_
         grid = want < cap ? want : cap;
         if (grid < 1) grid = 1;
     }
+    a.one_round = grid * (uint64_t)(block / 64) * (uint64_t)a.lanes >= count ? 1 : 0;
     reset_queue1<<<1, 64, 0, s>>>(d_work);
     const bool sph = h.geometry == RDDMC_SPHERE;
     const bool single = h.n_clouds == 1;

@@ -31,9 +31,12 @@
 // Escapes add face, lab bin, boundary pixel and time to the exact int64 tallies.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "mc_dev.h"
 #include "philox.h"
 #include "rddmc_internal.h"
+#include "wave_dev.h"
 
 namespace rddmc {
 
@@ -374,6 +377,187 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// ---- cooperative walk of one packet ----------------------------------------------------------
+// A lone lane takes ~0.65 us per DDMC step (its chain of dependent instructions and gathers), so a
+// wave's last packets are walked by whole waves, one packet each.  In a block, lane k draws the
+// k-th pair {time, event} of the packet's stream, the lanes hold the records of 63 bins of its
+// cell, every lane computes where event k would take a packet in its bin, and the packet's bin
+// follows by one readlane per step.  Lane 63 is the stop: a move out of the band (completed after
+// the chain) and what a block does not take, a tie, a spatial leak or a leak into a thin bin; those
+// steps, and the continuous-MC events that follow, run in lane 0 with the step functions until the
+// packet is in a DDMC state again.
+struct Tail3 {             // 88 bytes: a packet handed over by the lane walk
+    uint32_t cl, pid;
+    int32_t cell, j;
+    uint64_t steps, words;
+    double t;
+    uint32_t mcs, tomc, toddmc, refl;
+    uint32_t flags;        // bit 0 continuous MC, bit 1 a spatial leak to apply
+    float pos[3], n[3];
+    float x;
+};
+static_assert(sizeof(Tail3) == 88, "export slots are sized by the work-area query");
+// Work area (u64 words): [0] packet queue, [8] export slots handed out, [16] slots walked; slots
+// from byte 256 on.
+constexpr int kWGiven = 8, kWTaken = 16;
+
+__device__ __forceinline__ Tail3 *slots_of(unsigned long long *work)
+{
+    return reinterpret_cast<Tail3 *>(reinterpret_cast<uint8_t *>(work) + 256);
+}
+
+struct Band3 {
+    uint32_t lk, dhi, shi, flags;   // the lane's record
+    int dn, up;                     // where a frequency move leads (63: stop)
+};
+
+template <int G>
+__device__ __forceinline__ void band_from(const Band3 &w, uint32_t ew, int &p, int &post)
+{
+#define RDDMC_BAND_STEP(K)                                                       \
+    {                                                                            \
+        const uint32_t e = rl(ew, 8 * G + K);                                    \
+        const int f = e < w.dhi ? w.dn : w.up;                                   \
+        p = (int)rl((uint32_t)(e < w.shi ? f : 63), p);                          \
+        post = write_lane(p, 8 * G + K, post);                                   \
+    }
+    RDDMC_BAND_STEP(0) RDDMC_BAND_STEP(1) RDDMC_BAND_STEP(2) RDDMC_BAND_STEP(3)
+    RDDMC_BAND_STEP(4) RDDMC_BAND_STEP(5) RDDMC_BAND_STEP(6) RDDMC_BAND_STEP(7)
+#undef RDDMC_BAND_STEP
+    if constexpr (G < 7) {
+        if (p != 63) band_from<G + 1>(w, ew, p, post);
+    }
+}
+
+// One block of up to 64 frequency steps of a packet in (cell, j) (all arguments wave-uniform, at
+// least 64 steps below the step cap); returns true when it stopped at a step for lane 0.
+__device__ __forceinline__ bool band_block(const DevCloud &c, const uint8_t *__restrict__ tb, const Walk3Args &a,
+                                           uint32_t pid, uint32_t key, int cell, int &j, double &t, uint64_t &steps,
+                                           uint64_t &wp, int lane)
+{
+    const int nb = c.nb;
+    int j0 = j - 31;
+    if (j0 > nb - 63) j0 = nb - 63;
+    if (j0 < 0) j0 = 0;
+    const bool in = lane < 63 && j0 + lane < nb;
+    const uint4 r = reinterpret_cast<const uint4 *>(tb + c.off_hot)[(int64_t)cell * nb + (in ? j0 + lane : 0)];
+    const Band3 w{r.x, r.y, r.z, r.w, in && lane > 0 && !(r.w & kFlagDnThin) ? lane - 1 : 63,
+                  in && !(r.w & kFlagUpThin) ? lane + 1 : 63};
+    // pair `lane` of the stream from wp on
+    const uint64_t first = wp + 2ull * (uint64_t)lane;
+    const u32x4 b = philox4x32_10((uint32_t)(first >> 2), a.dom | (uint32_t)(first >> 34), pid, key, a.key0, a.key1);
+    const uint32_t after = (uint32_t)__shfl_down((int)b.x, 1);   // first word of the next lane's block
+    const int ix = (int)(first & 3ull);
+    const uint32_t tw = ix == 0 ? b.x : (ix == 1 ? b.y : (ix == 2 ? b.z : b.w));
+    const uint32_t ew = ix == 0 ? b.y : (ix == 1 ? b.z : (ix == 2 ? b.w : after));
+    const int m = (wp & 1ull) ? 63 : 64;   // lane 63's pair may end in a block no lane drew
+    const int p0 = (int)rl((uint32_t)(j - j0), 0);
+    int p = p0, post = 63;
+    band_from<0>(w, ew, p, post);
+    int at = __shfl_up(post, 1);
+    if (lane == 0) at = p0;
+    const uint32_t lk = (uint32_t)__shfl((int)w.lk, at), fl = (uint32_t)__shfl((int)w.flags, at);
+    const uint32_t dh = (uint32_t)__shfl((int)w.dhi, at), sh = (uint32_t)__shfl((int)w.shi, at);
+    const bool hard = ew == dh || ew >= sh || (fl & (ew < dh ? kFlagDnThin : kFlagUpThin)) != 0u;
+    const uint64_t hm = __ballot(hard) | (m < 64 ? 1ull << 63 : 0ull), om = __ballot(post == 63 && !hard);
+    const int out = om ? __ffsll((unsigned long long)om) - 1 : 64;
+    int done = hm ? __ffsll((unsigned long long)hm) - 1 : 64;
+    bool stopped = done < m && done <= out;
+    if (out < done) {   // the move out of the band completes its step
+        done = out + 1;
+        stopped = false;
+    }
+    if (done == 0) return stopped;
+    const double dd = lane < done ? (double)ddmc_path(tw, __uint_as_float(lk)) : 0.0;
+    if (!clock_parallel(t, dd))
+        clock_from<0>(t, (uint32_t)__double_as_longlong(dd), (uint32_t)((uint64_t)__double_as_longlong(dd) >> 32), done);
+    const int l = done - 1;
+    j = j0 + (int)rl((uint32_t)at, l) + (rl(ew < dh ? 1u : 0u, l) ? -1 : 1);
+    steps += (uint64_t)done;
+    wp += 2ull * (uint64_t)done;
+    return stopped;
+}
+
+// The packets the lane walk handed over, each by a whole wave.
+__global__ __launch_bounds__(256) void walk3d_coop(const uint8_t *__restrict__ tb, Walk3Args a,
+                                                   unsigned long long *__restrict__ tally,
+                                                   unsigned long long *__restrict__ work)
+{
+    const uint64_t given = work[kWGiven];
+    const uint64_t n = given < a.slots ? given : a.slots;
+    if (n == 0) return;
+    const DevHeader *H = reinterpret_cast<const DevHeader *>(tb);
+    const DevCloud *clouds = reinterpret_cast<const DevCloud *>(tb + H->off_clouds);
+    const float *vtab = reinterpret_cast<const float *>(tb + H->off_voigt);
+    const float *u0tab = reinterpret_cast<const float *>(tb + H->off_u0);
+    const int lane = threadIdx.x & 63;
+    for (;;) {
+        uint64_t i = 0;
+        if (lane == 0) i = atomicAdd(&work[kWTaken], 1ull);
+        i = rl64(i, 0);
+        if (i >= n) break;
+        const Tail3 &k = slots_of(work)[i];
+        Pk s;                                     // lane 0's packet
+        s.cl = (int)rl(k.cl, 0);
+        const DevCloud &c = clouds[s.cl];
+        s.cell = k.cell;
+        s.ix = (int)(k.cell % c.n[0]);
+        s.iy = (int)((k.cell / c.n[0]) % c.n[1]);
+        s.iz = (int)(k.cell / ((int64_t)c.n[0] * c.n[1]));
+        s.j = k.j;
+        s.active = true;
+        s.mc = (k.flags & 1u) != 0u;
+        s.pend = (k.flags & 2u) != 0u;
+        s.pos = make_float3(k.pos[0], k.pos[1], k.pos[2]);
+        s.n = make_float3(k.n[0], k.n[1], k.n[2]);
+        s.x = k.x;
+        s.t = k.t;
+        s.steps = k.steps;
+        s.mcs = k.mcs;
+        s.tomc = k.tomc;
+        s.toddmc = k.toddmc;
+        s.refl = k.refl;
+        s.r.pid = k.pid;
+        s.r.key = c.stream;
+        const uint32_t pid = rl(k.pid, 0), key = c.stream;
+        uint64_t wp = rl64(k.words, 0);
+        const float lambda = (float)c.lambda;
+        int singles = 1;
+        for (;;) {
+            if (lane == 0) {
+                set_words(s.r, wp, a);
+                do {
+                    if (s.pend) {
+                        ddmc_leak(s, c, tb, a, tally);
+                    } else if (s.steps >= a.max_steps) {
+                        finish(s, c, tally, false, 0, 0);
+                    } else {
+                        ++s.steps;
+                        --singles;
+                        if (s.mc)
+                            mc_step(s, c, tb, a, tally, vtab, u0tab, lambda);
+                        else
+                            ddmc_event(s, c, tb, a);
+                    }
+                } while (s.active && (s.mc || s.pend || singles > 0));
+                wp = word_pos(s.r);
+            }
+            if (rl(s.active ? 1u : 0u, 0) == 0u) break;
+            wp = rl64(wp, 0);
+            const int cell = (int)rl((uint32_t)s.cell, 0);
+            int j = (int)rl((uint32_t)s.j, 0);
+            double t = rl_f64(s.t, 0);
+            uint64_t steps = rl64(s.steps, 0);
+            bool stop = false;
+            while (!stop && a.max_steps - steps >= 64ull) stop = band_block(c, tb, a, pid, key, cell, j, t, steps, wp, lane);
+            singles = stop ? 1 : 64;              // near the cap lane 0 goes on alone
+            s.j = j;
+            s.t = t;
+            s.steps = steps;
+        }
+    }
+}
+
 template <bool SINGLE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void walk3d(const uint8_t *__restrict__ tb, Walk3Args a,
                                               unsigned long long *__restrict__ tally,
@@ -397,18 +581,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
     p.mcs = p.tomc = p.toddmc = p.refl = 0u;
     p.r = Rng{0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 4u, false, 0u, 0u, 0u, 0u};
     bool exhausted = false;
+    int pd = 0, pl = 0, pm = 0, wd = 0, wl = 0, wm = 0;   // recent passes and their lanes, by kind
 
     for (;;) {
         if (!exhausted) {
-            const uint64_t need = __ballot(!p.active);
+            const uint64_t need = __ballot(!p.active && lane < a.lanes);
             if (need) {
                 const int leader = __ffsll((unsigned long long)need) - 1;
                 const int cnt = __popcll(need);
                 uint64_t base = 0;
                 if (lane == leader) base = atomicAdd(work, (unsigned long long)cnt);
                 base = shfl64(base, leader);
-                if (base + cnt >= a.count) exhausted = true;
-                if (!p.active) {
+                if (base + cnt >= a.count || a.one_round) exhausted = true;
+                if (!p.active && lane < a.lanes) {
                     const uint64_t q = base + __popcll(need & ((1ull << lane) - 1ull));
                     if (q < a.count) {
                         const uint64_t g = a.first + q;
@@ -459,6 +644,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
         }
         if (!__any(p.active)) break;
 
+        // Hand the wave's packets over where the cooperative walk spends fewer issue cycles on the
+        // recent passes' work than they did: ~1600 a frequency pass, 1500 a leak pass, 3000 an MC
+        // pass here; 48 a frequency step, 9000 an MC event and 20000 a leak there (where leaks are most of
+        // the steps the lanes keep the packets).
+        if (a.slots && exhausted &&
+            48 * wd + 20000 * wl + 9000 * wm < 1600 * pd + 1500 * pl + 3000 * pm) {
+            const uint64_t go = __ballot(p.active);
+            const int leader = __ffsll((unsigned long long)go) - 1;
+            uint64_t base = 0;
+            if (lane == leader) base = atomicAdd(&work[kWGiven], (unsigned long long)__popcll(go));
+            base = shfl64(base, leader) + __popcll(go & ((1ull << lane) - 1ull));
+            if (p.active && base < a.slots) {
+                Tail3 k;
+                k.cl = (uint32_t)p.cl;
+                k.pid = p.r.pid;
+                k.cell = (int32_t)p.cell;
+                k.j = p.j;
+                k.steps = p.steps;
+                k.words = word_pos(p.r);
+                k.t = p.t;
+                k.mcs = p.mcs;
+                k.tomc = p.tomc;
+                k.toddmc = p.toddmc;
+                k.refl = p.refl;
+                k.flags = (p.mc ? 1u : 0u) | (p.pend ? 2u : 0u);
+                k.pos[0] = p.pos.x;
+                k.pos[1] = p.pos.y;
+                k.pos[2] = p.pos.z;
+                k.n[0] = p.n.x;
+                k.n[1] = p.n.y;
+                k.n[2] = p.n.z;
+                k.x = p.x;
+                slots_of(work)[base] = k;
+                p.active = false;
+            }
+            if (!__any(p.active)) continue;   // (packets that found no slot walk on here)
+        }
+        pd >>= 1; pl >>= 1; pm >>= 1; wd >>= 1; wl >>= 1; wm >>= 1;
+
         // Event-batched passes: a pass advances the wave's DDMC lanes by up to two steps, or
         // applies the spatial leaks its DDMC steps chose, or advances its continuous-MC lanes
         // by one event, never two of these, so a wave does not issue the long leak or MC path
@@ -482,6 +706,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
             const int nm = __popcll(bm), nl = __popcll(bl), nd = __popcll(bd);
             const int mode = (nm > 0 && (8 * nm >= nd + nl || (k & 15) == 15)) ? 2
                              : (nl > 0 && (16 * nl >= nd || (k & 31) == 31 || nd == 0)) ? 1 : 0;
+            pd += mode == 0 ? 1 : 0; pl += mode == 1 ? 1 : 0; pm += mode == 2 ? 1 : 0;
+            wd += mode == 0 ? 2 * nd : 0; wl += mode == 1 ? nl : 0; wm += mode == 2 ? nm : 0;
             if (p.active && (mode == 2 ? p.mc : (mode == 1 ? p.pend : !p.mc && !p.pend))) {
                 prefetch(p.r, a);
                 if (mode == 2) {
@@ -504,15 +730,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
 
 __global__ void reset_queue(unsigned long long *work)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) work[0] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x < 32) work[threadIdx.x] = 0ull;
 }
 
 }  // namespace
 
 hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddmc_run &run, uint64_t first,
-                         uint64_t count, unsigned long long *d_tally, unsigned long long *d_work, hipStream_t s)
+                         uint64_t count, unsigned long long *d_tally, unsigned long long *d_work, uint64_t work_bytes,
+                         hipStream_t s)
 {
-    Walk3Args a;
+    Walk3Args a{};
     a.first = first;
     a.count = count;
     a.max_steps = run.max_steps;
@@ -523,17 +750,30 @@ hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddm
     a.dom = kDom3D;
     const int block = run.block > 0 ? run.block : 256;
     uint64_t grid = run.grid > 0 ? (uint64_t)run.grid : 0;
+    // Jobs of less than a wave per SIMD spread over the device, fewer lanes to a wave: the lanes do
+    // not wait longer, and the cooperative walk finds the packets where it has issue slots.
+    a.slots = run.tail_lanes >= 0 && work_bytes > 256 ? (work_bytes - 256) / sizeof(Tail3) : 0;
+    a.lanes = 64;
+    if (grid == 0 && a.slots) {
+        const uint64_t waves = 4ull * (uint64_t)device_cu_count();
+        const uint64_t per = (count + waves - 1) / waves;
+        a.lanes = per < 64 ? (int)per : 64;
+    }
     if (grid == 0) {
-        const uint64_t want = (count + block - 1) / block;
+        const uint64_t want = (count + (uint64_t)a.lanes * (block / 64) - 1) / ((uint64_t)a.lanes * (block / 64));
         const uint64_t cap = (uint64_t)device_cu_count() * 8;
         grid = want < cap ? want : cap;
         if (grid < 1) grid = 1;
     }
+    a.one_round = grid * (uint64_t)(block / 64) * (uint64_t)a.lanes >= count ? 1 : 0;
     reset_queue<<<1, 64, 0, s>>>(d_work);
     if (h.n_clouds == 1)
         walk3d<true><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
     else
         walk3d<false><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
+    if (a.slots)
+        walk3d_coop<<<(unsigned)std::min<uint64_t>((count + 3) / 4, 4ull * (uint64_t)device_cu_count()), 256, 0, s>>>(
+            d_tables, a, d_tally, d_work);
     return hipGetLastError();
 }
 

@@ -13,6 +13,11 @@ __device__ __forceinline__ uint32_t rl(uint32_t v, int lane)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
+__device__ __forceinline__ uint64_t rl64(uint64_t v, int lane)
+{
+    return ((uint64_t)rl((uint32_t)(v >> 32), lane) << 32) | rl((uint32_t)v, lane);
+}
+
 // v with `s` (wave-uniform) in lane `lane`: the compiler has no builtin for v_writelane_b32, and
 // only the intrinsic lets it place the wait states after the instruction that wrote `s`
 extern "C" __device__ int amdgcn_writelane_i32(int s, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
