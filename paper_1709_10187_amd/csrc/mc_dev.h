@@ -88,6 +88,45 @@ __device__ __forceinline__ uint32_t draw(Rng &r, const McArgs &a)
     return v;
 }
 
+// The words ahead without a branch per draw: `ready` makes idx 0 .. 3 with the block after the
+// current one generated, so that the next five words are at hand; `peek` moves the next N of them
+// into w by two conditional shifts, and `advance` consumes n <= 5 of them.
+__device__ __forceinline__ void roll(Rng &r, bool on)
+{
+    r.c0 = on ? r.n0 : r.c0;
+    r.c1 = on ? r.n1 : r.c1;
+    r.c2 = on ? r.n2 : r.c2;
+    r.c3 = on ? r.n3 : r.c3;
+    r.ahead = r.ahead && !on;
+}
+__device__ __forceinline__ void ready(Rng &r, const McArgs &a)
+{
+    if (r.idx == 4u) {
+        prefetch(r, a);
+        roll(r, true);
+        r.idx = 0u;
+    }
+    prefetch(r, a);
+}
+template <int N>
+__device__ __forceinline__ void peek(const Rng &r, uint32_t *w)
+{
+    const uint32_t v[8] = {r.c0, r.c1, r.c2, r.c3, r.n0, r.n1, r.n2, r.n3};
+    const bool two = (r.idx & 2u) != 0u, one = (r.idx & 1u) != 0u;
+    uint32_t y[N + 1];
+#pragma unroll
+    for (int i = 0; i <= N; ++i) y[i] = two ? v[i + 2] : v[i];
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = one ? y[i + 1] : y[i];
+}
+__device__ __forceinline__ void advance(Rng &r, uint32_t n)
+{
+    r.idx += n;
+    const bool over = r.idx > 4u;
+    roll(r, over);
+    r.idx -= over ? 4u : 0u;
+}
+
 // Words of the stream consumed so far, and the stream positioned there.
 __device__ __forceinline__ uint64_t word_pos(const Rng &r)
 {

@@ -175,21 +175,17 @@ __device__ __forceinline__ void enter(Pk &p, int nix, int niy, int niz, int64_t 
     p.cell = ncell;
 }
 
-// The draw and event of one DDMC step of a packet in a thick state: the path length, then a
-// frequency leak (eq. 11) is applied at once; a spatial leak is only marked (pend) and applied
-// by ddmc_leak, with the next random words of the packet's stream, before its next step.
-__device__ void ddmc_event(Pk &p, const DevCloud &c, const uint8_t *__restrict__ tb, const Walk3Args &a)
+// The event a DDMC step's event word chooses: a frequency leak (eq. 11) is applied at once; a
+// spatial leak is only marked (pend) and applied by ddmc_leak, with the next random words of the
+// packet's stream, before its next step.
+__device__ void ddmc_decide(Pk &p, const DevCloud &c, const uint8_t *__restrict__ tb, const Walk3Args &a, uint4 rec,
+                            uint32_t ew)
 {
-    const int nb = c.nb;
-    const int64_t s = p.cell * nb + p.j;
-    const uint4 rec = reinterpret_cast<const uint4 *>(tb + c.off_hot)[s];
-    const uint32_t tw = draw(p.r, a), ew = draw(p.r, a);
-    p.t += (double)ddmc_path(tw, __uint_as_float(rec.x));
     int ev;
     if (ew != rec.y && ew != rec.z) {
         ev = ew < rec.y ? 0 : (ew < rec.z ? 1 : 2);
     } else {   // the high words tie: compare the full u64
-        const uint4 lw = reinterpret_cast<const uint4 *>(tb + c.off_lo_words)[s];
+        const uint4 lw = reinterpret_cast<const uint4 *>(tb + c.off_lo_words)[p.cell * c.nb + p.j];
         const uint64_t U = ((uint64_t)ew << 32) | draw(p.r, a);
         const uint64_t D = ((uint64_t)rec.y << 32) | lw.x;
         const uint64_t S = ((uint64_t)rec.z << 32) | lw.y;
@@ -209,6 +205,48 @@ __device__ void ddmc_event(Pk &p, const DevCloud &c, const uint8_t *__restrict__
     p.pend = true;
 }
 
+// One DDMC step of a packet in a thick state: the path length, then the event.
+__device__ void ddmc_event(Pk &p, const DevCloud &c, const uint8_t *__restrict__ tb, const Walk3Args &a)
+{
+    const uint4 rec = reinterpret_cast<const uint4 *>(tb + c.off_hot)[p.cell * c.nb + p.j];
+    const uint32_t tw = draw(p.r, a), ew = draw(p.r, a);
+    p.t += (double)ddmc_path(tw, __uint_as_float(rec.x));
+    ddmc_decide(p, c, tb, a, rec, ew);
+}
+
+// Up to two DDMC steps of a packet in a thick state: ddmc_event twice, with the four words of both
+// taken ahead and frequency moves inside the thick bins as selects.  The rest (a tie, a leak into a
+// thin bin: one step in thousands) is left to a branch behind the two steps.
+__device__ __forceinline__ void ddmc_pair(Pk &p, const DevCloud &c, const uint8_t *__restrict__ tb, const Walk3Args &a)
+{
+    const uint4 *row = reinterpret_cast<const uint4 *>(tb + c.off_hot) + p.cell * c.nb;
+    uint4 rec = row[p.j];
+    ready(p.r, a);
+    uint32_t w[4];
+    peek<4>(p.r, w);
+    uint32_t used = 0u;
+    bool rare = false;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const bool on = h == 0 || (!rare && !p.pend && p.steps < a.max_steps);
+        if (h == 1) rec = row[on ? p.j : 0];
+        const uint32_t ew = w[2 * h + 1];
+        const double t = p.t + (double)ddmc_path(w[2 * h], __uint_as_float(rec.x));
+        p.t = on ? t : p.t;
+        p.steps += on ? 1ull : 0ull;
+        used += on ? 2u : 0u;
+        const bool dn = ew < rec.y, freq = ew < rec.z;
+        const bool special = ew == rec.y || ew == rec.z || (freq && (rec.w & (dn ? kFlagDnThin : kFlagUpThin)) != 0u);
+        p.j += on && freq && !special ? (dn ? -1 : 1) : 0;
+        p.pend = on && !freq && !special ? true : p.pend;
+        rare = on ? special : rare;
+        if (h == 0) w[0] = ew;   // the word of a rare event: the last step taken
+        else w[0] = on ? ew : w[0];
+    }
+    advance(p.r, used);
+    if (rare) ddmc_decide(p, c, tb, a, row[p.j], w[0]);
+}
+
 // The spatial leak a DDMC step chose (p.pend): the face from the state's cumulative split, then
 // the move into the neighbour (Doppler re-binning of eq. 20), a conversion to continuous MC
 // through an interface face, or an escape.
@@ -219,11 +257,16 @@ __device__ void ddmc_leak(Pk &p, const DevCloud &c, const uint8_t *__restrict__ 
     const int nb = c.nb;
     const int64_t s = p.cell * nb + p.j;
     const uint4 rec = reinterpret_cast<const uint4 *>(tb + c.off_hot)[s];
-    const uint32_t v = draw(p.r, a) >> 1;
     const uint32_t *fs = reinterpret_cast<const uint32_t *>(tb + c.off_face_split) + s * 5;
-    int f = 0;
-    while (f < 5 && v >= fs[f]) ++f;
-    const float xin = bin_x(c, tb, p.j, uf(draw(p.r, a)));
+    uint32_t w[2];
+    ready(p.r, a);
+    peek<2>(p.r, w);
+    advance(p.r, 2u);
+    const uint32_t v = w[0] >> 1;
+    int f = 0;   // the split is cumulative: the first face with v below it
+#pragma unroll
+    for (int i = 0; i < 5; ++i) f += v >= fs[i] ? 1 : 0;
+    const float xin = bin_x(c, tb, p.j, uf(w[1]));
     int nix = 0, niy = 0, niz = 0;
     int64_t ncell = 0;
     const bool inside = neighbour(p, c, f, nix, niy, niz, ncell);
@@ -687,14 +730,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
         // applies the spatial leaks its DDMC steps chose, or advances its continuous-MC lanes
         // by one event, never two of these, so a wave does not issue the long leak or MC path
         // for one lane.  A lane whose step chose a spatial leak waits for a leak pass (taken
-        // once such lanes are a sixteenth of the stepping ones, or every 32nd pass); MC
-        // lanes wait until they are at least an eighth as many as the DDMC lanes, or every
-        // sixteenth pass.  (Thresholds measured on the 128^3 cube: leak passes at an eighth
-        // 1 926 ms, a quarter 1 902, a sixteenth 1 867, a 32nd 1 865; MC passes at an eighth
-        // with leak passes at a sixteenth 1 852.)  Each pass starts by generating every taking part lane's next random
-        // block together (two frequency steps read one block).  Every packet still takes its
-        // own steps in its own order from its own stream, so the results do not depend on
-        // this schedule.
+        // once such lanes are a sixteenth of the stepping ones, or every 32nd pass); MC lanes wait
+        // until they are at least a sixth as many as the DDMC lanes, or every sixteenth pass.
+        // (Thresholds on the 128^3 cube, 2^22 packets: MC passes at a sixth 443 ms, an eighth 449,
+        // a twelfth 471; leak passes at a sixteenth 449, a tenth 453, a 24th 452.)  A frequency
+        // pass takes both steps' words ahead and does the common moves as selects: bound by vector
+        // issue, ~75 instructions per step of which Philox is 25 (487 ms with a branch and a word
+        // select per draw; four steps per pass 573: more lanes idle and more registers spilled).
+        // Every packet still takes its own steps in its own order from its own stream, so the
+        // results do not depend on this schedule.
         const DevCloud &c = clouds[SINGLE ? 0 : p.cl];
         const float lambda = (float)c.lambda;
         for (int k = 0; k < a.chunk; ++k) {
@@ -704,24 +748,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
             const uint64_t bd = __ballot(p.active && !p.mc && !p.pend);
             if (!(bm | bd | bl)) break;
             const int nm = __popcll(bm), nl = __popcll(bl), nd = __popcll(bd);
-            const int mode = (nm > 0 && (8 * nm >= nd + nl || (k & 15) == 15)) ? 2
+            const int mode = (nm > 0 && (6 * nm >= nd + nl || (k & 15) == 15)) ? 2
                              : (nl > 0 && (16 * nl >= nd || (k & 31) == 31 || nd == 0)) ? 1 : 0;
             pd += mode == 0 ? 1 : 0; pl += mode == 1 ? 1 : 0; pm += mode == 2 ? 1 : 0;
             wd += mode == 0 ? 2 * nd : 0; wl += mode == 1 ? nl : 0; wm += mode == 2 ? nm : 0;
             if (p.active && (mode == 2 ? p.mc : (mode == 1 ? p.pend : !p.mc && !p.pend))) {
-                prefetch(p.r, a);
                 if (mode == 2) {
+                    prefetch(p.r, a);
                     ++p.steps;
                     mc_step(p, c, tb, a, tally, vtab, u0tab, lambda);
                 } else if (mode == 1) {
                     ddmc_leak(p, c, tb, a, tally);
                 } else {
-                    ++p.steps;
-                    ddmc_event(p, c, tb, a);
-                    if (!p.mc && !p.pend && p.steps < a.max_steps) {
-                        ++p.steps;
-                        ddmc_event(p, c, tb, a);
-                    }
+                    ddmc_pair(p, c, tb, a);
                 }
             }
         }
