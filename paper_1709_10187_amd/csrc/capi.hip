@@ -337,6 +337,10 @@ rddmc_status make_layout(const rddmc_batch *b, Layout &L)
         c.off_census = c.n_census > 0 ? take(8ull * (c.n_census + 1)) : 0;
         c.groups = (m.flags & RDDMC_FLAG_GROUPS) ? 1 : 0;
         c.dust_weight = (m.flags & RDDMC_FLAG_DUST_WEIGHT) ? 1 : 0;
+        if (hybrid1d)
+            for (int i = 0; i < c.nc && !c.any_thick; ++i)
+                c.any_thick = (m.k0[i] + (m.dust_sca ? m.dust_sca[i] : 0.0)) * (m.faces[0][i + 1] - m.faces[0][i]) >=
+                              m.tau_threshold * (1.0 - 1e-6) ? 1 : 0;
         if (c.dust_weight) L.h.dust_weight1d = 1u;
         if (m.n_census > 0) L.h.census1d = 1u;
         c.off_grp_prob = c.groups ? take(8ull * c.nb * c.nb) : 0;
@@ -579,16 +583,12 @@ rddmc_status rddmc_transport(const rddmc_batch *batch, const void *d_tables, con
     if (L.h.hybrid1d) {
         if (run->surrogate)
             return fail(RDDMC_EUNSUPPORTED, "the escape surrogate runs with pure-DDMC 1D batches only");
-        // no state is thick where the threshold is above every cell's line-centre width (H <= 1)
-        bool any_thick = false;
-        for (int ci = 0; ci < L.h.n_clouds && !any_thick; ++ci) {
-            const rddmc_medium &m = batch->clouds[ci];
-            for (int i = 0; i < m.n_cells[0] && !any_thick; ++i) {
-                const double ks = m.dust_sca ? m.dust_sca[i] : 0.0;
-                any_thick = (m.k0[i] + ks) * (m.faces[0][i + 1] - m.faces[0][i]) >= m.tau_threshold;
-            }
+        bool any_thick = false, all_groups = true;
+        for (const DevCloud &c : L.clouds) {
+            any_thick |= c.any_thick != 0;
+            all_groups &= c.groups != 0;
         }
-        hipError_t e = launch_walk1dh(static_cast<const uint8_t *>(d_tables), L.h, any_thick, *run, run->first, count,
+        hipError_t e = launch_walk1dh(static_cast<const uint8_t *>(d_tables), L.h, any_thick, all_groups, *run, run->first, count,
                                       static_cast<unsigned long long *>(d_tally),
                                       static_cast<unsigned long long *>(d_work), work_bytes,
                                       reinterpret_cast<hipStream_t>(stream));

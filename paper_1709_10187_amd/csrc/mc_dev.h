@@ -275,14 +275,21 @@ __device__ inline bool sample_upar(float a, float x, const float *__restrict__ u
     return false;
 }
 
-__device__ __forceinline__ float3 iso_dir(Rng &r, const McArgs &a)
+// isotropic direction from two words
+__device__ __forceinline__ float3 direction(uint32_t w0, uint32_t w1)
 {
-    const float mu = fmaf(2.0f, uf(draw(r, a)), -1.0f);
-    const float ph = kTwoPi * uf(draw(r, a));
+    const float mu = fmaf(2.0f, uf(w0), -1.0f);
+    const float ph = kTwoPi * uf(w1);
     const float s = sqrtf(fmaxf(0.0f, 1.0f - mu * mu));
     float sn, cs;
     sincosf(ph, &sn, &cs);
     return make_float3(s * cs, s * sn, mu);
+}
+
+__device__ __forceinline__ float3 iso_dir(Rng &r, const McArgs &a)
+{
+    const uint32_t w0 = draw(r, a), w1 = draw(r, a);
+    return direction(w0, w1);
 }
 
 }  // namespace mc

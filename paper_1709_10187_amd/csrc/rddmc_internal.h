@@ -108,6 +108,9 @@ struct alignas(16) DevCloud {
     uint64_t off_grp_alias;      //   u32x2 [nb * nb] Walker alias table per row {threshold, alias}
     int32_t groups;              // thin states carry a frequency group (Sec. 5.3)
     int32_t dust_weight;         // dust absorption by continuous weights (Sec. 2.4)
+    int32_t any_thick;           // 1D hybrid: a state can be thick (the threshold is not above every cell's
+                                 //   line-centre width; H(a, x) <= 1)
+    int32_t pad1;
     uint64_t wspec_off;          // (dust_weight) int64 word offset in the cloud's tally block:
                                  //   sum w t (128-bit, 2^-32 units), sum w t^2 (128-bit, 2^-20
                                  //   units), then the weighted and squared-weight spectra
@@ -165,7 +168,7 @@ hipError_t launch_build_line_tables(const DevHeader &h, uint8_t *d_tables, hipSt
 hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddmc_run &run, uint64_t first,
                          uint64_t count, unsigned long long *d_tally, unsigned long long *d_work, uint64_t work_bytes,
                          hipStream_t s);
-hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_thick, const rddmc_run &run,
+hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_thick, bool all_groups, const rddmc_run &run,
                           uint64_t first, uint64_t count, unsigned long long *d_tally, unsigned long long *d_work,
                           uint64_t work_bytes, hipStream_t s);
 hipError_t launch_philox_fill(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t c2,

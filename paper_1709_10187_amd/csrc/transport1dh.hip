@@ -139,19 +139,16 @@ __device__ __forceinline__ float3 cell_point(const double *fz, int cell, Rng &r,
     return make_float3(rr * w.x, rr * w.y, rr * w.z);
 }
 
-// distance along n to the boundary of cell `cell` from p, and the face it reaches.  A flight
+// distance along n from p to the boundary of a cell with faces lo and hi, and the face it reaches.  A flight
 // that starts on the inner sphere moving outward cannot meet that sphere again (a line leaves a
 // ball once); `left_inner` says so, where the sign of p . n cannot for a grazing flight.
 template <bool SPH>
-__device__ __forceinline__ float wall_distance(const double *fz, int cell, float3 p, float3 n, bool left_inner,
-                                               int &face)
+__device__ __forceinline__ float wall_distance(double lo, double hi, float3 p, float3 n, bool left_inner, int &face)
 {
-    const double lo = fz[cell], hi = fz[cell + 1];
-    if (!SPH) {
-        if (n.z > 0.0f) { face = 1; return fmaxf(0.0f, (float)((hi - (double)p.z) / (double)n.z)); }
-        if (n.z < 0.0f) { face = 0; return fmaxf(0.0f, (float)((lo - (double)p.z) / (double)n.z)); }
-        face = 1;
-        return INFINITY;
+    if (!SPH) {   // one division for either direction
+        face = n.z < 0.0f ? 0 : 1;
+        const float d = fmaxf(0.0f, (float)(((face ? hi : lo) - (double)p.z) / (double)n.z));
+        return n.z == 0.0f ? INFINITY : d;
     }
     const double px = p.x, py = p.y, pz = p.z;
     const double b = px * n.x + py * n.y + pz * n.z;
@@ -488,7 +485,7 @@ __device__ __forceinline__ void mc_step1(Pk1 &p, const DevCloud &c, const uint8_
     const float4 m1c = mcell[2 * p.cell + 1];   // u, and with dust k_s, k_a
     const float uc = m1c.x;
     int fexit = 1;
-    const float dwall = wall_distance<SPH>(fz, p.cell, p.pos, p.n, p.left_inner, fexit);
+    const float dwall = wall_distance<SPH>(fz[p.cell], fz[p.cell + 1], p.pos, p.n, p.left_inner, fexit);
     const float kl = m0.x * voigt_f32(m0.y, p.x, vtab);
     // dust absorption is an interaction, or (continuous weights) a decay of the weight
     const float kab = (WGT && c.dust_weight) ? 0.0f : m1c.z;
@@ -601,6 +598,9 @@ __device__ __forceinline__ void mc_step1(Pk1 &p, const DevCloud &c, const uint8_
 // (eq. 14) plus any dust; a scattering takes the outgoing bin from row j of the cloud's alias
 // table of eq. 42 (two 32-bit words) and an isotropic direction.  Boundaries as in mc_step1,
 // with the bin unchanged across faces (no velocities, one temperature).
+// Bound by one wave's serial issue (about 8 cycles an instruction) and three dependent gathers: the
+// opacity, the faces and, from its word of the stream, the alias entry are fetched before the next
+// random block is generated, and the flags of the state entered only in clouds with thick states.
 template <bool SPH, bool WGT, bool CEN>
 __device__ __forceinline__ void grp_step1(Pk1 &p, const DevCloud &c, const uint8_t *__restrict__ tb, const McArgs &a,
                           unsigned long long *__restrict__ tally)
@@ -609,9 +609,17 @@ __device__ __forceinline__ void grp_step1(Pk1 &p, const DevCloud &c, const uint8
     const double *fz = faces_of(c, tb, 0);
     const double *kt = reinterpret_cast<const double *>(tb + c.off_k);
     const int64_t s = (int64_t)p.cell * c.nb + p.j;
+    const double k64 = kt[s], lo = fz[p.cell], hi = fz[p.cell + 1];
+    ready(p.r, a);
+    uint32_t w[5];
+    peek<5>(p.r, w);
+    // words: flight, with dust the interaction, outgoing bin (two), direction (two)
+    const uint32_t w1 = c.dusty ? w[2] : w[1], w2 = c.dusty ? w[3] : w[2];
+    const int col = (int)(((uint64_t)w1 * (uint32_t)c.nb) >> 32);
+    const uint2 ent = reinterpret_cast<const uint2 *>(tb + c.off_grp_alias)[(int64_t)p.j * c.nb + col];
     int fexit = 1;
-    const float dwall = wall_distance<SPH>(fz, p.cell, p.pos, p.n, p.left_inner, fexit);
-    const float kl = (float)kt[s];
+    const float dwall = wall_distance<SPH>(lo, hi, p.pos, p.n, p.left_inner, fexit);
+    const float kl = (float)k64;
     float ka = 0.0f, ks = 0.0f, kd = 0.0f;   // kd: dust absorption rate (either method)
     if (c.dusty) {
         const float4 m1c = reinterpret_cast<const float4 *>(tb + c.off_mcell)[2 * p.cell + 1];
@@ -620,7 +628,7 @@ __device__ __forceinline__ void grp_step1(Pk1 &p, const DevCloud &c, const uint8
         ka = (WGT && c.dust_weight) ? 0.0f : kd;
     }
     const float kx = kl + ks + ka;
-    const float ds = -__logf(uf(draw(p.r, a))) / kx;
+    const float ds = -__logf(uf(w[0])) / kx;
     const double fl = (double)fminf(ds, dwall);
     if (CEN && c.n_census > 0) census_add<WGT>(p, c, tb, tally, s, p.t, p.t + fl, p.lw, (double)kd);
     if (WGT && c.dust_weight) {
@@ -637,34 +645,40 @@ __device__ __forceinline__ void grp_step1(Pk1 &p, const DevCloud &c, const uint8
         p.t += (double)ds;
         p.left_inner = false;
         if (c.dusty) {
-            const float v = uf(draw(p.r, a)) * kx;
+            const float v = uf(w[1]) * kx;
             if (v < ka) {
                 finish1<WGT, CEN>(p, c, tally, false, 0, 0, true);
                 return;
             }
             if (v < ka + ks) {   // dust: isotropic, the bin unchanged
-                p.n = iso_dir(p.r, a);
+                p.n = direction(w[2], w[3]);
+                advance(p.r, 4u);
                 return;
             }
         }
         // eq. 42: the outgoing bin from the row's alias table
-        const uint32_t w1 = draw(p.r, a), w2 = draw(p.r, a);
-        const int col = (int)(((uint64_t)w1 * (uint32_t)c.nb) >> 32);
-        const uint2 ent = reinterpret_cast<const uint2 *>(tb + c.off_grp_alias)[(int64_t)p.j * c.nb + col];
         const int jj = w2 < ent.x ? col : (int)ent.y;
-        p.n = iso_dir(p.r, a);
+        if (c.dusty) {
+            advance(p.r, 4u);
+            p.n = iso_dir(p.r, a);
+        } else {
+            p.n = direction(w[3], w[4]);
+            advance(p.r, 5u);
+        }
         p.j = jj;
-        if (reinterpret_cast<const uint4 *>(tb + c.off_hot)[(int64_t)p.cell * c.nb + jj].w & kFlagThick) {
+        if (c.any_thick &&
+            (reinterpret_cast<const uint4 *>(tb + c.off_hot)[(int64_t)p.cell * c.nb + jj].w & kFlagThick)) {
             p.mc = false;
             ++p.toddmc;
         }
         return;
     }
+    advance(p.r, 1u);
     // boundary crossing: put the point exactly on its plane or sphere
     p.pos.x = fmaf(dwall, p.n.x, p.pos.x);
     p.pos.y = fmaf(dwall, p.n.y, p.pos.y);
     p.pos.z = fmaf(dwall, p.n.z, p.pos.z);
-    const float rf = (float)fz[p.cell + fexit];
+    const float rf = (float)(fexit ? hi : lo);
     if (SPH) {
         const float3 e = radial(p.pos);
         p.pos = make_float3(rf * e.x, rf * e.y, rf * e.z);
@@ -677,7 +691,8 @@ __device__ __forceinline__ void grp_step1(Pk1 &p, const DevCloud &c, const uint8
         finish1<WGT, CEN>(p, c, tally, true, SPH ? 0 : fexit, p.j + 1);
         return;
     }
-    if (reinterpret_cast<const uint4 *>(tb + c.off_hot)[(int64_t)nbc * c.nb + p.j].w & kFlagThick) {
+    if (c.any_thick &&
+        (reinterpret_cast<const uint4 *>(tb + c.off_hot)[(int64_t)nbc * c.nb + p.j].w & kFlagThick)) {
         const float4 m1 = reinterpret_cast<const float4 *>(tb + c.off_mcell)[2 * nbc];
         const float kn = (float)kt[(int64_t)nbc * c.nb + p.j];
         const float mu = fabsf(dot3f(p.n, face_normal<SPH>(fexit, p.pos)));
@@ -1149,9 +1164,11 @@ __global__ __launch_bounds__(256) void walk1dh_coop(const uint8_t *__restrict__ 
 }
 
 // Lanes whose packets the cooperative walk should take now (0: none).  A side-by-side step costs
-// ~1000 issue cycles whatever the lanes, a cooperative one ~48, and a continuous-MC event ~4000
-// either way: with a share f of MC events the hand-over pays below (1000 + 4000 f) / (48 + 4000 f)
-// lanes, and never for packets that are mostly in MC states.
+// ~2000 cycles whatever the lanes (a wave or two per SIMD are left by then), a cooperative one
+// ~50-70, and a continuous-MC event ~4000 either way: with a share f of MC events the hand-over pays
+// below (2000 + 4000 f) / (60 + 4000 f) lanes, and never for packets that are mostly in MC states.
+// (At 1000 / 48 the dusty census slab, 16 packets to a wave, took 407 ms: most waves stayed just
+// above the limit.)
 __device__ __forceinline__ uint64_t hand_over(const Pk1 &p)
 {
     const bool fit = p.active && p.steps >= 64ull && 32ull * p.mcs < p.steps;
@@ -1163,7 +1180,216 @@ __device__ __forceinline__ uint64_t hand_over(const Pk1 &p)
         mc += __shfl_xor(mc, o);
     }
     const float f = 4000.0f * mc;
-    return (float)__popcll(m) * (48.0f * st + f) < 1000.0f * st + f ? m : 0ull;
+    return (float)__popcll(m) * (60.0f * st + f) < 2000.0f * st + f ? m : 0ull;
+}
+
+// Packet g of the batch's flattened packet space at its source.
+template <bool SINGLE>
+__device__ __forceinline__ void emit1(Pk1 &p, uint64_t g, const uint8_t *__restrict__ tb,
+                                      const DevCloud *__restrict__ clouds, const uint64_t *__restrict__ prefix,
+                                      const McArgs &a, unsigned long long *__restrict__ tally)
+{
+    int cl = 0;
+    if (!SINGLE) {
+        int lo = 0, hi = a.n_clouds;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (g >= prefix[mid]) lo = mid; else hi = mid;
+        }
+        cl = lo;
+    }
+    const DevCloud &c = clouds[cl];
+    p.cl = cl;
+    p.r = Rng{0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 4u, false, 0u, 0u, (uint32_t)(g - prefix[cl]),
+              c.stream};
+    // emission (Sec. 2.3): a source entry drawn by its probability
+    const double u = ud(draw(p.r, a));
+    const double *cdf = reinterpret_cast<const double *>(tb + c.off_src_cdf);
+    int lo = 0, hi = c.n_src - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (u < cdf[mid]) hi = mid; else lo = mid + 1;
+    }
+    const int64_t st = reinterpret_cast<const int32_t *>(tb + c.off_src_state)[lo];
+    p.cell = (int)(st / c.nb);
+    p.j = (int)(st - (int64_t)p.cell * c.nb);
+    p.t = 0.0;
+    p.lw = 0.0;
+    p.ci = 0;
+    p.tn = -__builtin_inf();
+    if (c.off_src_t) {   // emission uniform over the source's window
+        const double *tw = reinterpret_cast<const double *>(tb + c.off_src_t) + 2 * lo;
+        p.t = tw[0] + (tw[1] - tw[0]) * ud(draw(p.r, a));
+    }
+    p.steps = 0;
+    p.mcs = p.tomc = p.toddmc = p.refl = 0u;
+    p.active = true;
+    const uint4 rec = reinterpret_cast<const uint4 *>(tb + c.off_hot)[st];
+    p.mc = !(rec.w & kFlagThick);
+    if (p.mc) {   // a thin source state starts as an MC packet at the source
+        const float4 sp = reinterpret_cast<const float4 *>(tb + c.off_src_pos)[lo];
+        p.pos = make_float3(0.f, 0.f, sp.z);
+        p.x = sp.w;
+        p.n = iso_dir(p.r, a);
+        p.left_inner = false;
+    }
+    atomicAdd(&tally[c.tally_off + TW_LAUNCHED], 1ull);
+}
+
+// Pure frequency-group Monte Carlo: batches whose clouds all carry groups and have no thick state
+// (and neither census nor weights).  The events are grp_step1's, with nothing else in the loop, and
+// what the next event will gather is fetched as soon as it is known: the opacity with the outgoing
+// bin, the alias entry once the next words are there, the faces when the cell changes; the new
+// direction is computed while they are on their way.  A lone lane's event took 1.7 us with the
+// gathers one after another between the draws, 0.8 us here (tau0 = 3e3 slab, 64 x 128), about 250
+// vector instructions that one wave issues one every 4 to 8 cycles.
+template <bool SPH, bool SINGLE>
+__global__ __launch_bounds__(256) void walk1dg(const uint8_t *__restrict__ tb, McArgs a,
+                                               unsigned long long *__restrict__ tally,
+                                               unsigned long long *__restrict__ work)
+{
+    const DevHeader *H = reinterpret_cast<const DevHeader *>(tb);
+    const DevCloud *clouds = reinterpret_cast<const DevCloud *>(tb + H->off_clouds);
+    const uint64_t *prefix = reinterpret_cast<const uint64_t *>(tb + H->off_prefix);
+    const int lane = threadIdx.x & 63;
+    Pk1 p;
+    p.active = false;
+    p.mc = true;
+    p.left_inner = false;
+    p.cl = p.cell = p.j = 0;
+    p.pos = make_float3(0.f, 0.f, 0.f);
+    p.n = make_float3(0.f, 0.f, 1.f);
+    p.t = 0.0;
+    p.steps = 0;
+    p.mcs = p.tomc = p.toddmc = p.refl = 0u;
+    p.r = Rng{0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 4u, false, 0u, 0u, 0u, 0u};
+    double lo = 0.0, hi = 1.0, k64 = 1.0;
+    uint2 ent = make_uint2(0u, 0u);
+    uint32_t w0 = 0u, w1 = 0u, w2 = 0u, w3 = 0u, w4 = 0u;   // the next five words
+    auto take = [&]() {
+        uint32_t w[5];
+        ready(p.r, a);
+        peek<5>(p.r, w);
+        w0 = w[0];
+        w1 = w[1];
+        w2 = w[2];
+        w3 = w[3];
+        w4 = w[4];
+    };
+    bool exhausted = false;
+    for (;;) {
+        if (!exhausted) {
+            const uint64_t need = __ballot(!p.active && lane < a.lanes);
+            if (need) {
+                const int leader = __ffsll((unsigned long long)need) - 1;
+                const int cnt = __popcll(need);
+                uint64_t base = 0;
+                if (lane == leader) base = atomicAdd(work, (unsigned long long)cnt);
+                base = shfl64(base, leader);
+                if (base + cnt >= a.count || a.one_round) exhausted = true;
+                const uint64_t q = base + __popcll(need & ((1ull << lane) - 1ull));
+                if (!p.active && lane < a.lanes && q < a.count) {
+                    emit1<SINGLE>(p, a.first + q, tb, clouds, prefix, a, tally);
+                    const DevCloud &c = clouds[SINGLE ? 0 : p.cl];
+                    const double *fz = faces_of(c, tb, 0);
+                    lo = fz[p.cell];
+                    hi = fz[p.cell + 1];
+                    k64 = reinterpret_cast<const double *>(tb + c.off_k)[(int64_t)p.cell * c.nb + p.j];
+                    take();
+                    const int col = (int)(((uint64_t)(c.dusty ? w2 : w1) * (uint32_t)c.nb) >> 32);
+                    ent = reinterpret_cast<const uint2 *>(tb + c.off_grp_alias)[(int64_t)p.j * c.nb + col];
+                }
+            }
+        }
+        if (!__any(p.active)) break;
+        const DevCloud &c = clouds[SINGLE ? 0 : p.cl];
+        const double *fz = faces_of(c, tb, 0);
+        const double *kt = reinterpret_cast<const double *>(tb + c.off_k);
+        const uint2 *alias = reinterpret_cast<const uint2 *>(tb + c.off_grp_alias);
+        const int nb = c.nb, nc = c.nc;
+        const bool dusty = c.dusty != 0;
+        for (int k = 0; k < a.chunk; ++k) {
+            if (p.active && p.steps >= a.max_steps) finish1<false, false>(p, c, tally, false, 0, 0);
+            if (!__any(p.active)) break;
+            if (p.active) {
+                ++p.steps;
+                ++p.mcs;
+                int fexit = 1;
+                const float dwall = wall_distance<SPH>(lo, hi, p.pos, p.n, p.left_inner, fexit);
+                float ka = 0.0f, ks = 0.0f;
+                if (dusty) {
+                    const float4 m1c = reinterpret_cast<const float4 *>(tb + c.off_mcell)[2 * p.cell + 1];
+                    ks = m1c.y;
+                    ka = m1c.z;
+                }
+                const float kx = (float)k64 + ks + ka;
+                const float ds = -__logf(uf(w0)) / kx;
+                const bool inter = ds < dwall;
+                const float dl = inter ? ds : dwall;
+                p.pos.x = fmaf(dl, p.n.x, p.pos.x);
+                p.pos.y = fmaf(dl, p.n.y, p.pos.y);
+                p.pos.z = fmaf(dl, p.n.z, p.pos.z);
+                p.t += (double)dl;
+                // words of a new direction (at 3, 4; at 2, 3 after a dust scattering; a dusty cloud's
+                // last one follows the five)
+                uint32_t d0 = w3, d1 = w4;
+                bool turn = inter;
+                uint32_t used = 1u;
+                if (inter) {
+                    p.left_inner = false;
+                    used = 5u;
+                    bool lya = true;
+                    if (dusty) {
+                        const float v = uf(w1) * kx;
+                        if (v < ka) {
+                            finish1<false, false>(p, c, tally, false, 0, 0, true);
+                            turn = lya = false;
+                        } else if (v < ka + ks) {   // dust: isotropic, the bin unchanged
+                            d0 = w2;
+                            d1 = w3;
+                            used = 4u;
+                            lya = false;
+                        } else {
+                            d0 = w4;
+                        }
+                    }
+                    if (lya) {   // eq. 42: the outgoing bin from the row's alias table
+                        const int col = (int)(((uint64_t)(dusty ? w2 : w1) * (uint32_t)nb) >> 32);
+                        p.j = (dusty ? w3 : w2) < ent.x ? col : (int)ent.y;
+                        k64 = kt[(int64_t)p.cell * nb + p.j];
+                        if (dusty) {
+                            advance(p.r, 5u);
+                            d1 = draw(p.r, a);
+                            used = 0u;
+                        }
+                    }
+                } else {   // boundary crossing: put the point exactly on its plane or sphere
+                    const float rf = (float)(fexit ? hi : lo);
+                    if (SPH) {
+                        const float3 e = radial(p.pos);
+                        p.pos = make_float3(rf * e.x, rf * e.y, rf * e.z);
+                    } else {
+                        p.pos.z = rf;
+                    }
+                    const int nbc = fexit ? p.cell + 1 : p.cell - 1;
+                    if (nbc < 0 || nbc >= nc) {
+                        finish1<false, false>(p, c, tally, true, SPH ? 0 : fexit, p.j + 1);
+                    } else {
+                        p.cell = nbc;
+                        p.left_inner = fexit == 1;
+                        lo = fz[nbc];
+                        hi = fz[nbc + 1];
+                        k64 = kt[(int64_t)nbc * nb + p.j];
+                    }
+                }
+                if (used) advance(p.r, used);
+                take();
+                const int col = (int)(((uint64_t)(dusty ? w2 : w1) * (uint32_t)nb) >> 32);
+                ent = alias[(int64_t)p.j * nb + col];
+                if (turn) p.n = direction(d0, d1);
+            }
+        }
+    }
 }
 
 template <bool SPH, bool SINGLE, bool WGT, bool CEN>
@@ -1212,52 +1438,7 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
                 if (!p.active && lane < a.lanes) {
                     const uint64_t q = base + __popcll(need & ((1ull << lane) - 1ull));
                     if (q < a.count) {
-                        const uint64_t g = a.first + q;
-                        int cl = 0;
-                        if (!SINGLE) {
-                            int lo = 0, hi = a.n_clouds;
-                            while (hi - lo > 1) {
-                                const int mid = (lo + hi) >> 1;
-                                if (g >= prefix[mid]) lo = mid; else hi = mid;
-                            }
-                            cl = lo;
-                        }
-                        const DevCloud &c = clouds[cl];
-                        p.cl = cl;
-                        p.r = Rng{0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 4u, false, 0u, 0u, (uint32_t)(g - prefix[cl]),
-                                  c.stream};
-                        // emission (Sec. 2.3): a source entry drawn by its probability
-                        const double u = ud(draw(p.r, a));
-                        const double *cdf = reinterpret_cast<const double *>(tb + c.off_src_cdf);
-                        int lo = 0, hi = c.n_src - 1;
-                        while (lo < hi) {
-                            const int mid = (lo + hi) >> 1;
-                            if (u < cdf[mid]) hi = mid; else lo = mid + 1;
-                        }
-                        const int64_t st = reinterpret_cast<const int32_t *>(tb + c.off_src_state)[lo];
-                        p.cell = (int)(st / c.nb);
-                        p.j = (int)(st - (int64_t)p.cell * c.nb);
-                        p.t = 0.0;
-                        p.lw = 0.0;
-                        p.ci = 0;
-                        p.tn = -__builtin_inf();
-                        if (c.off_src_t) {   // emission uniform over the source's window
-                            const double *tw = reinterpret_cast<const double *>(tb + c.off_src_t) + 2 * lo;
-                            p.t = tw[0] + (tw[1] - tw[0]) * ud(draw(p.r, a));
-                        }
-                        p.steps = 0;
-                        p.mcs = p.tomc = p.toddmc = p.refl = 0u;
-                        p.active = true;
-                        const uint4 rec = reinterpret_cast<const uint4 *>(tb + c.off_hot)[st];
-                        p.mc = !(rec.w & kFlagThick);
-                        if (p.mc) {   // a thin source state starts as an MC packet at the source
-                            const float4 sp = reinterpret_cast<const float4 *>(tb + c.off_src_pos)[lo];
-                            p.pos = make_float3(0.f, 0.f, sp.z);
-                            p.x = sp.w;
-                            p.n = iso_dir(p.r, a);
-                            p.left_inner = false;
-                        }
-                        atomicAdd(&tally[c.tally_off + TW_LAUNCHED], 1ull);
+                        emit1<SINGLE>(p, a.first + q, tb, clouds, prefix, a, tally);
                     }
                 }
             }
@@ -1313,14 +1494,16 @@ __global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, M
             const int nm = __popcll(bm), nd = __popcll(bd);
             const bool mc_pass = nm > 0 && (4 * nm >= nd || (k & 7) == 7);
             if (p.active && p.mc == mc_pass) {
-                prefetch(p.r, a);
                 ++p.steps;
                 if (mc_pass) {
-                    if (c.groups)
+                    if (c.groups) {
                         grp_step1<SPH, WGT, CEN>(p, c, tb, a, tally);
-                    else
+                    } else {
+                        prefetch(p.r, a);
                         mc_step1<SPH, WGT, CEN>(p, c, tb, a, tally, vtab, u0tab);
+                    }
                 } else {
+                    prefetch(p.r, a);
                     ddmc_step1<SPH, WGT, CEN>(p, c, tb, a, tally);
                     if (p.active && !p.mc && p.steps < a.max_steps) {
                         ++p.steps;
@@ -1339,7 +1522,7 @@ __global__ void reset_queue1(unsigned long long *work)
 
 }  // namespace
 
-hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_thick, const rddmc_run &run,
+hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_thick, bool all_groups, const rddmc_run &run,
                           uint64_t first, uint64_t count, unsigned long long *d_tally, unsigned long long *d_work,
                           uint64_t work_bytes, hipStream_t s)
 {
@@ -1376,6 +1559,17 @@ hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_
     reset_queue1<<<1, 64, 0, s>>>(d_work);
     const bool sph = h.geometry == RDDMC_SPHERE;
     const bool single = h.n_clouds == 1;
+    if (all_groups && !any_thick && !h.dust_weight1d && !h.census1d) {
+        if (sph && single)
+            walk1dg<true, true><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
+        else if (sph)
+            walk1dg<true, false><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
+        else if (single)
+            walk1dg<false, true><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
+        else
+            walk1dg<false, false><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
+        return hipGetLastError();
+    }
     // batches with continuous dust weights or census estimators take instantiations of their
     // own, so that the others keep the registers (and occupancy) of a walk without them
     auto go = [&](auto wgt, auto cen) {
