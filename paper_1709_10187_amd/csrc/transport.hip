@@ -36,11 +36,14 @@ struct WalkArgs {
     int32_t chunk;
     int32_t n_clouds;
     int32_t tail_lanes;    // export a wave's packets once the queue is empty and <= this many remain
+    int32_t ahead;         // few waves per SIMD: records are fetched ahead of the step that needs them
     int32_t one_round;     // the producers have a lane for every packet: the queue is empty after one refill
     uint64_t tail_capacity;
     const uint8_t *surr;   // learned escape surrogate (windows and records) or null
     uint32_t producer_blocks;   // blocks [0, producer_blocks) walk packets from the queue;
     uint32_t producer_waves;    // later blocks walk handed-over packets cooperatively
+    uint32_t consumer_waves;
+    int32_t share;              // consumer waves that may be busy before a wave's last packets leave
 };
 
 // Work area (u64 words, the polled ones on their own 128-byte lines): [0] packet queue
@@ -177,7 +180,7 @@ __device__ __forceinline__ bool in_window(const Packet1D &p, const SurrWin &w)
 // Philox pair slot (the step count is rounded up to even, then advanced by 2), drawn in
 // its own counter domain.
 template <bool MOVING>
-__device__ void mdn_exit(Packet1D &p, const SurrWin &sw, const float *__restrict__ recs,
+__device__ __forceinline__ void mdn_exit(Packet1D &p, const SurrWin &sw, const float *__restrict__ recs,
                          const uint8_t *__restrict__ tb, const DevCloud &c, const WalkArgs &a)
 {
     p.steps = (p.steps + 1ull) & ~1ull;
@@ -271,7 +274,7 @@ __device__ __forceinline__ void rebin(Packet1D &p, int face, float4 cm, uint32_t
 // surrogate's counter domain per exit: x for the CDF, y for the branch, z for the re-binning, w
 // for E.
 template <bool MOVING>
-__device__ void exact_exit(Packet1D &p, const SurrWin &sw, const uint8_t *__restrict__ tb, const DevCloud &c,
+__device__ __forceinline__ void exact_exit(Packet1D &p, const SurrWin &sw, const uint8_t *__restrict__ tb, const DevCloud &c,
                            const WalkArgs &a)
 {
     p.steps = (p.steps + 1ull) & ~1ull;
@@ -426,15 +429,30 @@ __device__ __forceinline__ bool select_step(Packet1D &p, bool en, uint32_t tw, u
     return slow;
 }
 
-// Pairs of static-medium steps with wave-uniform control flow: every lane evaluates both
-// steps of a pair with selects, lanes that are done or past their budget are disabled, and
-// the slow path and record reloads run under masks only when some lane needs them.  Same
-// records, random words and arithmetic as one_step, so the same bits.
-template <bool MOVING, bool SURR = false>
-__device__ __forceinline__ void static_pairs(Packet1D &p, int budget, int last_state,
-                                             const uint8_t *__restrict__ tb, const DevCloud *__restrict__ clouds,
-                                             const WalkArgs &a, unsigned long long *__restrict__ tally,
-                                             const SurrWin *sw = nullptr, const float *__restrict__ recs = nullptr)
+// Whether the surrogate exits of a pass are taken now: an exit is a search of dependent gathers that
+// the wave's other lanes wait for, so lanes due for one wait until they are a third of the live
+// ones (or every eighth pass, or nobody else steps).  Which pass takes a packet's exit does not
+// change its steps.  (Exit kernel, tau0 = 1e7 sphere, 2^18 packets: 273 ms with an exit pass
+// whenever a lane is due, 262 ms so.)
+__device__ __forceinline__ bool exits_due(bool sx, bool step, int k)
+{
+    const uint64_t x = __ballot(sx), o = __ballot(step);
+    return x != 0ull && (2 * __popcll(x) >= __popcll(o) || (k & 7) == 7);
+}
+
+// Pairs of static-medium steps: the lanes that step share one masked region per pair, in which the
+// common moves are selects; ties and escapes run under a mask of their own.  Where waves fill the
+// SIMDs, each step's record is gathered when its state is known, one gather a step: the rate of
+// gathers binds before their latency does (2^20 packets of the efficient-grid tau0 = 1e7 sphere:
+// 154 ms with three gathers ahead and a fourth after a spatial move, 109 ms so, with the tail thresholds below).  With AHEAD, for
+// grids of a few waves per SIMD, the neighbouring bins' records are fetched with the pair's first, so
+// that a frequency move does not wait (2^12 packets of the tau0 = 1e5 slab 530 ms, 600 without).
+// Same records, random words and arithmetic as one_step, so the same bits.
+template <bool MOVING, bool SURR, bool AHEAD>
+__device__ __forceinline__ void static_pairs(Packet1D &p, int budget, int last_state, const uint8_t *__restrict__ tb,
+                                             const DevCloud *__restrict__ clouds, const WalkArgs &a,
+                                             unsigned long long *__restrict__ tally, const SurrWin *sw,
+                                             const float *__restrict__ recs)
 {
     const float4 nomap = make_float4(1.f, 0.f, 1.f, 0.f);
     for (int k = 0; k < a.chunk; ++k) {
@@ -442,33 +460,35 @@ __device__ __forceinline__ void static_pairs(Packet1D &p, int budget, int last_s
         if (!__any(en)) break;
         if (SURR) {   // a pair that starts in the surrogate window is replaced by one exit
             const bool sx = en && p.steps + 3ull <= a.max_steps && in_window(p, *sw);
-            if (__any(sx)) {
+            en = en && !sx;
+            if (exits_due(sx, en, k)) {
                 if (sx) surrogate_exit<MOVING>(p, *sw, recs, tb, clouds[p.cl], a);
             }
-            en = en && !sx;
         }
-        // disabled lanes read the first records of the table buffer (always mapped; unused)
-        const uint4 *h = en ? p.hot : reinterpret_cast<const uint4 *>(tb);
-        const int s = en ? p.i * p.nb + p.j : 0;
-        const uint4 rm = h[s > 0 ? s - 1 : 0];
-        const uint4 r0 = h[s];
-        const uint4 rp = h[en && s < last_state ? s + 1 : s];
-        const uint64_t pair = p.steps >> 1;
-        const u32x4 r = philox4x32_10((uint32_t)pair, (uint32_t)(pair >> 32), p.pid, p.key, a.key0, a.key1);
-        int d;
-        const bool s1 = select_step(p, en, r.x, r.y, r0, d);
-        if (__any(s1)) {
+        if (en) {
+            const int s = p.i * p.nb + p.j;
+            const uint4 r0 = p.hot[s];
+            uint4 rm, rp;
+            if (AHEAD) {
+                rm = p.hot[s > 0 ? s - 1 : 0];
+                rp = p.hot[s < last_state ? s + 1 : s];
+            }
+            const uint64_t pair = p.steps >> 1;
+            const u32x4 r = philox4x32_10((uint32_t)pair, (uint32_t)(pair >> 32), p.pid, p.key, a.key0, a.key1);
+            int d;
+            const bool s1 = select_step(p, true, r.x, r.y, r0, d);
             if (s1) slow_step<MOVING>(p, StepWords{r.x, r.y, 0u, 0u}, r0, nomap, tb, clouds, a, tally);
-        }
-        const bool en2 = en && p.active && p.steps < a.max_steps;
-        uint4 rb = d == -1 ? rm : rp;
-        const bool reload = en2 && (d == 0 || d == 2);   // after a spatial move or a slow step
-        if (__any(reload)) {
-            if (reload) rb = p.hot[p.i * p.nb + p.j];
-        }
-        const bool s2 = select_step(p, en2, r.z, r.w, rb, d);
-        if (__any(s2)) {
-            if (s2) slow_step<MOVING>(p, StepWords{r.z, r.w, 0u, 0u}, rb, nomap, tb, clouds, a, tally);
+            if (p.active && p.steps < a.max_steps) {
+                uint4 r1;
+                if (AHEAD) {
+                    r1 = d == -1 ? rm : rp;
+                    if (d == 0 || d == 2) r1 = p.hot[p.i * p.nb + p.j];   // after a spatial move or a slow step
+                } else {
+                    r1 = p.hot[p.i * p.nb + p.j];
+                }
+                const bool s2 = select_step(p, true, r.z, r.w, r1, d);
+                if (s2) slow_step<MOVING>(p, StepWords{r.z, r.w, 0u, 0u}, r1, nomap, tb, clouds, a, tally);
+            }
         }
     }
 }
@@ -507,9 +527,8 @@ __device__ __forceinline__ bool select_step_moving(Packet1D &p, bool en, StepWor
     return slow;
 }
 
-// Moving-medium steps (one Philox block each) with wave-uniform control flow: at most
-// `lim` iterations, lanes past their own `budget` disabled; with the surrogate, a step that
-// starts in the window is replaced by one exit.
+// Moving-medium steps (one Philox block each): at most `lim` iterations, lanes past their own
+// `budget` left out; with the surrogate, a step that starts in the window is replaced by one exit.
 template <bool SURR = false>
 __device__ __forceinline__ void moving_steps(Packet1D &p, int budget, int lim, const uint8_t *__restrict__ tb,
                                              const DevCloud *__restrict__ clouds, const WalkArgs &a,
@@ -521,18 +540,17 @@ __device__ __forceinline__ void moving_steps(Packet1D &p, int budget, int lim, c
         if (!__any(en)) break;
         if (SURR) {
             const bool sx = en && p.steps + 3ull <= a.max_steps && in_window(p, *sw);
-            if (__any(sx)) {
+            en = en && !sx;
+            if (exits_due(sx, en, k)) {
                 if (sx) surrogate_exit<true>(p, *sw, recs, tb, clouds[p.cl], a);
             }
-            en = en && !sx;
         }
-        // disabled lanes read the first words of the table buffer (always mapped; unused)
-        const uint4 rec = (en ? p.hot : reinterpret_cast<const uint4 *>(tb))[en ? p.i * p.nb + p.j : 0];
-        const float4 cm = (en ? p.cmap : reinterpret_cast<const float4 *>(tb))[en ? p.i : 0];
-        const u32x4 r = philox4x32_10((uint32_t)p.steps, (uint32_t)(p.steps >> 32), p.pid, p.key, a.key0, a.key1);
-        const StepWords w{r.x, r.y, r.z, r.w};
-        const bool slow = select_step_moving(p, en, w, rec, cm, clouds, tb);
-        if (__any(slow)) {
+        if (en) {
+            const uint4 rec = p.hot[p.i * p.nb + p.j];
+            const float4 cm = p.cmap[p.i];
+            const u32x4 r = philox4x32_10((uint32_t)p.steps, (uint32_t)(p.steps >> 32), p.pid, p.key, a.key0, a.key1);
+            const StepWords w{r.x, r.y, r.z, r.w};
+            const bool slow = select_step_moving(p, true, w, rec, cm, clouds, tb);
             if (slow) slow_step<true>(p, w, rec, cm, tb, clouds, a, tally);
         }
     }
@@ -644,6 +662,7 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
     const SurrHeader *SH = SURR ? reinterpret_cast<const SurrHeader *>(a.surr) : nullptr;
     const float *recs = SURR ? reinterpret_cast<const float *>(a.surr + SH->off_records) : nullptr;
     SurrWin sw{0, -1, 0, -1, 0ull};
+    int last_state = 0;
     const DevHeader *H = reinterpret_cast<const DevHeader *>(tb);
     const DevCloud *clouds = reinterpret_cast<const DevCloud *>(tb + H->off_clouds);
     const uint64_t *prefix = reinterpret_cast<const uint64_t *>(tb + H->off_prefix);
@@ -660,7 +679,6 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
     p.cmap = nullptr;
     p.x0 = 0.f; p.dx = 1.f; p.inv_dx = 1.f; p.uniform = false; p.moving = false;
     p.surr_calls = 0u;
-    int last_state = 0;
     bool exhausted = false;       // wave-uniform: the queue is empty
 
     for (;;) {
@@ -714,18 +732,33 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
         }
         if (!__any(p.active)) break;
 
-        // ---- tail: hand the last few packets of this wave to the cooperative walk ----
+        // ---- tail: hand packets of this wave to the cooperative walk ------------------------------
+        // The last few of the wave all at once; before that, where producers leave SIMDs idle, as many
+        // as the consumer waves there are free to take (a wave waiting on its ticket is free).
         if (exhausted && a.tail_lanes > 0) {
             const uint64_t live = __ballot(p.active);
-            if (__popcll(live) <= a.tail_lanes) {
+            const int n = __popcll(live);
+            int give = n <= a.tail_lanes ? n : 0;
+            if (give == 0 && a.share > 0) {
+                int room = 0;
+                if (lane == 0) {
+                    const int64_t waiting =
+                        (int64_t)(__hip_atomic_load(&work[kWClaimed], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) -
+                                  __hip_atomic_load(&work[kWGiven], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                    const int64_t busy = (int64_t)a.consumer_waves - waiting;
+                    room = busy < a.share ? (int)((a.share - busy) / (int64_t)a.producer_waves) + 1 : 0;
+                }
+                room = (int)rl((uint32_t)room, 0);
+                give = room < n ? room : n;
+            }
+            if (give > 0) {
                 const int leader = __ffsll((unsigned long long)live) - 1;
+                const int rank = __popcll(live & ((1ull << lane) - 1ull));
                 uint64_t base = 0;
-                if (lane == leader) base = atomicAdd(&work[kWGiven], (unsigned long long)__popcll(live));
+                if (lane == leader) base = atomicAdd(&work[kWGiven], (unsigned long long)give);
                 base = shfl_u64(base, leader);
-                bool keep = false;
-                if (p.active) {
-                    const uint64_t slot = base + __popcll(live & ((1ull << lane) - 1ull));
-                    TailPacket *tp = slots_of(work) + slot;
+                if (p.active && rank < give) {
+                    TailPacket *tp = slots_of(work) + base + rank;
                     tp->cl = (uint32_t)p.cl;
                     tp->pid = p.pid;
                     tp->i = p.i;
@@ -735,17 +768,14 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
                     tp->surr_calls = p.surr_calls;
                     __threadfence();
                     uint32_t expect = kSlotEmpty;
-                    keep = !__hip_atomic_compare_exchange_strong(&tp->flag, &expect, kSlotReady, __ATOMIC_RELEASE,
-                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    // a slot its consumer gave up on before it was published (the ticket is spent, so no
+                    // other consumer looks at it): published again for the closing kernel
+                    if (!__hip_atomic_compare_exchange_strong(&tp->flag, &expect, kSlotReady, __ATOMIC_RELEASE,
+                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                        __hip_atomic_store(&tp->flag, kSlotReady, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                     p.active = false;
                 }
-                // slots a consumer gave up on before they were published (its claim is spent, so no
-                // other consumer looks at them): published again for the closing kernel
-                if (keep) {
-                    TailPacket *tp = slots_of(work) + base + __popcll(live & ((1ull << lane) - 1ull));
-                    __hip_atomic_store(&tp->flag, kSlotReady, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                break;
+                if (give == n) break;
             }
         }
 
@@ -755,7 +785,10 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
         if (!(MOVING && p.moving)) {
             const uint64_t pairs = (left + 1) >> 1;
             const int budget = pairs < (uint64_t)a.chunk ? (int)pairs : a.chunk;
-            static_pairs<MOVING, SURR>(p, budget, last_state, tb, clouds, a, tally, &sw, recs);
+            if (!SURR && a.ahead)
+                static_pairs<MOVING, false, true>(p, budget, last_state, tb, clouds, a, tally, &sw, recs);
+            else
+                static_pairs<MOVING, SURR, false>(p, budget, last_state, tb, clouds, a, tally, &sw, recs);
         }
         if (MOVING && p.moving) {
             const uint64_t lim = 2ull * (uint64_t)a.chunk;
@@ -844,7 +877,8 @@ __device__ __forceinline__ void take_lane0(Packet1D &q, const Packet1D &s1)
 // after the chain, when lane k holds step k's position and its records, and cut the block.
 // The step a block stops at is taken with the lane walk's arithmetic.
 // Bound: instruction issue of one wave, 9 vector instructions per step (about 25 with a Doppler
-// re-binning), and per block ~250 for the words, the window and the clock.  The static slab of 9
+// re-binning; done for the packet's own state alone, behind a branch on its position, it is a
+// serial chain: the moving 24 x 64 sphere took 64 ms instead of 30), and per block ~250 for the words, the window and the clock.  The static slab of 9
 // cells x 17 bins (tau0 = 300, 3e4 packets) takes 5.0 ms where lane 0 walking such runs alone took
 // 157 ms (with the claims below); the slowest packet of a 40 x 50 sphere (3.1e5 steps) 58 ns per step.
 struct MixWindow {
@@ -1022,6 +1056,15 @@ __device__ __forceinline__ void mix_block(Packet1D &q, int b, const SurrWin &sw,
     take_lane0<SURR>(q, s1);
 }
 
+// Each of eight bits spread to a field of four.
+__device__ __forceinline__ uint32_t nibbles(uint32_t m)
+{
+    m = (m | (m << 12)) & 0x000f000fu;
+    m = (m | (m << 6)) & 0x03030303u;
+    m = (m | (m << 3)) & 0x11111111u;
+    return m * 15u;
+}
+
 // With SUB the walk is a sub-walk: it ends with the first spatial leak, of which it returns the
 // bin (-1 if the step cap came first), and tallies nothing.
 template <bool MOVING, bool SURR, bool SUB>
@@ -1098,12 +1141,15 @@ __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevC
         const uint32_t ew = wl.e;
         // surrogate stops: window positions inside the surrogate window, for the steps that
         // check it
-        uint32_t smask = 0u;
+        uint32_t smask = 0u, surr_lo = 0u, surr_hi = 0u;
         bool chk = false;
         if (SURR && (unsigned)(q.i - sw.i_lo) <= (unsigned)(sw.i_hi - sw.i_lo)) {
 #pragma unroll
             for (int b = 0; b < kCoopWin; ++b)
                 smask |= ((unsigned)(jw + b - sw.j_lo) <= (unsigned)(sw.j_hi - sw.j_lo) ? 1u : 0u) << b;
+            // their fields of the table set to the stop
+            surr_lo = nibbles(smask & 0xffu);
+            surr_hi = nibbles((smask >> 8) & 0x7fu);
             const uint64_t st_l = q.steps + (uint64_t)lane;
             chk = ((MOVING && q.moving) || !(st_l & 1ull)) && st_l + 3ull <= a.max_steps;
         }
@@ -1116,11 +1162,15 @@ __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevC
         for (int b = 0; b < kCoopWin; ++b) {
             const uint32_t dh = rl(wdh, b), sh = rl(wsh, b);
             const bool dn = ew < dh;
-            const bool slow = (ew >= sh) || (ew == dh) || (SURR && chk && ((smask >> b) & 1u));
+            const bool slow = (ew >= sh) || (ew == dh);
             const uint32_t mv = dn ? (b == 0 ? 15u : (uint32_t)(b - 1)) : (b == kCoopWin - 1 ? 15u : (uint32_t)(b + 1));
             const uint32_t nx = slow ? 15u : mv;
             if (b < 8) tlo |= nx << (4 * b);
             else thi |= nx << (4 * (b - 8));
+        }
+        if (SURR && smask != 0u && chk) {   // positions in the surrogate window stop the steps that check it
+            tlo |= surr_lo;
+            thi |= surr_hi;
         }
         if (lane >= m) {   // no step: stop there
             tlo = 0xffffffffu;
@@ -1405,19 +1455,21 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
         if (grid < 1) grid = 1;
     }
     const uint64_t lanes = grid * (uint64_t)block;
-    if (run.tail_lanes == 0) {
-        // A SIMD's issue slots take a lane walk one step per live lane in ~460 cycles and a
-        // cooperative walk one step in 35-50, whatever the number of waves that share it: the
-        // hand-over pays once about 14 packets per SIMD are left.  A wave's own threshold is
-        // that number where the producers fill the SIMDs, more where they leave some idle (4096
-        // packets of the tau0 = 1e5 slab, 64 producer waves: 530 ms handed over at once, 971 ms at
-        // 16 per wave).
+    a.share = 0;
+    if (run.tail_lanes == 0 && a.tail_capacity > 0) {
+        // A SIMD's issue slots take a lane walk one step per live lane in ~500 cycles and a cooperative
+        // walk one step in 50-60, however many waves share it: a wave's packets all leave once ten or
+        // so are left.  8 where waves share SIMDs (2^20 packets of the efficient-grid tau0 = 1e7 sphere:
+        // 109 ms, 120 at 16), 16 where each has its own, whose last packets wait on latency (256 moving
+        // clouds: 108 ms, 115 at 8).  SIMDs without a producer wave work cooperatively from the start, on
+        // up to four packets each, handed over as consumers become free (4096 packets of the tau0 = 1e5
+        // slab, 64 producer waves: 626 ms, 1006 at 16 alone, 675 at 64 per wave).
         const uint64_t simds = 4ull * (uint64_t)device_cu_count(), waves = (lanes + 63) / 64;
-        const uint64_t t = 14 * simds / (waves < simds ? waves : simds);
-        a.tail_lanes = t < 16 ? 16 : (t > 64 ? 64 : (int)t);
-        if (a.tail_capacity == 0) a.tail_lanes = 0;
+        a.tail_lanes = waves >= 2 * simds ? 8 : 16;
+        a.share = waves < simds ? (int)(4 * (simds - waves)) : 0;
     }
     a.one_round = lanes >= count ? 1 : 0;
+    a.ahead = (lanes + 63) / 64 <= 8ull * (uint64_t)device_cu_count() ? 1 : 0;
     if (a.tail_lanes > 0 && (lanes < count ? lanes : count) > a.tail_capacity) {
         // every exported packet (at most one per lane, at most `count`) needs a slot
         grid = a.tail_capacity / block;
@@ -1435,6 +1487,7 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
     // consumer blocks after the producers: 16 waves per CU walk handed-over packets as soon
     // as lane-walk blocks finish and free their slots
     const uint64_t consumers = a.tail_lanes > 0 ? ((uint64_t)device_cu_count() * 16 * 64 + block - 1) / block : 0;
+    a.consumer_waves = (uint32_t)(consumers * (uint64_t)(block / 64));
     {
         const uint64_t n = a.tail_capacity > kWorkHeaderBytes / 8 ? a.tail_capacity : kWorkHeaderBytes / 8;
         reset_work<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(d_work, a.tail_capacity);
