@@ -807,23 +807,26 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
 
 // Cooperative walk of ONE packet by a whole wave (the packet state is wave-uniform).
 //   * The 64 lanes hold the hot records of 64 consecutive bins of the packet's cell (the
-//     band); each block of up to 64 steps walks a 15-bin window of it, centred on the
-//     packet's bin.
-//   * Lane l draws the Philox words of step steps+l and builds the step's transition table
-//     over the window: 4 bits per window position giving the next position, or 15 ("stop")
-//     for a slow-path step (a tie with a threshold, a spatial leak), a move out of the
-//     window, or (with the surrogate) a step that starts in the surrogate window at one of
-//     the lane walk's check points; position 15 maps to itself.
-//   * Each even lane composes its table with the next lane's (two steps per table); the
-//     sequential part is a scalar chain of two instructions per pair of steps (a 4-bit
-//     field extract addressed by the position, a shift-add back to an address); even
-//     lanes receive the position their step starts from, odd lanes take one step from it.
-//   * The lane whose step stops classifies it: a move out of the window completes; a
-//     surrogate exit or a slow-path step runs in lane 0 with the lane walk's arithmetic.
+//     band); each block of up to 128 steps walks a 30-bin window of it.
+//   * Lane l draws the words of two steps (in static media one Philox pair).  A frequency step
+//     changes the parity of the position, so the first of a lane's steps starts at an even and
+//     the second at an odd window position: 15 each, which a table of 4-bit fields in two
+//     registers holds (field m: the next position's index, 15 out of the window).  The tables of
+//     a lane's two steps are composed by shifts and selects of whole words, and so are those of
+//     an even lane and the next.
+//   * The sequential part is a scalar chain of two instructions per four steps (a 4-bit field
+//     extract addressed by the position, a shift-add back to an address); even lanes receive the
+//     position their steps start from, the others derive theirs.
+//   * Each lane then looks at its two steps' thresholds: the first leak, tie, surrogate exit or
+//     move out of the window (or the step cap) ends the block; a move completes, the others run in
+//     lane 0 with the lane walk's arithmetic.
 // The clock gives the bits of the lane walk's ordered FP64 additions (clock_parallel, else
 // in order), so every tally is bit-identical to walking the packet in a single lane.
-constexpr int kCoopWin = 15;
-// scan state: 4 x window position in bits 0..5, field width 4 in bits 16..22 (the operand
+// Bound: dependent instructions of one wave, ~660 a block.  One packet of the tau0 = 1e5 slab (64 x
+// 128) takes 22 ns per step and one of a 3 x 300 slab 29 ns; with one step per lane, 15-bin windows
+// and all stops in the tables (58 instead of 102 steps a block) it was 30 and 37.
+constexpr int kCoopWin = 30;
+// scan state: 4 x position index in bits 0..5, field width 4 in bits 16..22 (the operand
 // layout of s_bfe_u64); kScanStop is the state of the stop position
 constexpr uint32_t kScanWidth = 4u << 16;
 constexpr uint32_t kScanStop = kScanWidth | (15u << 2);
@@ -839,8 +842,8 @@ __device__ __forceinline__ void scan_step(uint32_t &st, int &vst, uint32_t tlo, 
     asm("s_lshl2_add_u32 %0, %1, %2" : "=s"(st) : "s"((uint32_t)f), "s"(kScanWidth) : "scc");
 }
 
-// The chain over two-step tables held by the even lanes (lane 2k: steps 2k and 2k+1),
-// eight steps per group, leaving once the stop is reached.
+// The chain over four-step tables held by the even lanes, sixteen steps per group, leaving once
+// the stop is reached.
 template <int G>
 __device__ __forceinline__ void scan_from(uint32_t &st, int &vst, uint32_t tlo, uint32_t thi)
 {
@@ -878,8 +881,8 @@ __device__ __forceinline__ void take_lane0(Packet1D &q, const Packet1D &s1)
 // The step a block stops at is taken with the lane walk's arithmetic.
 // Bound: instruction issue of one wave, 9 vector instructions per step (about 25 with a Doppler
 // re-binning; done for the packet's own state alone, behind a branch on its position, it is a
-// serial chain: the moving 24 x 64 sphere took 64 ms instead of 30), and per block ~250 for the words, the window and the clock.  The static slab of 9
-// cells x 17 bins (tau0 = 300, 3e4 packets) takes 5.0 ms where lane 0 walking such runs alone took
+// serial chain: the moving 24 x 64 sphere took 64 ms instead of 30), and per block ~250 for the
+// words, the window and the clock.  The static slab of 9 cells x 17 bins (tau0 = 300, 3e4 packets) takes 5.0 ms where lane 0 walking such runs alone took
 // 157 ms (with the claims below); the slowest packet of a 40 x 50 sphere (3.1e5 steps) 58 ns per step.
 struct MixWindow {
     int b, wi, wj;                             // shape and corner
@@ -1056,13 +1059,22 @@ __device__ __forceinline__ void mix_block(Packet1D &q, int b, const SurrWin &sw,
     take_lane0<SURR>(q, s1);
 }
 
+// The fields of four that hold 15, all others zero.
+__device__ __forceinline__ uint32_t full_fields(uint32_t v)
+{
+    v &= v >> 1;
+    v &= v >> 2;
+    v &= 0x11111111u;
+    return (v << 4) - v;
+}
+
 // Each of eight bits spread to a field of four.
 __device__ __forceinline__ uint32_t nibbles(uint32_t m)
 {
     m = (m | (m << 12)) & 0x000f000fu;
     m = (m | (m << 6)) & 0x03030303u;
     m = (m | (m << 3)) & 0x11111111u;
-    return m * 15u;
+    return (m << 4) - m;
 }
 
 // With SUB the walk is a sub-walk: it ends with the first spatial leak, of which it returns the
@@ -1087,6 +1099,8 @@ __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevC
     bool mixed = false;
     int nt = 0, ns = 0;  // recent steps and spatial leaks (mixed blocks)
     uint32_t v_lk = 0u, v_dhi = 0u, v_shi = 0u, v_fhi = 0u;
+    int jw = 0;
+    uint32_t w_dh[kCoopWin];   // the window's lower thresholds, halved
     while (q.active) {
         const uint64_t left = a.max_steps - q.steps;
         if (left == 0) {
@@ -1112,10 +1126,10 @@ __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevC
             }
             continue;
         }
-        const int m = left < 64 ? (int)left : 64;
         // band of 64 bins around the packet (reloaded on a new cell or near its edges)
-        if (q.i != wi || (q.j - jb < kCoopWin / 2 && jb > 0) ||
-            (q.j - jb > 63 - kCoopWin / 2 && jb < q.nb - 64)) {
+        const bool fresh = q.i != wi || (q.j - jb <= kCoopWin / 2 && jb > 0) ||
+                           (q.j - jb > 63 - kCoopWin / 2 && jb < q.nb - 64);
+        if (fresh) {
             jb = q.j - 32;
             if (jb > q.nb - 64) jb = q.nb - 64;
             if (jb < 0) jb = 0;
@@ -1133,103 +1147,130 @@ __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevC
                 v_fhi = r.w;
             }
         }
-        int jw = q.j - kCoopWin / 2;
-        if (jw > jb + 64 - kCoopWin) jw = jb + 64 - kCoopWin;
-        if (jw < jb) jw = jb;
+        // The window stays where it is while the packet keeps off its edges.  A static walk pairs its
+        // steps by count: the packet is at an even position of the window before the first of a pair.
+        const bool mv = MOVING && q.moving;
+        if (fresh || (unsigned)(q.j - jw - 5) > (unsigned)(kCoopWin - 11) || (!mv && ((q.j - jw) ^ (int)q.steps) & 1)) {
+            jw = q.j - kCoopWin / 2;
+            if (jw > jb + 64 - kCoopWin) jw = jb + 64 - kCoopWin;
+            if (jw < jb) jw = jb;
+            if (!mv && ((q.j - jw) ^ (int)q.steps) & 1) jw += jw == jb + 64 - kCoopWin ? 1 : -1;   // off the grid at most
+#pragma unroll
+            for (int b = 0; b < kCoopWin; ++b) w_dh[b] = rl(v_dhi, (jw - jb + b) & 63) >> 1;
+        }
         const int wb = jw - jb;   // band lane of window position 0
-        const StepWords wl = words_of_step<MOVING>(q, q.steps + (uint64_t)lane, a);
-        const uint32_t ew = wl.e;
-        // surrogate stops: window positions inside the surrogate window, for the steps that
-        // check it
-        uint32_t smask = 0u, surr_lo = 0u, surr_hi = 0u;
-        bool chk = false;
-        if (SURR && (unsigned)(q.i - sw.i_lo) <= (unsigned)(sw.i_hi - sw.i_lo)) {
-#pragma unroll
-            for (int b = 0; b < kCoopWin; ++b)
-                smask |= ((unsigned)(jw + b - sw.j_lo) <= (unsigned)(sw.j_hi - sw.j_lo) ? 1u : 0u) << b;
-            // their fields of the table set to the stop
-            surr_lo = nibbles(smask & 0xffu);
-            surr_hi = nibbles((smask >> 8) & 0x7fu);
-            const uint64_t st_l = q.steps + (uint64_t)lane;
-            chk = ((MOVING && q.moving) || !(st_l & 1ull)) && st_l + 3ull <= a.max_steps;
-        }
-        // the window's thresholds rotated into lanes 0..14
-        const uint32_t wdh = (uint32_t)__shfl((int)v_dhi, (wb + lane) & 63);
-        const uint32_t wsh = (uint32_t)__shfl((int)v_shi, (wb + lane) & 63);
-        // the step's table: field b = next window position from position b
-        uint32_t tlo = 0u, thi = 15u << 28;
-#pragma unroll
-        for (int b = 0; b < kCoopWin; ++b) {
-            const uint32_t dh = rl(wdh, b), sh = rl(wsh, b);
-            const bool dn = ew < dh;
-            const bool slow = (ew >= sh) || (ew == dh);
-            const uint32_t mv = dn ? (b == 0 ? 15u : (uint32_t)(b - 1)) : (b == kCoopWin - 1 ? 15u : (uint32_t)(b + 1));
-            const uint32_t nx = slow ? 15u : mv;
-            if (b < 8) tlo |= nx << (4 * b);
-            else thi |= nx << (4 * (b - 8));
-        }
-        if (SURR && smask != 0u && chk) {   // positions in the surrogate window stop the steps that check it
-            tlo |= surr_lo;
-            thi |= surr_hi;
-        }
-        if (lane >= m) {   // no step: stop there
-            tlo = 0xffffffffu;
-            thi = 0xffffffffu;
-        }
-        // even lanes: the table of two steps (this lane's, then the next lane's)
-        const uint64_t tab = ((uint64_t)thi << 32) | tlo;
-        const uint64_t nxt = ((uint64_t)(uint32_t)__shfl_down((int)thi, 1) << 32) | (uint32_t)__shfl_down((int)tlo, 1);
-        uint32_t clo = 0u, chi = 0u;
-#pragma unroll
-        for (int b = 0; b < 16; ++b) {
-            const uint32_t mid = (uint32_t)(tab >> (4 * b)) & 15u;
-            const uint32_t two = (uint32_t)(nxt >> (4 * mid)) & 15u;
-            if (b < 8) clo |= two << (4 * b);
-            else chi |= two << (4 * (b - 8));
-        }
-        // sequential part: the chain of positions, in scalar registers, two steps at a time
-        uint32_t st = rl(kScanWidth | ((uint32_t)(q.j - jw) << 2), 0);
-        int vst = (int)kScanStop;
-        scan_from<0>(st, vst, clo, chi);
-        // each lane's starting position (odd lanes: one step from the even lane before);
-        // the first lane whose step stops
-        const int pe = (int)(((uint32_t)vst & 63u) >> 2);
-        const uint32_t ne = (uint32_t)(tab >> (4 * pe)) & 15u;
-        const uint32_t from_even = (uint32_t)__shfl_up((int)ne, 1);
-        const int pl = (lane & 1) ? (int)from_even : pe;
-        const bool stops = pl != 15 && ((uint32_t)(tab >> (4 * pl)) & 15u) == 15u;
-        const uint64_t sb = __ballot(stops);
-        const int ls = sb ? __ffsll((unsigned long long)sb) - 1 : 64;
-        // the records of the lane's bin
-        const int src = (wb + (pl < 15 ? pl : 0)) & 63;
-        const uint32_t lk = (uint32_t)__shfl((int)v_lk, src);
-        const uint32_t dhl = (uint32_t)__shfl((int)v_dhi, src);
-        const uint32_t shl = (uint32_t)__shfl((int)v_shi, src);
-        int done, pos;
-        bool special = false, surr_stop = false;
-        if (ls >= m) {                         // m steps, no stop
-            done = m;
-            pos = ls < 64 ? (int)rl((uint32_t)pl, ls) : (int)((st & 63u) >> 2);
+        // each lane's two steps, from an even and an odd position; a packet at an odd one starts with
+        // the second step of lane 0
+        const int odd = (q.j - jw) & 1;
+        StepWords wa, wc;
+        if (mv) {
+            wa = words_of_step<MOVING>(q, q.steps + 2ull * (uint64_t)lane - (uint64_t)odd, a);
+            wc = words_of_step<MOVING>(q, q.steps + 2ull * (uint64_t)lane - (uint64_t)odd + 1ull, a);
         } else {
-            const bool sstop = SURR && chk && pl < 15 && ((smask >> pl) & 1u);
-            surr_stop = SURR && rl(sstop ? 1u : 0u, ls) != 0u;
-            const uint32_t slow = (sstop || (ew >= shl) || (ew == dhl)) ? 1u : 0u;
-            const int p = (int)rl((uint32_t)pl, ls);
-            if (rl(slow, ls)) {                // step ls takes the slow path
-                special = true;
-                done = ls;
-                pos = p;
-            } else {                           // step ls leaves the window: it is done
-                done = ls + 1;
-                pos = p + (rl(ew < dhl ? 1u : 0u, ls) ? -1 : 1);
+            const uint64_t pr = (q.steps >> 1) + (uint64_t)lane;
+            const u32x4 r = philox4x32_10((uint32_t)pr, (uint32_t)(pr >> 32), q.pid, q.key, a.key0, a.key1);
+            wa = StepWords{r.x, r.y, 0u, 0u};
+            wc = StepWords{r.z, r.w, 0u, 0u};
+        }
+        const bool none = lane == 0 && odd != 0;   // the step taken before
+        // bit m: the first step from position 2m, the second from 2m + 1 goes down (the sign of a
+        // difference of halves; equal halves count as ties below)
+        const uint32_t ea = wa.e >> 1, ec = wc.e >> 1;
+        uint32_t da = 0u, dc = 0u;
+#pragma unroll
+        for (int m = kCoopWin / 2 - 1; m >= 0; --m) {
+            da = __funnelshift_l(ea - w_dh[2 * m], da, 1);
+            dc = __funnelshift_l(ec - w_dh[2 * m + 1], dc, 1);
+        }
+        // tables of next positions, one 4-bit field per position (15: out of the window).  The second
+        // step leads from 2m + 1 to m or m + 1, both together from 2m to where the second leads from
+        // 2 (m - 1) + 1 or 2m + 1
+        const uint32_t da_lo = nibbles(da & 0xffu), da_hi = nibbles(da >> 8);
+        const uint32_t dc_lo = nibbles(dc & 0xffu), dc_hi = nibbles(dc >> 8);
+        const uint32_t b_lo = (0x76543210u & dc_lo) | (0x87654321u & ~dc_lo);
+        const uint32_t b_hi = (0xfedcba98u & dc_hi) | (0xffedcba9u & ~dc_hi);
+        uint32_t c_lo = ((b_lo << 4 | 0xfu) & da_lo) | (b_lo & ~da_lo);
+        uint32_t c_hi = (__funnelshift_l(b_lo, b_hi, 4) & da_hi) | (b_hi & ~da_hi) | 0xf0000000u;
+        if (none) {
+            c_lo = b_lo;
+            c_hi = b_hi;
+        }
+        // even lanes: the table of four steps (this lane's, then the next lane's): the two steps of a
+        // lane go one field down, nowhere or one up; the one step of `none` nowhere or up
+        const uint32_t n_lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c_lo, 0xf5, 0xf, 0xf, false);
+        const uint32_t n_hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c_hi, 0xf5, 0xf, 0xf, false);
+        const uint32_t dd_lo = none ? 0u : da_lo & (dc_lo << 4);
+        const uint32_t dd_hi = none ? 0u : da_hi & __funnelshift_l(dc_lo, dc_hi, 4);
+        const uint32_t uu_lo = ~((none ? 0u : da_lo) | dc_lo), uu_hi = ~((none ? 0u : da_hi) | dc_hi);
+        uint32_t f_lo = ((n_lo << 4) & dd_lo) | (__funnelshift_r(n_lo, n_hi, 4) & uu_lo) | (n_lo & ~(dd_lo | uu_lo));
+        uint32_t f_hi = (__funnelshift_l(n_lo, n_hi, 4) & dd_hi) | ((n_hi >> 4) & uu_hi) | (n_hi & ~(dd_hi | uu_hi));
+        f_lo |= full_fields(c_lo);
+        f_hi |= full_fields(c_hi);
+        // sequential part: the chain of positions, in scalar registers, four steps at a time
+        uint32_t st = rl(kScanWidth | ((uint32_t)(q.j - jw) >> 1 << 2), 0);
+        int vst = (int)kScanStop;
+        scan_from<0>(st, vst, f_lo, f_hi);
+        // each lane's starting position (odd lanes: two steps from the even lane before); what its
+        // steps do there
+        const uint32_t p4 = (uint32_t)vst & 63u;
+        const uint32_t after = (p4 < 32u ? c_lo >> p4 : c_hi >> (p4 - 32u)) & 15u;
+        const uint32_t from_even = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)after, 0xa0, 0xf, 0xf, false);
+        const int ma = (lane & 1) ? (int)from_even : (int)(p4 >> 2);
+        const int mc = ma - (none ? 0 : (int)((da >> ma) & 1u));
+        const int pa = 2 * ma, pc = 2 * mc + 1;
+        const int pd = pc + 1 - 2 * (int)((dc >> (mc & 31)) & 1u);
+        const int la = (wb + pa) & 63, lc = (wb + pc) & 63;
+        const uint32_t lk_a = (uint32_t)__shfl((int)v_lk, la), lk_c = (uint32_t)__shfl((int)v_lk, lc);
+        const uint32_t dh_a = (uint32_t)__shfl((int)v_dhi, la), dh_c = (uint32_t)__shfl((int)v_dhi, lc);
+        const uint32_t sh_a = (uint32_t)__shfl((int)v_shi, la), sh_c = (uint32_t)__shfl((int)v_shi, lc);
+        // stops: leaks, ties, surrogate exits, the step cap
+        bool slow_a = !none && (wa.e >= sh_a || ea == dh_a >> 1), slow_c = wc.e >= sh_c || ec == dh_c >> 1;
+        bool exit_a = false, exit_c = false;
+        if (SURR && (unsigned)(q.i - sw.i_lo) <= (unsigned)(sw.i_hi - sw.i_lo)) {
+            const uint64_t k = 2ull * (uint64_t)lane - (uint64_t)odd;
+            exit_a = !none && k + 3ull <= left && (unsigned)(jw + pa - sw.j_lo) <= (unsigned)(sw.j_hi - sw.j_lo);
+            exit_c = mv && k + 4ull <= left && (unsigned)(jw + pc - sw.j_lo) <= (unsigned)(sw.j_hi - sw.j_lo);
+            slow_a |= exit_a;
+            slow_c |= exit_c;
+        }
+        if (left < 128ull) {
+            slow_a |= 2 * lane - odd >= (int)left;
+            slow_c |= 2 * lane + 1 - odd >= (int)left;
+        }
+        const bool end_a = slow_a || (unsigned)pc >= (unsigned)kCoopWin;
+        const bool end_c = slow_c || (unsigned)pd >= (unsigned)kCoopWin;
+        // the first step that stops: one that leaves the window is done, any other is not
+        const uint64_t sb = __ballot(ma != 15 && (end_a || end_c));
+        int done = 128, pos = (int)((st & 63u) >> 1);
+        bool special = false, surr_stop = false;
+        StepWords ws = {0u, 0u, 0u, 0u};
+        if (sb) {
+            const int ls = __ffsll((unsigned long long)sb) - 1;
+            const uint32_t kind = (end_a ? 0u : 1u) | ((end_a ? slow_a : slow_c) ? 2u : 0u) |
+                                  ((end_a ? exit_a : exit_c) ? 4u : 0u);
+            const uint32_t kd = rl(kind, ls);
+            special = (kd & 2u) != 0u;
+            done = 2 * ls + (int)(kd & 1u) + (special ? 0 : 1);
+            pos = (int)rl((uint32_t)(special ? (end_a ? pa : pc) : (end_a ? pc : pd)), ls);
+            surr_stop = SURR && (kd & 4u) != 0u;
+            if (special) {
+                ws.t = (kd & 1u) ? rl(wc.t, ls) : rl(wa.t, ls);
+                ws.e = (kd & 1u) ? rl(wc.e, ls) : rl(wa.e, ls);
+                ws.z = (kd & 1u) ? rl(wc.z, ls) : rl(wa.z, ls);
+                ws.w = (kd & 1u) ? rl(wc.w, ls) : rl(wa.w, ls);
             }
         }
-        const float dl = lane < done ? path_length(wl.t, __uint_as_float(lk)) : 0.0f;
-        const double dd = (double)dl;
-        const uint32_t dlo = (uint32_t)__double_as_longlong(dd);
-        const uint32_t dhi = (uint32_t)((uint64_t)__double_as_longlong(dd) >> 32);
+        const double ta = 2 * lane < done && !none ? (double)path_length(wa.t, __uint_as_float(lk_a)) : 0.0;
+        const double tc = 2 * lane + 1 < done ? (double)path_length(wc.t, __uint_as_float(lk_c)) : 0.0;
         double t = q.t;                    // the lane walk's FP64 additions, same bits
-        if (done > 0 && !clock_parallel(t, dd)) clock_from<0>(t, dlo, dhi, done);
+        if (!clock_parallel(t, ta, tc)) {
+            for (int l = 0; 2 * l < done; ++l) {
+                t += rl_f64(ta, l);
+                t += rl_f64(tc, l);
+            }
+        }
+        done -= odd;
+        special = special && (uint64_t)done < left;
         q.t = t;
         q.steps += (uint64_t)done;
         const int jj = jw + pos;
@@ -1239,7 +1280,6 @@ __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevC
             // the step at `done` in lane 0 with the lane walk's arithmetic; several blocks in a
             // row that stopped early (spatial leaks are frequent here) hand over to mixed blocks
             const int b = (jj - jb) & 63;
-            const StepWords ws = {rl(wl.t, done), rl(ew, done), rl(wl.z, done), rl(wl.w, done)};
             const uint4 rec = make_uint4(rl(v_lk, b), rl(v_dhi, b), rl(v_shi, b), rl(v_fhi, b));
             Packet1D s1 = q;
             if (lane == 0 && SURR && surr_stop) {

@@ -44,18 +44,17 @@ __device__ __forceinline__ double rl_f64(double v, int lane)
 // halfway between integers (then the rounding depends on the running sum).  Without such
 // a tie the block's result is t0 + ulp * (sum of the rint values): an exact integer sum,
 // reduced across the wave in any order.  Returns false (t unchanged) where the premises
-// fail; the caller then adds in order.
-__device__ __forceinline__ bool clock_parallel(double &t, double dd)
+// fail; the caller then adds in order.  The first form takes two steps per lane.
+__device__ __forceinline__ bool clock_parallel(double &t, double da, double db)
 {
     const uint64_t tbits = (uint64_t)__double_as_longlong(t);
     const int be = (int)((tbits >> 52) & 0x7ffu);
     if (be == 0 || be >= 0x7fe) return false;        // zero, subnormal or near the top
     const int e = be - 1023;
-    const double qv = ldexp(dd, 52 - e);               // exact: a power-of-two scaling
-    const double n = rint(qv);
-    const bool tie = (qv - floor(qv)) == 0.5;
+    const double qa = ldexp(da, 52 - e), qb = ldexp(db, 52 - e);   // exact: power-of-two scalings
+    const bool tie = (qa - floor(qa)) == 0.5 || (qb - floor(qb)) == 0.5;
     if (__any(tie)) return false;
-    double s = n;                                      // integers below 2^53: exact sums
+    double s = rint(qa) + rint(qb);                    // integers below 2^53: exact sums
     s += dpp_f64<0xb1>(s);                             // quad_perm [1,0,3,2]
     s += dpp_f64<0x4e>(s);                             // quad_perm [2,3,0,1]
     s += dpp_f64<0x124>(s);                            // row_ror:4
@@ -66,6 +65,8 @@ __device__ __forceinline__ bool clock_parallel(double &t, double dd)
     t = tf;
     return true;
 }
+
+__device__ __forceinline__ bool clock_parallel(double &t, double dd) { return clock_parallel(t, dd, 0.0); }
 
 // Clock of a block: t += the FP64 path lengths of lanes 0, 1, ... in order (lanes at or
 // beyond `done` hold +0, which leaves t unchanged).

@@ -25,10 +25,18 @@ CASES = {
     "sphere_moving_nonuniform": (media.sphere(300.0, 1e4, 15, 40, v_max=50.0, n_packets=1000).replace(bin_edges=_E), {}),
     "cap_odd": (media.sphere(2e3, 1e4, 24, 64, x_max=8.0, v_max=60.0, n_packets=2000), {"max_steps": 3333}),
     "cap_short": (media.slab(300.0, 1e4, 8, 16, n_packets=2000), {"max_steps": 67}),
+    "slab_3x300": (media.slab(1e3, 1e4, 3, 300, n_packets=600), {}),        # bands move, windows at their edges
+    "slab_2x64": (media.slab(1e3, 1e4, 2, 64, n_packets=600), {}),          # one band covers the grid
+    "slab_2x31": (media.slab(1e3, 1e4, 2, 31, n_packets=600), {}),          # a window and one bin
+    "sphere_moving_wide": (media.sphere(1e3, 1e4, 3, 200, v_max=5.0, n_packets=600), {}),
+    "grid_ends_in_the_core": (media.slab(1e3, 1e4, 4, 101, x_max=2.0, n_packets=600), {"max_steps": 20001}),
+    "cap_in_block": (media.slab(1e4, 1e4, 3, 300, n_packets=600), {"max_steps": 1001}),
+    "cap_in_block_moving": (media.sphere(1e4, 1e4, 3, 200, v_max=5.0, n_packets=600), {"max_steps": 130}),
     "several_waves_per_simd": (media.slab(20.0, 1e4, 8, 16, n_packets=(1 << 18) + 5), {}),
     "one_wave_per_simd": (media.slab(50.0, 1e4, 8, 16, n_packets=(1 << 16) - 3), {}),
     "exit_kernel": (media.sphere(1e5, 1e4, 32, 64, n_packets=2000), {"exit": True}),
     "exit_kernel_moving": (media.sphere(1e5, 1e4, 32, 64, x_max=40.0, v_max=50.0, n_packets=2000), {"exit": True}),
+    "exit_kernel_wide": (media.sphere(1e5, 1e4, 16, 300, n_packets=600), {"exit": True}),
     "exit_kernel_cap": (media.sphere(1e5, 1e4, 32, 64, n_packets=2000), {"exit": True, "max_steps": 301}),
 }
 
