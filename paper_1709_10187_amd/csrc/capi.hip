@@ -525,9 +525,9 @@ rddmc_status rddmc_build_leakage(const rddmc_batch *batch, void *d_tables, size_
                 return hip_fail(e, "hipMemcpyAsync(census)");
         }
     }
+    if ((e = launch_build(L.clouds, static_cast<uint8_t *>(d_tables), s)) != hipSuccess)
+        return hip_fail(e, "build kernels");
     for (int ci = 0; ci < L.h.n_clouds; ++ci) {
-        if ((e = launch_build(L.clouds[ci], ci, static_cast<uint8_t *>(d_tables), s)) != hipSuccess)
-            return hip_fail(e, "build kernels");
         if ((e = launch_build_redistribution(L.clouds[ci], static_cast<uint8_t *>(d_tables), s)) != hipSuccess)
             return hip_fail(e, "redistribution kernels");
     }

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/rddmc.h"
 
 namespace rddmc {
@@ -142,7 +144,7 @@ enum BuildError : uint32_t {
 };
 
 // ---- launchers (defined in the .hip translation units) ------------------------------
-hipError_t launch_build(const DevCloud &c, int cloud_index, uint8_t *d_tables, hipStream_t s);
+hipError_t launch_build(const std::vector<DevCloud> &clouds, uint8_t *d_tables, hipStream_t s);
 hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevCloud *host_clouds,
                        const rddmc_run &run, uint64_t first, uint64_t count,
                        unsigned long long *d_tally, unsigned long long *d_work, uint64_t work_bytes,
