@@ -1500,10 +1500,11 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
         // A SIMD's issue slots take a lane walk one step per live lane in ~500 cycles and a cooperative
         // walk one step in 50-60, however many waves share it: a wave's packets all leave once ten or
         // so are left.  8 where waves share SIMDs (2^20 packets of the efficient-grid tau0 = 1e7 sphere:
-        // 109 ms, 120 at 16), 16 where each has its own, whose last packets wait on latency (256 moving
-        // clouds: 108 ms, 115 at 8).  SIMDs without a producer wave work cooperatively from the start, on
-        // up to four packets each, handed over as consumers become free (4096 packets of the tau0 = 1e5
-        // slab, 64 producer waves: 626 ms, 1006 at 16 alone, 675 at 64 per wave).
+        // 109 ms, 120 at 16), 16 where each has its own, whose last packets wait on latency (2^16 packets of
+        // moving spheres: 108 ms, 115 at 8).  SIMDs without a producer wave work cooperatively from the start, on
+        // up to four packets each, handed over as consumers become free (2^14 packets of the tau0 = 1e5
+        // slab, 256 producer waves, with the table blocks of that time: 626 ms, 1006 at 16 alone, 675 at
+        // 64 per wave; 530 ms with the present ones).
         const uint64_t simds = 4ull * (uint64_t)device_cu_count(), waves = (lanes + 63) / 64;
         a.tail_lanes = waves >= 2 * simds ? 8 : 16;
         a.share = waves < simds ? (int)(4 * (simds - waves)) : 0;
