@@ -1424,8 +1424,10 @@ __global__ __launch_bounds__(256) void subwalk1d(const uint8_t *__restrict__ tb,
         if (lane == l) {
             p.t = u.t;
             p.steps = u.steps;
-            face = j < 0 ? -1 : (u.i > i0 ? 1 : 0);
-            jexit = j < 0 ? u.j : j;
+            if (j >= 0) {   // a walk the cap cut keeps its entry bin, as one cut side by side
+                face = u.i > i0 ? 1 : 0;
+                jexit = j;
+            }
         }
     }
     if (!mine) return;
