@@ -748,6 +748,15 @@ struct Window1 {
 constexpr int kPend = 64;                 // position bit: the face pair comes next
 __shared__ unsigned long long s_path_block[kBlockMax];   // a block's residence sums per position
 
+// What the wave's lanes wrote to LDS before is seen by all of them after (the barrier alone holds the
+// lanes together, but lets the compiler take a lane's own earlier store for its later load).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 template <bool WGT>
 __device__ __forceinline__ void window_load(Window1 &w, const Pk1 &q, const DevCloud &c, const uint8_t *__restrict__ tb,
                                             int b, int lane)
@@ -968,12 +977,12 @@ __device__ __forceinline__ bool window_block(Pk1 &q, uint64_t &wp, const DevClou
             // the block's residences per position, then one add per visited state
             unsigned long long *acc = s_path_block + (threadIdx.x & ~63);
             acc[lane] = 0ull;
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             if (lane < done && !face && t1 > t0) {
                 const double r = wgt ? weight_integral(t0, t1, t0, lw0, ka) : t1 - t0;
                 atomicAdd(&acc[at], (unsigned long long)rint(r * kPathFix));
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             const unsigned long long v = acc[lane];
             if (v) {
                 const int64_t s = (int64_t)(w.wi + (lane >> w.b)) * c.nb + w.wj + (lane & ((1 << w.b) - 1));
