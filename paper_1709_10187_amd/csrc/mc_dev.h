@@ -111,13 +111,21 @@ __device__ __forceinline__ void ready(Rng &r, const McArgs &a)
 template <int N>
 __device__ __forceinline__ void peek(const Rng &r, uint32_t *w)
 {
+    // selects of values: a choice between two array elements would be one of addresses, and the
+    // arrays would live in scratch or LDS
     const uint32_t v[8] = {r.c0, r.c1, r.c2, r.c3, r.n0, r.n1, r.n2, r.n3};
     const bool two = (r.idx & 2u) != 0u, one = (r.idx & 1u) != 0u;
     uint32_t y[N + 1];
 #pragma unroll
-    for (int i = 0; i <= N; ++i) y[i] = two ? v[i + 2] : v[i];
+    for (int i = 0; i <= N; ++i) {
+        const uint32_t near = v[i], far = v[i + 2];
+        y[i] = two ? far : near;
+    }
 #pragma unroll
-    for (int i = 0; i < N; ++i) w[i] = one ? y[i + 1] : y[i];
+    for (int i = 0; i < N; ++i) {
+        const uint32_t near = y[i], far = y[i + 1];
+        w[i] = one ? far : near;
+    }
 }
 __device__ __forceinline__ void advance(Rng &r, uint32_t n)
 {
