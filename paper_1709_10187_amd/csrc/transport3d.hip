@@ -601,6 +601,20 @@ __global__ __launch_bounds__(256) void walk3d_coop(const uint8_t *__restrict__ t
     }
 }
 
+// Whether the cooperative walk spends fewer issue cycles on the work of a wave's recent passes than
+// they did: ~1600 a frequency pass, 1500 a leak pass, 3000 an MC pass here; 48 a frequency step, 9000 an
+// MC event and 20000 a leak there (where leaks are most of the steps the lanes keep the packets).  The
+// counts are sums over the passes since a refill, halved at each: below 2^28 with at most kMaxPasses
+// passes, so that their products take 64 bits.
+constexpr int kMaxPasses = 1 << 20;
+__host__ __device__ constexpr bool coop_pays(int pd, int pl, int pm, int wd, int wl, int wm)
+{
+    return 48ll * wd + 20000ll * wl + 9000ll * wm < 1600ll * pd + 1500ll * pl + 3000ll * pm;
+}
+// every pass of the longest run a leak pass, an MC pass or a frequency pass of a full wave; of one lane
+static_assert(!coop_pays(0, 2 * kMaxPasses, 0, 0, 128 * kMaxPasses, 0) && !coop_pays(0, 0, 2 * kMaxPasses, 0, 0, 128 * kMaxPasses));
+static_assert(!coop_pays(2 * kMaxPasses, 0, 0, 256 * kMaxPasses - 1, 0, 0) && coop_pays(2 * kMaxPasses, 0, 0, 4 * kMaxPasses, 0, 0));
+
 template <bool SINGLE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void walk3d(const uint8_t *__restrict__ tb, Walk3Args a,
                                               unsigned long long *__restrict__ tally,
@@ -687,12 +701,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
         }
         if (!__any(p.active)) break;
 
-        // Hand the wave's packets over where the cooperative walk spends fewer issue cycles on the
-        // recent passes' work than they did: ~1600 a frequency pass, 1500 a leak pass, 3000 an MC
-        // pass here; 48 a frequency step, 9000 an MC event and 20000 a leak there (where leaks are most of
-        // the steps the lanes keep the packets).
-        if (a.slots && exhausted &&
-            48 * wd + 20000 * wl + 9000 * wm < 1600 * pd + 1500 * pl + 3000 * pm) {
+        // hand the wave's packets over to the cooperative walk
+        if (a.slots && exhausted && coop_pays(pd, pl, pm, wd, wl, wm)) {
             const uint64_t go = __ballot(p.active);
             const int leader = __ffsll((unsigned long long)go) - 1;
             uint64_t base = 0;
@@ -784,7 +794,7 @@ hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddm
     a.max_steps = run.max_steps;
     a.key0 = (uint32_t)run.seed;
     a.key1 = (uint32_t)(run.seed >> 32);
-    a.chunk = run.chunk > 0 ? run.chunk : 64;
+    a.chunk = run.chunk > 0 ? std::min(run.chunk, kMaxPasses) : 64;
     a.n_clouds = h.n_clouds;
     a.dom = kDom3D;
     const int block = run.block > 0 ? run.block : 256;

@@ -59,3 +59,11 @@ def test_few_export_slots():
     for slots in (0, 1, 100):
         print(f"[3D tail] {slots} slots", flush=True)
         _same(ref, _run(meds, slots=slots))
+
+
+@pytest.mark.parametrize("chunk", [1, 1000, (1 << 31) - 1])
+def test_steps_between_refills_do_not_change_the_bits(chunk):
+    """The hand-over rule counts the passes since a refill, up to the longest the call accepts."""
+    meds = CASES["moving"]
+    print(f"[3D tail] chunk {chunk}", flush=True)
+    _same(_run(meds, tail_lanes=-1), _run(meds, chunk=chunk))
