@@ -1401,8 +1401,11 @@ __global__ __launch_bounds__(256) void walk1dg(const uint8_t *__restrict__ tb, M
     }
 }
 
+// Four waves per SIMD, three with census estimators or weights, two with both: the registers of the
+// hand-over and of the five words of a group event had taken one wave from ten of the sixteen (2^20 packets
+// of eight slabs: weights 1340 -> 1134 ms, census 1226 -> 1125, plain 925 -> 865, four spilled registers).
 template <bool SPH, bool SINGLE, bool WGT, bool CEN>
-__global__ __launch_bounds__(256) void walk1dh(const uint8_t *__restrict__ tb, McArgs a,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGT && CEN ? 2 : (WGT || CEN ? 3 : 4)))) void walk1dh(const uint8_t *__restrict__ tb, McArgs a,
                                                unsigned long long *__restrict__ tally,
                                                unsigned long long *__restrict__ work)
 {

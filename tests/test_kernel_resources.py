@@ -2,6 +2,7 @@
 takes from its packet's stream stay in registers (no scratch, and no LDS beyond the census sums), where the
 walks are bound by instruction issue and a word through memory is a dependent store and load per step."""
 import os
+import re
 import struct
 import subprocess
 
@@ -67,7 +68,15 @@ def test_words_of_the_stream_stay_in_registers(prefix, lds):
     for name, k in _walks(prefix):
         census = name.startswith("walk1dh") and name.endswith("true>")   # path sums of census instantiations
         assert k[".group_segment_fixed_size"] <= (lds if census else 0), name
-        if prefix != "walk3d":
-            assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
-        else:   # kept at four waves per SIMD: a few spilled registers
-            assert k[".private_segment_fixed_size"] <= 48, name
+        # none but the few registers that a kernel held at four waves per SIMD spills
+        held = k[".vgpr_count"] in (127, 128)
+        assert k[".private_segment_fixed_size"] <= (48 if held else 0), name
+
+
+def test_hybrid_walks_keep_their_waves_per_simd():
+    """512 vector registers per SIMD lane, handed out in eights: four waves of the plain walks, three with
+    weights or census estimators, two with both."""
+    for name, k in _walks("walk1dh<"):
+        sphere, single, weights, census = (v == "true" for v in re.findall("true|false", name))
+        waves = 512 // (-(-k[".vgpr_count"] // 8) * 8)
+        assert waves >= 4 - weights - census, name
