@@ -1172,24 +1172,35 @@ __global__ __launch_bounds__(256) void walk1dh_coop(const uint8_t *__restrict__ 
     }
 }
 
-// Lanes whose packets the cooperative walk should take now (0: none).  A side-by-side step costs
-// ~2000 cycles whatever the lanes (a wave or two per SIMD are left by then), a cooperative one
-// ~50-70, and a continuous-MC event ~4000 either way: with a share f of MC events the hand-over pays
-// below (2000 + 4000 f) / (60 + 4000 f) lanes, and never for packets that are mostly in MC states.
+// Whether the cooperative walk should take the n live packets of a wave, of st steps and mc
+// continuous-MC events together.  A side-by-side step costs ~2000 cycles whatever the lanes (a wave or
+// two per SIMD are left by then), a cooperative one ~50-70, and an MC event ~4000 either way: with a share
+// f of MC events the hand-over pays below (2000 + 4000 f) / (60 + 4000 f) lanes.  A packet that leaves for
+// an MC state now and then costs a block and lane 0's steps each time: above f = 1/10 the walk in the lanes
+// is the faster one (slab of 2^18 packets, f = 0.06: 667 ms in the lanes, 638 so; sphere, f = 0.07: 416
+// and 395, f = 0.14: 377 and 417 if handed over).  All live packets go or none, by the wave's own share: the
+// wave goes on for those that stay, and the cooperative walk starts when the last wave has ended.
+// (By each packet's own share, at 1/32, half the packets of a 24 x 40 sphere at f = 0.032 left:
+// 2^17 packets 336 ms, 2^20 737 ms; 275 and 652 without the hand-over; 228 and 600 so.)
 // (At 1000 / 48 the dusty census slab, 16 packets to a wave, took 407 ms: most waves stayed just
 // above the limit.)
+__host__ __device__ constexpr bool coop_pays(float n, float st, float mc)
+{
+    return st >= 64.0f * n && 10.0f * mc < st && n * (60.0f * st + 4000.0f * mc) < 2000.0f * st + 4000.0f * mc;
+}
+static_assert(coop_pays(33, 33e4f, 0) && !coop_pays(34, 34e4f, 0), "pure DDMC packets");
+static_assert(coop_pays(11, 11e4f, 3.5e3f) && !coop_pays(12, 12e4f, 3.84e3f), "an MC event in 31 steps");
+static_assert(!coop_pays(1, 1e4f, 1.1e3f) && !coop_pays(1, 63, 0), "mostly MC, or just emitted");
+
 __device__ __forceinline__ uint64_t hand_over(const Pk1 &p)
 {
-    const bool fit = p.active && p.steps >= 64ull && 32ull * p.mcs < p.steps;
-    const uint64_t m = __ballot(fit);
-    if (!m) return 0ull;
-    float st = fit ? (float)p.steps : 0.0f, mc = fit ? (float)p.mcs : 0.0f;
+    const uint64_t m = __ballot(p.active);
+    float st = p.active ? (float)p.steps : 0.0f, mc = p.active ? (float)p.mcs : 0.0f;
     for (int o = 32; o > 0; o >>= 1) {
         st += __shfl_xor(st, o);
         mc += __shfl_xor(mc, o);
     }
-    const float f = 4000.0f * mc;
-    return (float)__popcll(m) * (60.0f * st + f) < 2000.0f * st + f ? m : 0ull;
+    return coop_pays((float)__popcll(m), st, mc) ? m : 0ull;
 }
 
 // Packet g of the batch's flattened packet space at its source.
