@@ -161,11 +161,22 @@ struct Packet1D {
     uint32_t surr_calls;       // exits taken from the learned surrogate
 };
 
-// The cloud's surrogate window (empty: i_hi < i_lo).
+// The cloud's surrogate window.
 struct SurrWin {
     int i_lo, i_hi, j_lo, j_hi;
     uint64_t rec_off;
 };
+
+// The windows are tested by unsigned differences, in which an empty one (i_hi < i_lo) would hold
+// every state: it becomes one of a cell that no cloud has.
+constexpr SurrWin kNoWindow{0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff, 0ull};
+__device__ __forceinline__ SurrWin surr_window(const uint8_t *__restrict__ surr, int cl)
+{
+    const SurrHeader *SH = reinterpret_cast<const SurrHeader *>(surr);
+    const SurrCloud *c = reinterpret_cast<const SurrCloud *>(surr + SH->off_clouds) + cl;
+    if (c->i_hi < c->i_lo || c->j_hi < c->j_lo) return kNoWindow;
+    return SurrWin{c->i_lo, c->i_hi, c->j_lo, c->j_hi, c->rec_off};
+}
 
 __device__ __forceinline__ bool in_window(const Packet1D &p, const SurrWin &w)
 {
@@ -661,7 +672,7 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
 {
     const SurrHeader *SH = SURR ? reinterpret_cast<const SurrHeader *>(a.surr) : nullptr;
     const float *recs = SURR ? reinterpret_cast<const float *>(a.surr + SH->off_records) : nullptr;
-    SurrWin sw{0, -1, 0, -1, 0ull};
+    SurrWin sw = kNoWindow;
     int last_state = 0;
     const DevHeader *H = reinterpret_cast<const DevHeader *>(tb);
     const DevCloud *clouds = reinterpret_cast<const DevCloud *>(tb + H->off_clouds);
@@ -721,10 +732,7 @@ __global__ __launch_bounds__(256) void walk1d(const uint8_t *__restrict__ tb, Wa
                         p.steps = 0;
                         p.active = true;
                         p.surr_calls = 0u;
-                        if (SURR) {
-                            const SurrCloud *scl = reinterpret_cast<const SurrCloud *>(a.surr + SH->off_clouds) + lo;
-                            sw = SurrWin{scl->i_lo, scl->i_hi, scl->j_lo, scl->j_hi, scl->rec_off};
-                        }
+                        if (SURR) sw = surr_window(a.surr, lo);
                         atomicAdd(&tally[c.tally_off + TW_LAUNCHED], 1ull);
                     }
                 }
@@ -1086,13 +1094,12 @@ __device__ int coop_walk(Packet1D &q, const uint8_t *__restrict__ tb, const DevC
     // the cloud's surrogate window: a step that starts in it is replaced by one exit, at the
     // same points as in the lane walk (every step in moving media, even step counts in
     // static media, and only with room for three more steps)
-    SurrWin sw{0, -1, 0, -1, 0ull};
+    SurrWin sw = kNoWindow;
     const float *recs = nullptr;
     if (SURR) {
         const SurrHeader *SH = reinterpret_cast<const SurrHeader *>(a.surr);
         recs = reinterpret_cast<const float *>(a.surr + SH->off_records);
-        const SurrCloud *scl = reinterpret_cast<const SurrCloud *>(a.surr + SH->off_clouds) + q.cl;
-        sw = SurrWin{scl->i_lo, scl->i_hi, scl->j_lo, scl->j_hi, scl->rec_off};
+        sw = surr_window(a.surr, q.cl);
     }
     int wi = -1, jb = 0;
     int short_run = 0;   // consecutive table blocks stopped by a slow-path step within 16 steps
