@@ -26,7 +26,7 @@ struct McArgs {
     int32_t chunk, n_clouds;
     uint32_t dom;
     int32_t lanes;     // lanes of a wave that take packets
-    int32_t one_round; // there is a lane for every packet: the queue is empty after one refill
+    int32_t one_round; // the queue is empty after one refill
     uint64_t slots;    // export slots for the cooperative walk (0: it takes no packets)
 };
 

@@ -37,7 +37,7 @@ struct WalkArgs {
     int32_t n_clouds;
     int32_t tail_lanes;    // export a wave's packets once the queue is empty and <= this many remain
     int32_t ahead;         // few waves per SIMD: records are fetched ahead of the step that needs them
-    int32_t one_round;     // the producers have a lane for every packet: the queue is empty after one refill
+    int32_t one_round;     // the queue is empty after one refill
     uint64_t tail_capacity;
     const uint8_t *surr;   // learned escape surrogate (windows and records) or null
     uint32_t producer_blocks;   // blocks [0, producer_blocks) walk packets from the queue;
@@ -1518,7 +1518,7 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
         a.tail_lanes = waves >= 2 * simds ? 8 : 16;
         a.share = waves < simds ? (int)(4 * (simds - waves)) : 0;
     }
-    a.one_round = lanes >= count ? 1 : 0;
+    a.one_round = queue_in_one_round(grid * (uint64_t)(block / 64), 64, count, (uint64_t)device_cu_count()) ? 1 : 0;
     a.ahead = (lanes + 63) / 64 <= 8ull * (uint64_t)device_cu_count() ? 1 : 0;
     if (a.tail_lanes > 0 && (lanes < count ? lanes : count) > a.tail_capacity) {
         // every exported packet (at most one per lane, at most `count`) needs a slot
@@ -1527,7 +1527,7 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
             grid = 1;
             a.tail_lanes = 0;
         }
-        a.one_round = grid * (uint64_t)block >= count ? 1 : 0;
+        a.one_round = queue_in_one_round(grid * (uint64_t)(block / 64), 64, count, (uint64_t)device_cu_count()) ? 1 : 0;
     }
     bool moving = false;
     for (int c = 0; c < h.n_clouds; ++c) moving |= host_clouds[c].moving != 0;

@@ -1578,7 +1578,7 @@ hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_
         grid = want < cap ? want : cap;
         if (grid < 1) grid = 1;
     }
-    a.one_round = grid * (uint64_t)(block / 64) * (uint64_t)a.lanes >= count ? 1 : 0;
+    a.one_round = queue_in_one_round(grid * (uint64_t)(block / 64), (uint64_t)a.lanes, count, (uint64_t)device_cu_count()) ? 1 : 0;
     reset_queue1<<<1, 64, 0, s>>>(d_work);
     const bool sph = h.geometry == RDDMC_SPHERE;
     const bool single = h.n_clouds == 1;

@@ -814,7 +814,7 @@ hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddm
         grid = want < cap ? want : cap;
         if (grid < 1) grid = 1;
     }
-    a.one_round = grid * (uint64_t)(block / 64) * (uint64_t)a.lanes >= count ? 1 : 0;
+    a.one_round = queue_in_one_round(grid * (uint64_t)(block / 64), (uint64_t)a.lanes, count, (uint64_t)device_cu_count()) ? 1 : 0;
     reset_queue<<<1, 64, 0, s>>>(d_work);
     if (h.n_clouds == 1)
         walk3d<true><<<(unsigned)grid, block, 0, s>>>(d_tables, a, d_tally, d_work);
