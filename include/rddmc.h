@@ -195,7 +195,8 @@ typedef struct {
  *                advances one packet (0 = automatic: 16, 8 where several waves share a SIMD,
  *                and in runs too small to occupy the device as soon as waves are free to take
  *                packets; < 0 = never).  The hybrid walks decide by the packets'
- *                shares of events when it is not negative.  Results are
+ *                shares of events when it is not negative; 3D batches with a cloud of
+ *                tau_threshold = 0 hand over nothing.  Results are
  *                bit-identical either way.
  *   surrogate    1D clouds: learned escape surrogate (rddmc_surrogate_attach), exact exit
  *                kernel (rddmc_exitkernel_build) or NULL for plain rDDMC; with one, a packet

@@ -574,7 +574,9 @@ rddmc_status rddmc_transport(const rddmc_batch *batch, const void *d_tables, con
     if (count > total - run->first) return fail(RDDMC_EINVAL, "first + count beyond the batch's packets");
     if (count == 0) return RDDMC_OK;
     if (L.h.geometry == RDDMC_CART3D) {
-        hipError_t e = launch_walk3d(static_cast<const uint8_t *>(d_tables), L.h, *run, run->first, count,
+        bool any_pure = false;
+        for (const DevCloud &c : L.clouds) any_pure |= !(c.tau_th > 0.0);
+        hipError_t e = launch_walk3d(static_cast<const uint8_t *>(d_tables), L.h, any_pure, *run, run->first, count,
                                      static_cast<unsigned long long *>(d_tally),
                                      static_cast<unsigned long long *>(d_work), work_bytes,
                                      reinterpret_cast<hipStream_t>(stream));

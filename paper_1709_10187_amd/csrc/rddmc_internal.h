@@ -167,7 +167,7 @@ hipError_t mdn_loss_grad(void *d_params, void *d_work, int64_t cap, const float 
 hipError_t mdn_adam(void *d_params, int64_t step, float lr, hipStream_t s);
 hipError_t launch_build_redistribution(const DevCloud &c, uint8_t *d_tables, hipStream_t s);
 hipError_t launch_build_line_tables(const DevHeader &h, uint8_t *d_tables, hipStream_t s);
-hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, const rddmc_run &run, uint64_t first,
+hipError_t launch_walk3d(const uint8_t *d_tables, const DevHeader &h, bool any_pure, const rddmc_run &run, uint64_t first,
                          uint64_t count, unsigned long long *d_tally, unsigned long long *d_work, uint64_t work_bytes,
                          hipStream_t s);
 hipError_t launch_walk1dh(const uint8_t *d_tables, const DevHeader &h, bool any_thick, bool all_groups, const rddmc_run &run,

@@ -67,3 +67,18 @@ def test_steps_between_refills_do_not_change_the_bits(chunk):
     meds = CASES["moving"]
     print(f"[3D tail] chunk {chunk}", flush=True)
     _same(_run(meds, tail_lanes=-1), _run(meds, chunk=chunk))
+
+
+def test_batches_that_leak_or_scatter_stay_in_the_lanes():
+    """No hand-over (counted in the work area) in a batch with a cloud that is diffusive in every state, and
+    none from waves with many continuous-MC events; packets of thick clouds are handed over."""
+    given = {}
+    for name in ("pure", "thin", "moving"):
+        p = rddmc.Problem(CASES[name])
+        p.run(seed=17)
+        given[name] = int(p.work[8])
+    mixed = rddmc.Problem(CASES["moving"] + CASES["pure"])
+    mixed.run(seed=17)
+    print(f"[3D tail] handed over {given}", flush=True)
+    assert given["pure"] == 0 and given["thin"] == 0 and int(mixed.work[8]) == 0
+    assert given["moving"] > 0
