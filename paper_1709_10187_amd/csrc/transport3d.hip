@@ -615,6 +615,13 @@ __host__ __device__ constexpr bool coop_pays(int pd, int pl, int pm, int wd, int
 static_assert(!coop_pays(0, 2 * kMaxPasses, 0, 0, 128 * kMaxPasses, 0) && !coop_pays(0, 0, 2 * kMaxPasses, 0, 0, 128 * kMaxPasses));
 static_assert(!coop_pays(2 * kMaxPasses, 0, 0, 256 * kMaxPasses - 1, 0, 0) && coop_pays(2 * kMaxPasses, 0, 0, 4 * kMaxPasses, 0, 0));
 
+// ... and whether it will go on paying: packets do not come back, and the cooperative walk starts when the
+// last wave has ended.  Above one MC event in sixteen of all that the wave has walked (d DDMC steps, m MC
+// events), a packet's last stretch, out of the thick states, is the lanes' work (8.8e5 packets of a 26^3 cube
+// at a share of 0.39: 402 ms with the recent passes alone asked, 324 so, 363 without any hand-over before).
+__host__ __device__ constexpr bool stays_ddmc(uint32_t d, uint32_t m) { return m <= d / 16u; }
+static_assert(stays_ddmc(1600, 100) && !stays_ddmc(1600, 101) && stays_ddmc(0, 0));
+
 template <bool SINGLE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void walk3d(const uint8_t *__restrict__ tb, Walk3Args a,
                                               unsigned long long *__restrict__ tally,
@@ -639,6 +646,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
     p.r = Rng{0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 4u, false, 0u, 0u, 0u, 0u};
     bool exhausted = false;
     int pd = 0, pl = 0, pm = 0, wd = 0, wl = 0, wm = 0;   // recent passes and their lanes, by kind
+    uint32_t all_d = 0u, all_m = 0u;                      // DDMC steps and MC events of the wave so far
 
     for (;;) {
         if (!exhausted) {
@@ -702,7 +710,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
         if (!__any(p.active)) break;
 
         // hand the wave's packets over to the cooperative walk
-        if (a.slots && exhausted && coop_pays(pd, pl, pm, wd, wl, wm)) {
+        if (a.slots && exhausted && coop_pays(pd, pl, pm, wd, wl, wm) && stays_ddmc(all_d, all_m)) {
             const uint64_t go = __ballot(p.active);
             const int leader = __ffsll((unsigned long long)go) - 1;
             uint64_t base = 0;
@@ -735,6 +743,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
             if (!__any(p.active)) continue;   // (packets that found no slot walk on here)
         }
         pd >>= 1; pl >>= 1; pm >>= 1; wd >>= 1; wl >>= 1; wm >>= 1;
+        if ((all_d | all_m) >> 30) {
+            all_d >>= 1;
+            all_m >>= 1;
+        }
 
         // Event-batched passes: a pass advances the wave's DDMC lanes by up to two steps, or
         // applies the spatial leaks its DDMC steps chose, or advances its continuous-MC lanes
@@ -762,6 +774,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void w
                              : (nl > 0 && (16 * nl >= nd || (k & 31) == 31 || nd == 0)) ? 1 : 0;
             pd += mode == 0 ? 1 : 0; pl += mode == 1 ? 1 : 0; pm += mode == 2 ? 1 : 0;
             wd += mode == 0 ? 2 * nd : 0; wl += mode == 1 ? nl : 0; wm += mode == 2 ? nm : 0;
+            all_d += mode == 0 ? 2 * nd : 0; all_m += mode == 2 ? nm : 0;
             if (p.active && (mode == 2 ? p.mc : (mode == 1 ? p.pend : !p.mc && !p.pend))) {
                 if (mode == 2) {
                     prefetch(p.r, a);
