@@ -192,7 +192,7 @@ typedef struct {
  *   chunk        steps between refills of finished lanes (0 = automatic).
  *   tail_lanes   once every packet of the run has started, a wave with at most this many
  *                packets left hands them to a cooperative walk in which a whole wave
- *                advances one packet (0 = automatic: 16, 8 where several waves share a SIMD,
+ *                advances one packet (0 = automatic: 16, 12 or 8 where waves share a SIMD,
  *                and in runs too small to occupy the device as soon as waves are free to take
  *                packets; < 0 = never).  The hybrid walks decide by the packets'
  *                shares of events when it is not negative; 3D batches with a cloud of

@@ -1515,7 +1515,7 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
         // slab, 256 producer waves, with the table blocks of that time: 626 ms, 1006 at 16 alone, 675 at
         // 64 per wave; 530 ms with the present ones).
         const uint64_t simds = 4ull * (uint64_t)device_cu_count(), waves = (lanes + 63) / 64;
-        a.tail_lanes = waves >= 2 * simds ? 8 : 16;
+        a.tail_lanes = waves >= 4 * simds ? 8 : (waves >= 2 * simds ? 12 : 16);
         a.share = waves < simds ? (int)(4 * (simds - waves)) : 0;
     }
     a.one_round = queue_in_one_round(grid * (uint64_t)(block / 64), 64, count, (uint64_t)device_cu_count()) ? 1 : 0;
