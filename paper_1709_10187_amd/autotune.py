@@ -6,9 +6,13 @@ Two phases:
     the work per packet, so the trial measures the schedule's steps/s), timed with device
     events on their own tally and work buffers;
   * tail: with the fastest bulk schedule, each candidate hand-over threshold of the cooperative
-    tail walk (``tail_lanes``) walks a per-cloud sample of the batch WHOLE (every packet to
-    escape, or to a generous step cap) in one launch; the shortest launch wins.  A launch of
-    a tail-bound workload ends with its slowest packets, which the bulk phase cannot see.
+    tail walk (``tail_lanes``; 0 is the automatic hand-over) walks a per-cloud sample of the
+    batch WHOLE (every packet to escape, or to a generous step cap) in one launch; the shortest
+    launch wins.  A launch of a tail-bound workload ends with its slowest packets, which the
+    bulk phase cannot see.
+The all-automatic schedule (0, 0, 0) is among the default candidates and walks the whole sample
+too where another is the fastest in bulk: a fixed grid keeps small jobs from being spread over
+the device, so it wins where it ends first and its bulk rate is within 5 % of the fastest.
 The result is remembered per batch signature for the process.
 
 ``pilot_costs`` / ``longest_first``: a short pilot walk of every cloud gives its mean steps per
@@ -33,13 +37,20 @@ def signature(batch: rddmc.Batch) -> tuple:
 
 
 def default_candidates(n_cu: int) -> Iterable[Tuple[int, int, int]]:
+    yield 0, 0, 0
     for block, per_cu, chunk in itertools.product((64, 128, 256), (2, 4, 8), (32, 128)):
         yield block, per_cu * n_cu * (256 // block), chunk
 
 
+def prefers_automatic(auto_ms: float, auto_rate: float, tuned_ms: float, tuned_rate: float) -> bool:
+    """Whether the all-automatic schedule is taken: the whole walk ends first and the bulk rate is
+    within 5 % of the tuned schedule's."""
+    return auto_ms < tuned_ms and auto_rate >= 0.95 * tuned_rate
+
+
 def tune(problem: "rddmc.Problem", sample_packets: int = 1 << 18, trial_steps: int = 20000,
          candidates: Optional[Iterable[Tuple[int, int, int]]] = None, seed: int = 0,
-         use_cache: bool = True, tail_candidates: Iterable[int] = (16, -1, 8, 32),
+         use_cache: bool = True, tail_candidates: Iterable[int] = (0, 16, -1, 8, 32),
          tail_packets_per_cloud: int = 64, tail_max_steps: int = 1 << 26) -> dict:
     import torch
     b = problem.batch
@@ -73,16 +84,25 @@ def tune(problem: "rddmc.Problem", sample_packets: int = 1 << 18, trial_steps: i
         # a per-cloud sample of the batch, walked whole: tables of the same clouds with fewer packets
         meds = [m.with_packets(min(int(m.n_packets), int(tail_packets_per_cloud))) for m in b.meds]
         sample = rddmc.Problem(meds, streams=list(b.streams))
-        for tl in tails:
+
+        def whole_walk(tl, s):
             sample.reset()
             start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             start.record(stream)
-            sample.run(seed=seed, max_steps=tail_max_steps, tail_lanes=tl, block=best["block"],
-                       grid=best["grid"], chunk=best["chunk"])
+            sample.run(seed=seed, max_steps=tail_max_steps, tail_lanes=tl, block=s["block"], grid=s["grid"],
+                       chunk=s["chunk"])
             stop.record(stream)
             torch.cuda.synchronize()
-            out["tail_trials"].append({"tail_lanes": tl, "ms": start.elapsed_time(stop)})
-        out["tail_lanes"] = min(out["tail_trials"], key=lambda r: r["ms"])["tail_lanes"]
+            return start.elapsed_time(stop)
+
+        out["tail_trials"] = [{"tail_lanes": tl, "ms": whole_walk(tl, best)} for tl in tails]
+        fastest = min(out["tail_trials"], key=lambda r: r["ms"])
+        out["tail_lanes"] = fastest["tail_lanes"]
+        auto = next((r for r in results if r["block"] == r["grid"] == r["chunk"] == 0), None)
+        if auto is not None and auto is not best:
+            out["automatic_ms"] = whole_walk(0, auto)
+            if prefers_automatic(out["automatic_ms"], auto["steps_per_s"], fastest["ms"], best["steps_per_s"]):
+                out.update(block=0, grid=0, chunk=0, tail_lanes=0, steps_per_s=auto["steps_per_s"])
         del sample
     _CACHE[key] = out
     return out
