@@ -366,7 +366,7 @@ __device__ __forceinline__ void ddmc_step1(Pk1 &p, const DevCloud &c, const uint
     const double t0 = p.t;
     p.t += dl;
     if (WGT && c.dust_weight) {
-        p.lw += ka * dl;
+        p.lw = fma(ka, dl, p.lw);
         if (p.lw > kLogWMin) {   // negligible weight: eliminated
             finish1<WGT, CEN>(p, c, tally, false, 0, 0, true);
             return;
@@ -449,7 +449,7 @@ __device__ __forceinline__ void ddmc_step1(Pk1 &p, const DevCloud &c, const uint
         const double *mp = reinterpret_cast<const double *>(tb + c.off_map) + 3 * (p.cell * 2 + f);
         const double rho = mp[0], sh = mp[1];
         if (rho != 1.0 || sh != 0.0) {
-            xs = (float)(rho * (double)xin + sh);
+            xs = (float)fma(rho, (double)xin, sh);
             const int jn = bin_of(c, tb, xs);
             p.j = jn < 0 ? 0 : (jn > nb - 1 ? nb - 1 : jn);
         }
@@ -499,7 +499,7 @@ __device__ __forceinline__ void mc_step1(Pk1 &p, const DevCloud &c, const uint8_
         census_add<WGT>(p, c, tb, tally, (int64_t)p.cell * c.nb + jc, p.t, p.t + fl, p.lw, (double)m1c.z);
     }
     if (WGT && c.dust_weight) {
-        p.lw += (double)m1c.z * fl;
+        p.lw = fma((double)m1c.z, fl, p.lw);
         if (p.lw > kLogWMin) {   // negligible weight: eliminated
             finish1<WGT, CEN>(p, c, tally, false, 0, 0, true);
             return;
@@ -632,7 +632,7 @@ __device__ __forceinline__ void grp_step1(Pk1 &p, const DevCloud &c, const uint8
     const double fl = (double)fminf(ds, dwall);
     if (CEN && c.n_census > 0) census_add<WGT>(p, c, tb, tally, s, p.t, p.t + fl, p.lw, (double)kd);
     if (WGT && c.dust_weight) {
-        p.lw += (double)kd * fl;
+        p.lw = fma((double)kd, fl, p.lw);
         if (p.lw > kLogWMin) {   // negligible weight: eliminated
             finish1<WGT, CEN>(p, c, tally, false, 0, 0, true);
             return;
@@ -815,7 +815,7 @@ __device__ __forceinline__ void window_step(const Window1 &w, const DevCloud &c,
             const int j = w.wj + (lane & ((1 << w.b) - 1));
             const float xin = fmaf((float)j + uf(rl(wb, K)), c.dx, c.x0);
             const double rho = upper ? w.rho[1] : w.rho[0], sh = upper ? w.sh[1] : w.sh[0];
-            const float x = ((float)(rho * (double)xin + sh) - c.x0) * c.inv_dx;
+            const float x = ((float)fma(rho, (double)xin, sh) - c.x0) * c.inv_dx;
             int jn = !(x >= 0.0f) ? 0 : (x >= (float)(c.nb - 1) ? c.nb - 1 : (int)x);
             if (rho == 1.0 && sh == 0.0) jn = j;
             const int to = nf + (jn - j);
