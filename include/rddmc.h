@@ -470,8 +470,8 @@ rddmc_status rddmc_surrogate_samples(const rddmc_batch *batch, const void *d_tab
                                      void *d_scratch, size_t scratch_bytes, float *d_x, float *d_y,
                                      uint64_t *d_steps, void *stream);
 
-/* Bytes of the surrogate buffer for a batch (windows, staging for max_batch states, one
- * 512-byte sampling record per window state) and the number of window states. */
+/* Bytes of the surrogate buffer for a batch (windows, one 512-byte sampling record per window
+ * state) and the number of window states.  max_batch in [1, 2^24] does not change them. */
 rddmc_status rddmc_surrogate_bytes(const rddmc_batch *batch, const rddmc_surrogate_cfg *cfg, int64_t max_batch,
                                    size_t *bytes, uint64_t *n_states);
 
@@ -480,9 +480,9 @@ rddmc_status rddmc_surrogate_bytes(const rddmc_batch *batch, const rddmc_surroga
 rddmc_status rddmc_surrogate_window(const rddmc_batch *batch, const rddmc_surrogate_cfg *cfg, int32_t cloud,
                                     int32_t *window);
 
-/* Evaluate the network (rddmc_mdn_*) on every window state in batches of max_batch (BF16
- * matrix cores) and store the sampling records in d_surr (>= rddmc_surrogate_bytes,
- * 256-byte aligned); pass d_surr as rddmc_run.surrogate.  Synchronises.
+/* Evaluate the network (rddmc_mdn_*) on every window state (BF16 matrix cores, one launch) and
+ * store the sampling records in d_surr (>= rddmc_surrogate_bytes, 256-byte aligned); pass d_surr
+ * as rddmc_run.surrogate.  d_work, the network's work buffer, is not written.  Synchronises.
  * Errors: EINVAL, ESIZE, EHIP. */
 rddmc_status rddmc_surrogate_attach(const rddmc_batch *batch, const void *d_tables, void *d_params, void *d_work,
                                     int64_t max_batch, const rddmc_surrogate_cfg *cfg, void *d_surr, size_t bytes,

@@ -806,7 +806,7 @@ SurrCloud surrogate_window(const rddmc_medium &m, const rddmc_surrogate_cfg &cfg
 struct SurrLayout {
     SurrHeader h{};
     std::vector<SurrCloud> clouds;
-    uint64_t off_x = 0, off_sw = 0, bytes = 0;
+    uint64_t bytes = 0;
 };
 
 rddmc_status surrogate_layout(const rddmc_batch *b, const rddmc_surrogate_cfg *cfg, int64_t max_batch,
@@ -827,15 +827,10 @@ rddmc_status surrogate_layout(const rddmc_batch *b, const rddmc_surrogate_cfg *c
         if (w.i_hi >= w.i_lo) rec += (uint64_t)(w.i_hi - w.i_lo + 1) * (w.j_hi - w.j_lo + 1);
         S.clouds[c] = w;
     }
-    const int64_t cap = (max_batch + 31) & ~31ll;
     uint64_t off = align_up(sizeof(SurrHeader));
     S.h.n_clouds = n;
     S.h.off_clouds = off;
     off = align_up(off + sizeof(SurrCloud) * n);
-    S.off_x = off;
-    off = align_up(off + 4ull * kSurrIn * cap);
-    S.off_sw = off;
-    off = align_up(off + 8ull * cap);
     S.h.off_records = off;
     S.h.n_records = rec;
     S.bytes = off + 4ull * kSurrRec * rec;
@@ -881,7 +876,7 @@ rddmc_status rddmc_surrogate_attach(const rddmc_batch *batch, const void *d_tabl
     if (bytes < S.bytes) return fail(RDDMC_ESIZE, "surrogate buffer %zu < required %llu", bytes,
                                      (unsigned long long)S.bytes);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    std::vector<uint8_t> hdr(S.off_x, 0);
+    std::vector<uint8_t> hdr(S.h.off_records, 0);
     std::memcpy(hdr.data(), &S.h, sizeof S.h);
     std::memcpy(hdr.data() + S.h.off_clouds, S.clouds.data(), sizeof(SurrCloud) * S.clouds.size());
     uint8_t *base = static_cast<uint8_t *>(d_surr);
