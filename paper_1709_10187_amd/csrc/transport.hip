@@ -19,6 +19,8 @@
 // tallies with device atomics; results depend only on (seed, cloud, packet id).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "philox.h"
 #include "rddmc_internal.h"
 #include "surrogate_dev.h"
@@ -1489,7 +1491,8 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
     a.max_steps = run.max_steps;
     a.key0 = (uint32_t)run.seed;
     a.key1 = (uint32_t)(run.seed >> 32);
-    a.chunk = run.chunk > 0 ? (run.chunk + 1) / 2 : 32;   // in pairs of steps
+    // in pairs of steps; bounded, so that neither the pairs of the largest chunk nor their steps leave an int
+    a.chunk = run.chunk > 0 ? (int)((std::min<int64_t>(run.chunk, 1 << 21) + 1) / 2) : 32;
     a.n_clouds = h.n_clouds;
     a.tail_lanes = run.tail_lanes < 0 ? 0 : run.tail_lanes;
     a.tail_capacity = work_bytes > kWorkHeaderBytes ? (work_bytes - kWorkHeaderBytes) / sizeof(TailPacket) : 0;
