@@ -337,10 +337,17 @@ rddmc_status make_layout(const rddmc_batch *b, Layout &L)
         c.off_census = c.n_census > 0 ? take(8ull * (c.n_census + 1)) : 0;
         c.groups = (m.flags & RDDMC_FLAG_GROUPS) ? 1 : 0;
         c.dust_weight = (m.flags & RDDMC_FLAG_DUST_WEIGHT) ? 1 : 0;
-        if (hybrid1d)
-            for (int i = 0; i < c.nc && !c.any_thick; ++i)
-                c.any_thick = (m.k0[i] + (m.dust_sca ? m.dust_sca[i] : 0.0)) * (m.faces[0][i + 1] - m.faces[0][i]) >=
-                              m.tau_threshold * (1.0 - 1e-6) ? 1 : 0;
+        if (hybrid1d) {
+            // H(a, x) <= 1 + a^2 (eq. 12's expansion, above 1 in gas colder than 2 mK); the average over a
+            // narrow bin is a difference of integrals of order 1 + a^2, rounded
+            double dx = m.bin_edges[m.n_bins] - m.bin_edges[0];
+            for (int j = 0; j < m.n_bins; ++j) dx = std::min(dx, m.bin_edges[j + 1] - m.bin_edges[j]);
+            for (int i = 0; i < c.nc && !c.any_thick; ++i) {
+                const double a = 4.702e-4 * std::sqrt(1.0e4 / m.temp[i]);   // Sec. 2.1
+                const double kmax = m.k0[i] * (1.0 + a * a) * (1.0 + 1e-6 + 1e-14 / dx) + (m.dust_sca ? m.dust_sca[i] : 0.0);
+                c.any_thick = kmax * (m.faces[0][i + 1] - m.faces[0][i]) >= m.tau_threshold * (1.0 - 1e-6) ? 1 : 0;
+            }
+        }
         if (c.dust_weight) L.h.dust_weight1d = 1u;
         if (m.n_census > 0) L.h.census1d = 1u;
         c.off_grp_prob = c.groups ? take(8ull * c.nb * c.nb) : 0;

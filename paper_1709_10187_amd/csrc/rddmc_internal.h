@@ -111,7 +111,7 @@ struct alignas(16) DevCloud {
     int32_t groups;              // thin states carry a frequency group (Sec. 5.3)
     int32_t dust_weight;         // dust absorption by continuous weights (Sec. 2.4)
     int32_t any_thick;           // 1D hybrid: a state can be thick (the threshold is not above every cell's
-                                 //   line-centre width; H(a, x) <= 1)
+                                 //   depth at the largest H(a, x) that eq. 12 gives, 1 + a^2)
     int32_t pad1;
     uint64_t wspec_off;          // (dust_weight) int64 word offset in the cloud's tally block:
                                  //   sum w t (128-bit, 2^-32 units), sum w t^2 (128-bit, 2^-20
