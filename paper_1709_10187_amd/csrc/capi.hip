@@ -230,6 +230,9 @@ rddmc_status make_layout(const rddmc_batch *b, Layout &L)
                 if (m.vel[i] != 0.0) c.moving = 1;
         }
         L.any_moving |= c.moving != 0;
+        c.rebins = c.moving != 0;
+        for (int i = 1; i < c.nc; ++i)
+            if (m.temp[i] != m.temp[0]) c.rebins = 1u;
         c.n_packets = m.n_packets;
         c.stream = m.stream;
         c.packet_base = L.prefix[ci];

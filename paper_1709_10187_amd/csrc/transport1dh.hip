@@ -443,9 +443,11 @@ __device__ __forceinline__ void ddmc_step1(Pk1 &p, const DevCloud &c, const uint
         ++p.tomc;
         return;
     }
-    // thick neighbour (vacuum faces always carry the interface bit)
+    // thick neighbour (vacuum faces always carry the interface bit); re-binned wherever the face's map
+    // is not the identity, as the face flags and rates were built: in bin j itself the neighbour may
+    // be thin, and its record empty
     float xs = xin;
-    if (c.moving) {
+    if (c.rebins) {
         const double *mp = reinterpret_cast<const double *>(tb + c.off_map) + 3 * (p.cell * 2 + f);
         const double rho = mp[0], sh = mp[1];
         if (rho != 1.0 || sh != 0.0) {
@@ -456,7 +458,7 @@ __device__ __forceinline__ void ddmc_step1(Pk1 &p, const DevCloud &c, const uint
     }
     p.cell = nbc;
     bool ddmc_in = true;
-    if (c.moving) {
+    if (c.rebins) {
         const uint4 rn = reinterpret_cast<const uint4 *>(tb + c.off_hot)[(int64_t)p.cell * nb + p.j];
         if (!(rn.w & kFlagThick)) {   // re-binned into a thin state: MC in the new cell
             p.pos = cell_point<SPH>(fz, p.cell, p.r, a);
@@ -732,8 +734,8 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
 // and a second {face, x} if its event is a spatial leak: a position with bit 6 set waits for its
 // face pair.  Lane 63 is the stop: moves out of the window lead to it (the step is completed after
 // the chain), and so do the steps a block does not take: ties, leaks into thin states or vacuum,
-// dust absorption, spatial leaks of a moving cloud on a non-uniform grid or out of the window, and a
-// residence that crosses a census time.
+// dust absorption, spatial leaks of a cloud that re-bins on a non-uniform grid or out of the
+// window, and a residence that crosses a census time.
 // Those run in lane 0 with the step functions above, as do the continuous-MC events that follow
 // a conversion, until the packet is in a DDMC state again.  The clock is that of the cooperative
 // walk of pure clouds, census sums are integers: results do not depend on who walks a packet.
@@ -742,7 +744,7 @@ struct Window1 {
     uint32_t lk, dhi, shi, ahi, split, flags;
     int dn, up, lo, hi, pend;             // where the events lead (63: stop)
     double ka;                            // continuous dust weights: absorption of the lane's cell
-    double rho[2], sh[2];                 // moving clouds: eq. 20 across the faces of the lane's cell
+    double rho[2], sh[2];                 // clouds that re-bin: eq. 20 across the faces of the lane's cell
 };
 
 constexpr int kPend = 64;                 // position bit: the face pair comes next
@@ -793,8 +795,8 @@ __device__ __forceinline__ void window_load(Window1 &w, const Pk1 &q, const DevC
     w.lo = live && il > 0 && !(r.w & (1u << kFlagFaceShift)) ? lane - wjn : 63;
     w.hi = live && il < win - 1 && !(r.w & (2u << kFlagFaceShift)) ? lane + wjn : 63;
     // re-binning on non-uniform grids searches the edges: left to lane 0
-    w.pend = live && (!c.moving || c.uniform_bins) ? lane | kPend : 63;
-    if (c.moving) {
+    w.pend = live && (!c.rebins || c.uniform_bins) ? lane | kPend : 63;
+    if (c.rebins) {
         const double *mp = reinterpret_cast<const double *>(tb + c.off_map) + 6 * (in ? wi + il : 0);
         w.rho[0] = mp[0];
         w.sh[0] = mp[1];
@@ -811,7 +813,7 @@ __device__ __forceinline__ void window_step(const Window1 &w, const DevCloud &c,
     if (p & kPend) {
         const bool upper = (rl(wa, K) >> 1) >= w.split;
         int nf = upper ? w.hi : w.lo;
-        if (c.moving) {   // ddmc_step1's re-binning: x uniform in the bin, moved to the neighbour's frame
+        if (c.rebins) {   // ddmc_step1's re-binning: x uniform in the bin, moved to the neighbour's frame
             const int j = w.wj + (lane & ((1 << w.b) - 1));
             const float xin = fmaf((float)j + uf(rl(wb, K)), c.dx, c.x0);
             const double rho = upper ? w.rho[1] : w.rho[0], sh = upper ? w.sh[1] : w.sh[0];
@@ -822,7 +824,7 @@ __device__ __forceinline__ void window_step(const Window1 &w, const DevCloud &c,
             nf = nf == 63 || (unsigned)(jn - w.wj) >= (1u << w.b) ? 63 : to;
         }
         p = (int)rl((uint32_t)nf, p & 63);
-        if (c.moving && !(rl(w.flags, p) & kFlagThick)) p = 63;   // into a thin state: lane 0
+        if (c.rebins && !(rl(w.flags, p) & kFlagThick)) p = 63;   // into a thin state: lane 0
     } else {
         const uint32_t e = rl(wb, K);
         const int f = e < w.dhi ? w.dn : w.up;
@@ -913,10 +915,10 @@ __device__ __forceinline__ bool window_block(Pk1 &q, uint64_t &wp, const DevClou
     const int f = (wa >> 1) >= split ? 1 : 0;
     // the first pair a block leaves out: a step lane 0 takes (its event pair, also where its face
     // pair decides it), or the end
-    // (in moving clouds a leak out of the window too: where it ends is not known here)
-    const bool hard = face ? (fl & (1u << (kFlagFaceShift + f))) != 0u || (c.moving && post == 63)
+    // (in clouds that re-bin a leak out of the window too: where it ends is not known here)
+    const bool hard = face ? (fl & (1u << (kFlagFaceShift + f))) != 0u || (c.rebins && post == 63)
                            : (wb == dh || wb == sh ||
-                              (spatial ? wb >= ah || (c.moving && !c.uniform_bins)
+                              (spatial ? wb >= ah || (c.rebins && !c.uniform_bins)
                                        : (fl & (wb < dh ? kFlagDnThin : kFlagUpThin)) != 0u));
     const uint64_t hm = __ballot(hard), fm = __ballot(face);
     uint64_t cutm = (hm & ~fm) | ((hm & fm) >> 1) | (m < 64 ? 1ull << 63 : 0ull);

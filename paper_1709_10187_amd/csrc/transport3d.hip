@@ -289,9 +289,11 @@ __device__ void ddmc_leak(Pk &p, const DevCloud &c, const uint8_t *__restrict__ 
         ++p.tomc;
         return;
     }
-    // thick neighbour (vacuum faces always carry the interface bit)
+    // thick neighbour (vacuum faces always carry the interface bit); re-binned wherever the face's map
+    // is not the identity, as the face flags and rates were built: in bin j itself the neighbour may
+    // be thin, and its record empty
     float xs = xin;
-    if (c.moving) {
+    if (c.rebins) {
         const double *mp = reinterpret_cast<const double *>(tb + c.off_map) + 3 * (p.cell * 6 + f);
         const double rho = mp[0], sh = mp[1];
         if (rho != 1.0 || sh != 0.0) {
@@ -301,7 +303,7 @@ __device__ void ddmc_leak(Pk &p, const DevCloud &c, const uint8_t *__restrict__ 
         }
     }
     enter(p, nix, niy, niz, ncell);
-    if (c.moving) {
+    if (c.rebins) {
         const uint4 rn = reinterpret_cast<const uint4 *>(tb + c.off_hot)[p.cell * nb + p.j];
         if (!(rn.w & kFlagThick)) {   // re-binned into a thin state: MC in the new cell
             p.pos = cell_point(p, c, tb, -1, p.r, a);
