@@ -10,10 +10,11 @@
  *   - time advances by dl / c (c = 1);
  *   - a leak through a vacuum face removes the packet (Sec. 2.3) and its
  *     escape frequency, face and time are tallied;
- *   - with bulk velocity, a leak into a neighbour draws x uniformly in the
- *     bin, shifts it into the neighbour's frame, x' = rho x + shift (Sec. 2.5,
- *     eq. 20), and re-bins it (clamped to the grid's first/last bin); an
- *     escaping packet's lab frequency is x + mu u_n with mu uniform in (0, 1].
+ *   - with bulk velocity or temperatures that differ, a leak into a neighbour
+ *     draws x uniformly in the bin, shifts it into the neighbour's frame,
+ *     x' = rho x + shift (Sec. 2.5, eq. 20), and re-bins it (clamped to the
+ *     grid's first/last bin); with bulk velocity an escaping packet's lab
+ *     frequency is x + mu u_n with mu uniform in (0, 1].
  *
  * Random numbers: one xoshiro256** stream per packet (Blackman & Vigna 2018),
  * its 256-bit state filled by splitmix64 (Steele, Lea & Flood 2014) started
@@ -195,14 +196,12 @@ static void walk_one(const o1_problem *p, uint64_t id, uint64_t seed, uint64_t m
             break;
         }
         int jn = j;
-        if (p->moving) {
-            double rho = p->rho[c * nf + ev], sh = p->shift[c * nf + ev];
-            if (rho != 1.0 || sh != 0.0) {
-                double x = lo + (hi - lo) * xo_open01(&rng);
-                jn = locate(p->edges, nb, rho * x + sh);
-                if (jn < 0) jn = 0;
-                if (jn > nb - 1) jn = nb - 1;
-            }
+        const double rho = p->rho[c * nf + ev], sh = p->shift[c * nf + ev];
+        if (rho != 1.0 || sh != 0.0) {   /* also at rest, where the temperatures differ */
+            double x = lo + (hi - lo) * xo_open01(&rng);
+            jn = locate(p->edges, nb, rho * x + sh);
+            if (jn < 0) jn = 0;
+            if (jn > nb - 1) jn = nb - 1;
         }
         s = n * nb + jn;
     }

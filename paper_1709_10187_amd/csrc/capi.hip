@@ -923,7 +923,7 @@ rddmc_status rddmc_surrogate_samples(const rddmc_batch *batch, const void *d_tab
         if (h_state[q] < 0 || (uint64_t)h_state[q] >= dc.n_states || i < 1 || i > dc.nc - 2)
             return fail(RDDMC_EINVAL, "sample %lld: the start state must lie in a cell with two neighbours",
                         (long long)q);
-        moving |= dc.moving != 0;
+        moving |= dc.rebins != 0u;
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     int32_t *dc = static_cast<int32_t *>(d_scratch);

@@ -72,7 +72,7 @@ struct alignas(16) DevCloud {
     int32_t n_src, keep_rates, n_rows, dirichlet;
     uint32_t stream;
     uint32_t rebins;             // some face map is not the identity (bulk velocity, or temperatures that
-                                 // differ): the hybrid and 3D walks re-bin a leak between thick cells
+                                 // differ): the walks re-bin a leak between thick cells
     uint64_t n_packets;
     uint64_t packet_base;        // flattened index of this cloud's first packet
     uint64_t n_states;

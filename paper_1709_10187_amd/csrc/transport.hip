@@ -158,7 +158,8 @@ struct Packet1D {
     const float4 *cmap;        // per-cell Doppler maps {rho0, shift0, rho1, shift1}
     float x0, dx, inv_dx;      // uniform bin grid
     bool uniform;
-    bool moving;               // the cloud has bulk velocity (one Philox block per step)
+    bool moving;               // the cloud re-bins: bulk velocity or temperatures that differ (one
+                               // Philox block per step)
     bool active;
     uint32_t surr_calls;       // exits taken from the learned surrogate
 };
@@ -239,7 +240,7 @@ __device__ __forceinline__ void mdn_exit(Packet1D &p, const SurrWin &sw, const f
 }
 
 // Random words of one step.  Static clouds: one Philox block serves two steps (time and
-// event words); moving clouds: one block per step (time, event, re-binning, escape mu).
+// event words); clouds that re-bin: one block per step (time, event, re-binning, escape mu).
 // The layout is a property of the cloud, so a cloud's packets draw the same numbers in
 // whichever kernel variant walks them.
 struct StepWords {
@@ -595,7 +596,7 @@ __device__ __forceinline__ void set_cloud(Packet1D &p, const uint8_t *__restrict
     p.dx = c.dx;
     p.inv_dx = c.inv_dx;
     p.uniform = c.uniform_bins != 0;
-    p.moving = c.moving != 0;
+    p.moving = c.rebins != 0u;
 }
 
 // The packet of an export slot as a wave-uniform state.
@@ -1533,7 +1534,7 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
         a.one_round = queue_in_one_round(grid * (uint64_t)(block / 64), 64, count, (uint64_t)device_cu_count()) ? 1 : 0;
     }
     bool moving = false;
-    for (int c = 0; c < h.n_clouds; ++c) moving |= host_clouds[c].moving != 0;
+    for (int c = 0; c < h.n_clouds; ++c) moving |= host_clouds[c].rebins != 0u;
     a.surr = static_cast<const uint8_t *>(run.surrogate);
     a.producer_blocks = (uint32_t)grid;
     a.producer_waves = (uint32_t)(grid * (uint64_t)(block / 64));

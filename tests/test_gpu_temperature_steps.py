@@ -7,7 +7,7 @@ import math
 import numpy as np
 import pytest
 
-from oracle import chain, tables, walk1dh, walk3d
+from oracle import chain, tables, walk, walk1dh, walk3d
 from paper_1709_10187_amd import media, rddmc
 from tests._stats import assert_spectrum_matches, compare_exact, compare_two_samples
 
@@ -67,6 +67,45 @@ def test_pure_3d_walk_matches_exact_chain():
     assert_spectrum_matches(r, l1_max=max(0.01, 2.5 * r["expected_noise_L1"]))
     assert abs(g.steps_mean - ref.steps) < 4 * math.sqrt(ref.steps_var / n)
     assert abs(g.t_mean - ref.t_mean) < 4 * math.sqrt(ref.t_var / n)
+
+
+_TWO = 1e4 * np.where(np.arange(9) % 3 == 0, 4.0, 1.0)
+_EP = np.sort(np.concatenate([np.random.default_rng(5).uniform(-3.0, 3.0, 20), [-3.0, 3.0]]))
+PURE = {
+    "slab": media.slab(300.0, 1e4, 9, 24, x_max=3.0).replace(temp=_TWO),
+    "slab_other_grid": media.slab(300.0, 1e4, 9, 21, x_max=3.0).replace(temp=_TWO, bin_edges=_EP),
+    "sphere": media.sphere(500.0, 1e4, 9, 24, x_max=3.0).replace(temp=_TWO),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PURE))
+def test_pure_oracle_walker_matches_exact_chain(name):
+    m, n = PURE[name], 10000
+    ref, o = chain.solve(m), walk.run(m, n_packets=n, seed=3)
+    r = compare_exact(o.spectrum, ref.spectrum, n)
+    assert_spectrum_matches(r, l1_max=2.5 * r["expected_noise_L1"])
+    assert abs(o.steps_mean - ref.steps) < 4 * math.sqrt(ref.steps_var / n)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(PURE))
+def test_pure_1d_walk_matches_exact_chain(name):
+    m, n = PURE[name], 100000
+    ref, g = chain.solve(m), _run(m, n)
+    assert g.escaped == n
+    r = compare_exact(g.spectrum, ref.spectrum, n)
+    assert_spectrum_matches(r, l1_max=max(0.01, 2.5 * r["expected_noise_L1"]))
+    assert abs(g.steps_mean - ref.steps) < 4 * math.sqrt(ref.steps_var / n)
+    assert abs(g.t_mean - ref.t_mean) < 4 * math.sqrt(ref.t_var / n)
+    # lanes alone, and beside a cloud without steps: the same packets
+    for meds, kw in (([m], dict(tail_lanes=-1)), ([m, media.slab(300.0, 1e4, 9, 24, x_max=3.0)
+                                                   if m.geometry == media.SLAB else
+                                                   media.sphere(500.0, 1e4, 9, 24, x_max=3.0)], {})):
+        p = rddmc.Problem([q.with_packets(3000) for q in meds])
+        p.run(seed=3, **kw)
+        a, b = p.results()[0], _run(m, 3000)
+        np.testing.assert_array_equal(a.spectrum, b.spectrum)
+        assert (a.steps_total, a.t_mean) == (b.steps_total, b.t_mean)
 
 
 @pytest.mark.gpu
