@@ -447,7 +447,7 @@ __device__ __forceinline__ bool select_step(Packet1D &p, bool en, uint32_t tw, u
 // the wave's other lanes wait for, so lanes due for one wait until they are a third of the live
 // ones (or every eighth pass, or nobody else steps).  Which pass takes a packet's exit does not
 // change its steps.  (Exit kernel, tau0 = 1e7 sphere, 2^18 packets: 273 ms with an exit pass
-// whenever a lane is due, 262 ms so.)
+// whenever a lane is due, 262 ms so, both before the present hand-over.)
 __device__ __forceinline__ bool exits_due(bool sx, bool step, int k)
 {
     const uint64_t x = __ballot(sx), o = __ballot(step);
@@ -456,11 +456,12 @@ __device__ __forceinline__ bool exits_due(bool sx, bool step, int k)
 
 // Pairs of static-medium steps: the lanes that step share one masked region per pair, in which the
 // common moves are selects; ties and escapes run under a mask of their own.  Where waves fill the
-// SIMDs, each step's record is gathered when its state is known, one gather a step: the rate of
-// gathers binds before their latency does (2^20 packets of the efficient-grid tau0 = 1e7 sphere:
-// 154 ms with three gathers ahead and a fourth after a spatial move, 109 ms so, with the tail thresholds below).  With AHEAD, for
-// grids of a few waves per SIMD, the neighbouring bins' records are fetched with the pair's first, so
-// that a frequency move does not wait (2^12 packets of the tau0 = 1e5 slab 530 ms, 600 without).
+// SIMDs, each step's record is gathered when its state is known, one gather a step: other waves
+// cover its latency, and gathers ahead cost more than they save (2^20 packets of the efficient-grid
+// tau0 = 1e7 sphere: 154 ms with three gathers ahead and a fourth after a spatial move, 109 ms so, with
+// the tail thresholds below).  With AHEAD, for grids of a few waves per SIMD, the neighbouring bins'
+// records are fetched with the pair's first, so that a frequency move does not wait (2^12 packets of
+// the tau0 = 1e5 slab 530 ms, 600 without).
 // Same records, random words and arithmetic as one_step, so the same bits.
 template <bool MOVING, bool SURR, bool AHEAD>
 __device__ __forceinline__ void static_pairs(Packet1D &p, int budget, int last_state, const uint8_t *__restrict__ tb,
@@ -1512,9 +1513,10 @@ hipError_t launch_walk(const uint8_t *d_tables, const DevHeader &h, const DevClo
     if (run.tail_lanes == 0 && a.tail_capacity > 0) {
         // A SIMD's issue slots take a lane walk one step per live lane in ~500 cycles and a cooperative
         // walk one step in 50-60, however many waves share it: a wave's packets all leave once ten or
-        // so are left.  8 where waves share SIMDs (2^20 packets of the efficient-grid tau0 = 1e7 sphere:
-        // 109 ms, 120 at 16), 16 where each has its own, whose last packets wait on latency (2^16 packets of
-        // moving spheres: 108 ms, 115 at 8).  SIMDs without a producer wave work cooperatively from the start, on
+        // so are left.  8 from four waves per SIMD on (2^20 packets of the efficient-grid tau0 = 1e7 sphere:
+        // 109 ms, 120 at 16), 16 below two, whose last packets wait on latency (2^16 packets of moving
+        // spheres: 108 ms, 115 at 8), 12 between (2^17 packets of a moving 6 x 131 sphere: 279 ms, 326 at 8, 261
+        // at 16; the efficient-grid sphere there 3 % slower than at 8).  SIMDs without a producer wave work cooperatively from the start, on
         // up to four packets each, handed over as consumers become free (2^14 packets of the tau0 = 1e5
         // slab, 256 producer waves, with the table blocks of that time: 626 ms, 1006 at 16 alone, 675 at
         // 64 per wave; 530 ms with the present ones).
